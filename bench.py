@@ -48,9 +48,9 @@ With --workload (c3 included) the line carries that workload only.
 
 Other legs (one JSON line each, not the default):
   --workload c5   batched serving: 64 independent controllers of uneven size
-                  in one step call (persistent work-queue kernel replayed
-                  from a HIP graph, autotuned grid), closed loop through the
-                  host plant; compared with 64 sequential single-controller
+                  in one step call (one workgroup per item of a work list,
+                  replayed from a HIP graph, autotuned order), closed loop
+                  through the host plant; compared with 64 sequential single-controller
                   steps of the same controllers
   --grad          the free-energy gradient dJ/dV on the workload (default
                   c4: K = 4096, T = 50, M = 64): evaluations per second, its

@@ -326,8 +326,8 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params *p, const float *cons
 /* One step of every controller: x0_host n x 4 measured states (finite),
  * step_idx_host n call indices, u0_host NULL or n x 2 (first commands before
  * any shift; the call then waits for the step).  The step is three kernels:
- * per-controller set-up, one persistent rollout launch whose workgroups take
- * (controller, workgroup) items from a queue, and one update launch over every
+ * per-controller set-up, one rollout launch with a workgroup for every item
+ * of a (controller, workgroup) list, and one update launch over every
  * controller's chunks; with the graph on (the default) they are replayed from
  * a HIP graph captured on the first step.  Controller i's results equal those
  * of mppi_step with the same parameters and inputs.  Before writing the inputs
@@ -335,11 +335,10 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params *p, const float *cons
 mppi_status mppi_batch_step(mppi_batch *b, const float *x0_host, const uint32_t *step_idx_host,
                             float *u0_host, void *stream);
 
-/* Picks the persistent grid (workgroups per compute unit, powers of two up to
- * the occupancy limit) and the queue order (0: controller order, 1: longest
- * workgroups first) by timing `trials` steps of each candidate with the last
- * inputs; the mean sequences are restored afterwards.  Writes the choice to
- * the non-NULL outputs. */
+/* Picks the order in which the rollout workgroups start (0: controller order,
+ * 1: longest workgroups first) by timing `trials` steps of each with the last
+ * inputs; the mean sequences are restored afterwards.  Writes the workgroups
+ * that a compute unit holds at once and the order to the non-NULL outputs. */
 mppi_status mppi_batch_autotune(mppi_batch *b, int32_t trials, void *stream, int32_t *wg_per_cu,
                                 int32_t *order);
 
@@ -348,7 +347,7 @@ mppi_status mppi_batch_set_graph(mppi_batch *b, int enable);
 
 /* Kernel timing of batched steps: while enabled, steps launch their three
  * kernels directly (not from the graph; the kernels are the same) with HIP
- * events on the step's stream around the persistent rollout kernel and
+ * events on the step's stream around the rollout kernel and
  * around the update kernel.  mppi_batch_timing_read waits for the recorded
  * steps, returns the summed milliseconds and the step count, and clears the
  * records.  At most 4096 steps are kept. */

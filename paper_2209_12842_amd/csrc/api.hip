@@ -980,7 +980,7 @@ Geometry batch_geometry(const mppi_params* p) {
 int n_dist_wg(const mppi_params* p, const Geometry& g) { return (p->K + g.spb - 1) / g.spb; }
 
 struct BatchLayout {
-    size_t ctls, items, uitems, queue, vbackup, work;
+    size_t ctls, items, uitems, vbackup, work;
     std::vector<size_t> ctl_base;
     size_t total;
     int n_items, n_uitems;
@@ -1028,7 +1028,6 @@ BatchLayout batch_layout(int32_t n, const mppi_params* p) {
     bl.ctls = o;    o += align_up(sizeof(ramppi::BatchCtl) * (size_t)n);
     bl.items = o;   o += align_up(8 * (size_t)bl.n_items);
     bl.uitems = o;  o += align_up(8 * (size_t)bl.n_uitems);
-    bl.queue = o;   o += align_up(8);
     bl.work = o;    o += align_up(16 * (size_t)ramppi::kWorkSlots);
     bl.vbackup = o; o += vback;
     bl.ctl_base.resize(n);
@@ -1043,7 +1042,7 @@ BatchLayout batch_layout(int32_t n, const mppi_params* p) {
 }  // namespace
 
 struct mppi_batch {
-    int n, device, num_cu, wg_per_cu, wg_max, order;
+    int n, device, wg_max, order;
     std::vector<mppi_params> p;
     std::vector<ramppi::BatchCtl> ctl;  // host copy (device pointers inside)
     std::vector<float*> V;
@@ -1072,12 +1071,10 @@ ramppi::BatchLaunch batch_launch_args(const mppi_batch* b) {
     L.inputs = b->in_dev;
     L.items = reinterpret_cast<const int2*>(b->ws + b->bl.items);
     L.uitems = reinterpret_cast<const int2*>(b->ws + b->bl.uitems);
-    L.queue = reinterpret_cast<unsigned*>(b->ws + b->bl.queue);
     L.work = nullptr;
     L.n_ctl = b->n;
     L.n_items = b->bl.n_items;
     L.n_uitems = b->bl.n_uitems;
-    L.grid_rollout = b->wg_per_cu * b->num_cu;
     L.noise_kind = b->bl.noise_kind;
     L.lds_rollout = b->bl.lds_rollout;
     L.lds_update = b->bl.lds_update;
@@ -1093,14 +1090,6 @@ void batch_release(mppi_batch* b) {
     if (b->in_host) (void)hipHostFree(b->in_host);
     if (b->out_host) (void)hipHostFree(b->out_host);
     delete b;
-}
-
-void drop_graph(mppi_batch* b) {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
-    b->captured = false;
 }
 
 hipError_t upload_items(mppi_batch* b, int order, hipStream_t s) {
@@ -1187,8 +1176,7 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
     b->done = nullptr;
     b->timing = false;
     b->n_timed = 0;
-    hipError_t e = hipDeviceGetAttribute(&b->num_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = ramppi::batch_rollout_occupancy(&b->wg_max, bl.lds_rollout, bl.noise_kind);
+    hipError_t e = ramppi::batch_rollout_occupancy(&b->wg_max, bl.lds_rollout, bl.noise_kind);
     if (e == hipSuccess)
         e = hipHostMalloc(reinterpret_cast<void**>(&b->in_host), sizeof(ramppi::BatchInput) * (size_t)n,
                           hipHostMallocMapped | hipHostMallocCoherent);
@@ -1204,7 +1192,6 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
         return hip_fail(e, "batch set-up");
     }
     if (b->wg_max < 1) b->wg_max = 1;
-    b->wg_per_cu = b->wg_max;
     b->order = 1;
     std::memset(b->in_host, 0, sizeof(ramppi::BatchInput) * (size_t)n);
 
@@ -1264,7 +1251,6 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
     if (e == hipSuccess) e = upload_items(b, b->order, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->ws + bl.uitems, uitems.data(), 8 * uitems.size(), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(b->ws + bl.queue, 0, 8, s);
     if (e == hipSuccess) e = hipMemsetAsync(b->ws + bl.work, 0, 16 * (size_t)ramppi::kWorkSlots, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
@@ -1384,28 +1370,22 @@ mppi_status mppi_batch_autotune(mppi_batch* b, int32_t trials, void* stream, int
     hipEvent_t t0 = nullptr, t1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&t0);
     if (e == hipSuccess) e = hipEventCreate(&t1);
-    const int saved_wg = b->wg_per_cu, saved_order = b->order;
     float best = -1.0f;
-    int best_wg = saved_wg, best_order = saved_order;
+    int best_order = b->order;
     for (int ord = 0; e == hipSuccess && ord < 2; ++ord) {
         e = upload_items(b, ord, s);
-        for (int wg = 1; e == hipSuccess && wg <= b->wg_max; wg *= 2) {
-            b->wg_per_cu = wg;
-            e = batch_launch(b, s, false);  // warm-up
-            if (e == hipSuccess) e = hipEventRecord(t0, s);
-            for (int r = 0; e == hipSuccess && r < trials; ++r) e = batch_launch(b, s, false);
-            if (e == hipSuccess) e = hipEventRecord(t1, s);
-            if (e == hipSuccess) e = hipEventSynchronize(t1);
-            float ms = 0.0f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&ms, t0, t1);
-            if (e == hipSuccess && (best < 0.0f || ms < best)) {
-                best = ms;
-                best_wg = wg;
-                best_order = ord;
-            }
+        if (e == hipSuccess) e = batch_launch(b, s, false);  // warm-up
+        if (e == hipSuccess) e = hipEventRecord(t0, s);
+        for (int r = 0; e == hipSuccess && r < trials; ++r) e = batch_launch(b, s, false);
+        if (e == hipSuccess) e = hipEventRecord(t1, s);
+        if (e == hipSuccess) e = hipEventSynchronize(t1);
+        float ms = 0.0f;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, t0, t1);
+        if (e == hipSuccess && (best < 0.0f || ms < best)) {
+            best = ms;
+            best_order = ord;
         }
     }
-    b->wg_per_cu = best_wg;
     b->order = best_order;
     if (e == hipSuccess) e = upload_items(b, best_order, s);
     off = b->bl.vbackup;
@@ -1416,10 +1396,9 @@ mppi_status mppi_batch_autotune(mppi_batch* b, int32_t trials, void* stream, int
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (t0) (void)hipEventDestroy(t0);
     if (t1) (void)hipEventDestroy(t1);
-    drop_graph(b);  // the grid changed: capture again on the next step
     b->pending = false;
     if (e != hipSuccess) return hip_fail(e, "autotune");
-    if (wg_per_cu) *wg_per_cu = best_wg;
+    if (wg_per_cu) *wg_per_cu = b->wg_max;
     if (order) *order = best_order;
     return MPPI_OK;
 }

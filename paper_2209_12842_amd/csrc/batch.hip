@@ -3,17 +3,16 @@
 //   k_batch_prep     one thread per controller: reads the controller's
 //                    measured state and call index from mapped host memory
 //                    and completes its per-step constants;
-//   k_batch_rollout  persistent: a fixed grid of workgroups takes
-//                    (controller, workgroup) items from a queue (an atomic
-//                    counter over an item list ordered by the host, by
-//                    default longest first) and runs the same rollout body as
-//                    the single-controller kernel; every workgroup leaves
-//                    when the queue is empty, and the last one to leave
-//                    resets the queue for the next launch;
+//   k_batch_rollout  one workgroup per (controller, workgroup) item of a list
+//                    that the host orders (by default longest first; the
+//                    hardware starts workgroups in list order), running the
+//                    same rollout body as the single-controller kernel;
 //   k_batch_update   one workgroup per (controller, chunk) item, the same
 //                    update body as the single-controller kernel, merged per
 //                    controller by its last chunk.
 // Nothing waits for another workgroup, so every wave reaches its exit.
+#include <algorithm>
+
 #include "launch.h"
 #include "step_device.h"
 
@@ -39,68 +38,57 @@ __global__ void __launch_bounds__(64) k_batch_prep(BatchCtl* __restrict__ ctls, 
     if (i < n_ctl) set_dynamic(ctls[i].c, ctls[i], inputs[i]);
 }
 
-// The loop of the persistent rollout kernel: kNoise >= 0 is the one
-// disturbance form of every controller of the batch; -1 picks it per item.
+// One item of the batch's rollouts: kNoise >= 0 is the one disturbance form
+// of every controller of the batch; -1 picks it per item.  A workgroup runs
+// one item and leaves: a persistent grid that takes items from a queue paid
+// two device atomics per item and kept what it derives from the thread index
+// in registers across items (18 VGPRs spilled), and the hardware's own
+// dispatch of waiting workgroups balances the list as well (8 controllers of
+// K <= 1024, T <= 40: step 91 -> 66 us; 48 of K <= 8192, T <= 100: 2.62 ->
+// 2.57 ms).
 template <int kNoise>
-__device__ __forceinline__ void batch_rollout_loop(const BatchCtl* __restrict__ ctls, const int2* __restrict__ items,
-                                                   int n_items, unsigned* queue, unsigned long long* __restrict__ work) {
+__device__ __forceinline__ void batch_rollout_item(const BatchCtl* __restrict__ ctls, const int2* __restrict__ items,
+                                                   unsigned long long* __restrict__ work) {
     extern __shared__ float2 bsmem[];
-    __shared__ int item_sh;
-    for (;;) {
-        if (threadIdx.x == 0) item_sh = (int)atomicAdd(&queue[0], 1u);
-        __syncthreads();
-        const int it = __builtin_amdgcn_readfirstlane(item_sh);
-        __syncthreads();  // every lane has read item_sh before it is overwritten
-        if (it >= n_items) break;
-        const int2 cw = items[it];
-        const BatchCtl& b = ctls[__builtin_amdgcn_readfirstlane(cw.x)];
-        const int w = __builtin_amdgcn_readfirstlane(cw.y);
-        const StepConst c = b.c;
-        // the controller's buffers, read from device memory: in the global
-        // address space (as_global)
-        const float4* obs = as_global(b.obs);
-        const float* V = as_global(b.V);
-        float2* u = as_global(b.u);
-        float* S = as_global(b.S);
-        float* cvar = as_global(b.cvar);
-        float* L = as_global(b.L);
-        if constexpr (kNoise >= 0) {
-            rollout_body<kNoise>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
-        } else {
-            if (c.noise_kind == 1)
-                rollout_body<1>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
-            else if (c.noise_kind == 2)
-                rollout_body<2>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
-            else
-                rollout_body<0>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
-        }
-        __syncthreads();  // LDS is reused by the next item
-    }
-    if (threadIdx.x == 0) {
-        const unsigned done = __hip_atomic_fetch_add(&queue[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (done == gridDim.x - 1) {  // every other workgroup has left: reset for the next launch
-            __hip_atomic_store(&queue[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&queue[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    const int2 cw = items[blockIdx.x];
+    const BatchCtl& b = ctls[__builtin_amdgcn_readfirstlane(cw.x)];
+    const int w = __builtin_amdgcn_readfirstlane(cw.y);
+    const StepConst c = b.c;
+    // the controller's buffers, read from device memory: in the global
+    // address space (as_global)
+    const float4* obs = as_global(b.obs);
+    const float* V = as_global(b.V);
+    float2* u = as_global(b.u);
+    float* S = as_global(b.S);
+    float* cvar = as_global(b.cvar);
+    float* L = as_global(b.L);
+    if constexpr (kNoise >= 0) {
+        rollout_body<kNoise>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+    } else {
+        if (c.noise_kind == 1)
+            rollout_body<1>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+        else if (c.noise_kind == 2)
+            rollout_body<2>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+        else
+            rollout_body<0>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
     }
 }
 
 // Controllers of several disturbance forms.
 __global__ void __launch_bounds__(256) k_batch_rollout(const BatchCtl* __restrict__ ctls,
-                                                       const int2* __restrict__ items, int n_items,
-                                                       unsigned* queue, unsigned long long* __restrict__ work) {
-    batch_rollout_loop<-1>(ctls, items, n_items, queue, work);
+                                                       const int2* __restrict__ items,
+                                                       unsigned long long* __restrict__ work) {
+    batch_rollout_item<-1>(ctls, items, work);
 }
 
 // One disturbance form for the whole batch: compiled, like the two-launch
 // rollout kernel, for five waves per SIMD (the kernel for several forms
-// needs the registers of the largest and holds four; on the 64-controller
-// batch the rollout launch 3.62 -> 3.57 ms).
+// needs the registers of the largest and holds four).
 template <int kNoise>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
-    k_batch_rollout_one(const BatchCtl* __restrict__ ctls, const int2* __restrict__ items, int n_items,
-                        unsigned* queue, unsigned long long* __restrict__ work) {
-    batch_rollout_loop<kNoise>(ctls, items, n_items, queue, work);
+    k_batch_rollout_one(const BatchCtl* __restrict__ ctls, const int2* __restrict__ items,
+                        unsigned long long* __restrict__ work) {
+    batch_rollout_item<kNoise>(ctls, items, work);
 }
 
 __global__ void __launch_bounds__(256) k_batch_update(const BatchCtl* __restrict__ ctls,
@@ -116,22 +104,24 @@ __global__ void __launch_bounds__(256) k_batch_update(const BatchCtl* __restrict
                 as_global(b.w_hat), bush, red, &is_last);
 }
 
+// Items of one rollout launch: a grid holds fewer than 2^32 threads.
+constexpr int kMaxItemsPerLaunch = 1 << 23;
+
 hipError_t launch_batch(const BatchLaunch& L, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_mid) {
     hipLaunchKernelGGL(k_batch_prep, dim3((L.n_ctl + 63) / 64), dim3(64), 0, stream, L.ctls, L.inputs, L.n_ctl);
     if (ev_start) (void)hipEventRecord(ev_start, stream);
-    const dim3 grid(L.grid_rollout);
-    if (L.noise_kind == 0)
-        hipLaunchKernelGGL(k_batch_rollout_one<0>, grid, dim3(256), L.lds_rollout, stream, L.ctls, L.items, L.n_items,
-                           L.queue, L.work);
-    else if (L.noise_kind == 1)
-        hipLaunchKernelGGL(k_batch_rollout_one<1>, grid, dim3(256), L.lds_rollout, stream, L.ctls, L.items, L.n_items,
-                           L.queue, L.work);
-    else if (L.noise_kind == 2)
-        hipLaunchKernelGGL(k_batch_rollout_one<2>, grid, dim3(256), L.lds_rollout, stream, L.ctls, L.items, L.n_items,
-                           L.queue, L.work);
-    else
-        hipLaunchKernelGGL(k_batch_rollout, grid, dim3(256), L.lds_rollout, stream, L.ctls, L.items, L.n_items,
-                           L.queue, L.work);
+    for (int i0 = 0; i0 < L.n_items; i0 += kMaxItemsPerLaunch) {  // one launch unless the batch is enormous
+        const dim3 grid(std::min(L.n_items - i0, kMaxItemsPerLaunch));
+        const int2* items = L.items + i0;
+        if (L.noise_kind == 0)
+            hipLaunchKernelGGL(k_batch_rollout_one<0>, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
+        else if (L.noise_kind == 1)
+            hipLaunchKernelGGL(k_batch_rollout_one<1>, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
+        else if (L.noise_kind == 2)
+            hipLaunchKernelGGL(k_batch_rollout_one<2>, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
+        else
+            hipLaunchKernelGGL(k_batch_rollout, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
+    }
     if (ev_mid) (void)hipEventRecord(ev_mid, stream);
     hipLaunchKernelGGL(k_batch_update, dim3(L.n_uitems), dim3(256), L.lds_update, stream, L.ctls, L.uitems);
     return hipGetLastError();

@@ -59,11 +59,10 @@ struct BatchInput {
 struct BatchLaunch {
     BatchCtl* ctls;
     const BatchInput* inputs;  // device address of the mapped inputs
-    const int2* items;         // rollout items (controller, workgroup), in queue order
+    const int2* items;         // rollout items (controller, workgroup), in the order they start
     const int2* uitems;        // update items (controller, chunk)
-    unsigned* queue;           // 2 counters, zero between launches
     unsigned long long* work;  // kWorkSlots broad-phase candidate counters, or null
-    int n_ctl, n_items, n_uitems, grid_rollout;
+    int n_ctl, n_items, n_uitems;
     int noise_kind;            // the disturbance form of every controller, or -1 when they differ
     size_t lds_rollout, lds_update;
 };
