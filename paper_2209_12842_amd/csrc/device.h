@@ -691,6 +691,138 @@ __device__ __forceinline__ void bitonic_wave_stages(float& v, int& id, int i, in
     bitonic_cx_lanes<1>(v, id, i, k);
 }
 
+// The values of lanes l and l ^ kJ, as an unordered pair that both lanes see
+// (a power of two below 64, every lane active), without the LDS unit: DPP
+// quad permutations for 1 and 2, two row shifts merged by bank for 4, a row
+// rotation for 8, and gfx950's row and half-wave swaps for 16 and 32.
+template <int kJ>
+__device__ __forceinline__ void lane_pair(float v, float& a, float& b) {
+    const int x = __float_as_int(v);
+    if constexpr (kJ == 32 || kJ == 16) {
+        // the swap of two copies leaves the lower partner's value in every
+        // lane of the first and the upper partner's in the second
+        const auto r = kJ == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                                : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        a = __int_as_float((int)r[0]);
+        b = __int_as_float((int)r[1]);
+    } else {
+        int y;
+        if constexpr (kJ == 4) {
+            y = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xF, 0x5, false);  // banks 0, 2 read lane + 4
+            y = __builtin_amdgcn_update_dpp(y, x, 0x114, 0xF, 0xA, false);  // banks 1, 3 read lane - 4
+        } else {
+            y = lane_xor<kJ>(x);
+        }
+        a = v;
+        b = __int_as_float(y);
+    }
+}
+
+// One exchange at distance kJ of a bitonic sort: the lower lane of a pair
+// keeps the larger value and the upper one the smaller, the other way round
+// where the top bit of `flip` is set, as the median of the two values and
+// +-infinity.  The sign comes from the lane number by arithmetic: constant
+// lane masks would fill the scalar registers of the rollout kernels.
+template <int kJ>
+__device__ __forceinline__ float sort_cx(float v, uint32_t lane, uint32_t flip) {
+    float a, b;
+    lane_pair<kJ>(v, a, b);
+    const uint32_t t = (lane << (31 - __builtin_ctz(kJ))) ^ flip;
+    return __builtin_amdgcn_fmed3f(a, b, __uint_as_float((t & 0x80000000u) | 0x7F800000u));
+}
+
+// Merge block k (a power of two up to 64, the same in every lane) of a
+// bitonic sort of one value per lane.
+__device__ __forceinline__ float sort_block(float v, uint32_t lane, int k, uint32_t flip) {
+    if (k > 32) v = sort_cx<32>(v, lane, flip);
+    if (k > 16) v = sort_cx<16>(v, lane, flip);
+    if (k > 8) v = sort_cx<8>(v, lane, flip);
+    if (k > 4) v = sort_cx<4>(v, lane, flip);
+    if (k > 2) v = sort_cx<2>(v, lane, flip);
+    return sort_cx<1>(v, lane, flip);
+}
+
+// Sorts the values of each segment of P lanes (a power of two up to 64, the
+// same in every lane), one per lane, without NaN: larger first, or smaller
+// first when the top bit of `flip` is set.  The loop over the merge blocks
+// stays a loop: unrolled, its code takes longer to fetch than to run in a
+// launch that sorts once.
+__device__ __forceinline__ float sort_lanes(float v, uint32_t lane, int P, uint32_t flip) {
+    const uint32_t i = lane & (uint32_t)(P - 1);
+#pragma clang loop unroll(disable)
+    for (int k = 2; k <= P; k <<= 1) v = sort_block(v, lane, k, flip ^ ((i & (uint32_t)k) ? 0x80000000u : 0u));
+    return v;
+}
+
+// Longest tail that wave_tail_mean can take: the lanes of a wave.
+constexpr int kWaveTail = 64;
+
+// Lanes of a wave that hold one sample of M draws in wave_tail_mean.
+__host__ __device__ __forceinline__ int tail_lanes(int M) {
+    int P = 1;
+    while (P < M && P < 64) P <<= 1;
+    return P;
+}
+
+// Mean of the n_tail (at most kWaveTail) largest of a sample's M values,
+// summed in descending order -- the bits of tail_rank_scatter and tail_sum --
+// by the lanes of one segment of P = tail_lanes(M) lanes, each segment of the
+// wave a sample of its own.  value(i) is the sample's value i < M for this
+// lane's sample; lane is the lane's number in its wave.  The first P values are sorted across the lanes; every
+// further column of 64 is sorted the other way round, so that the larger of
+// the two in each lane are the 64 largest of both as a bitonic sequence,
+// which one merge block sorts.  A value that is not a number makes the mean
+// one too.  Every lane of the wave must be active; the result is in every
+// lane of the segment.
+template <class Value>
+__device__ __forceinline__ float wave_tail_mean(Value value, uint32_t lane, int M, int P, int n_tail) {
+    const float ninf = -__builtin_inff();
+    float v = 0.0f;
+    uint64_t nans = 0;
+#pragma clang loop unroll(disable)
+    for (int c = 0; c < M; c += 64) {  // one column when M <= 64
+        const int i = c + (int)(lane & (uint32_t)(P - 1));
+        float w = i < M ? value(i) : ninf;
+        nans |= __builtin_amdgcn_ballot_w64(w != w);
+        w = sort_lanes(w, lane, P, c ? 0x80000000u : 0u);
+        v = c ? sort_block(fmaxf(v, w), lane, 64, 0u) : w;
+    }
+    // the segment's first n_tail lanes, added in order by every lane of it
+    const int base = (int)(lane & ~(uint32_t)(P - 1)) << 2;
+    float s = 0.0f;
+#pragma clang loop unroll(disable)
+    for (int r = 0; r < n_tail; r += 8) {
+        float t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            t[q] = __int_as_float(
+                __builtin_amdgcn_ds_bpermute(base + (min(r + q, n_tail - 1) << 2), __float_as_int(v)));
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s = r + q < n_tail ? s + t[q] : s;
+    }
+    s = s / (float)n_tail;
+    if (nans) {  // of this segment's lanes
+        const uint64_t seg = (P == 64 ? ~0ull : ((1ull << P) - 1ull)) << (base >> 2);
+        if (nans & seg) s = __builtin_nanf("");
+    }
+    return s;
+}
+
+// Sum of v[0..M-1] (LDS) in index order, eight loads in flight.
+__device__ __forceinline__ float seq_sum(const float* v, int M) {
+    float s = 0.0f;
+    int j = 0;
+    for (; j + 8 <= M; j += 8) {
+        float t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t[q] = v[j + q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += t[q];
+    }
+    for (; j < M; ++j) s += v[j];
+    return s;
+}
+
 __device__ __forceinline__ float tail_sum(const float* tail, int n_tail) {
     float s = 0.0f;
     for (int r = 0; r < n_tail; ++r) s += tail[r];

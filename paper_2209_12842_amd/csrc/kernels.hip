@@ -181,8 +181,37 @@ __global__ void __launch_bounds__(1024) k_cvar(const float* __restrict__ L, int 
     if (active && m == 0) cvar_out[k] = cv;
 }
 
-// The CVaR pass of the flattened two-launch step (M > 256): one sample per
-// workgroup of P threads, P the power of two at or above M (at most 1024).
+// CVaR of stored risk costs for tails of at most kWaveTail values: a wave per
+// sample, or for M <= 32 a segment of a wave (wave_tail_mean); the mean for
+// the risk scaling from the sample's costs staged in LDS.  The stage entry
+// point and the CVaR pass of the flattened two-launch step (M > 256) use it
+// (K = 1024, M = 300: 10.7 -> 5.6 us against one 512-thread workgroup per
+// sample, whose exchanges across waves meet at barriers).
+__global__ void __launch_bounds__(256) k_cvar_wave(const float* __restrict__ L, int K, int M, int P, int n_tail,
+                                                   int scale_risk, float B, float* __restrict__ cvar_out) {
+    extern __shared__ float wsh[];  // 4 waves x 64 / P samples x M, with scale_risk only
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, per = 64 / P;
+    const int seg = lane / P;
+    const int k = (blockIdx.x * 4 + wv) * per + seg;
+    const float* Lk = L + (size_t)min(k, K - 1) * M;
+    float mu = 0.0f;
+    if (scale_risk) {
+        float* v = wsh + (size_t)(wv * per + seg) * M;
+        for (int i = lane & (P - 1); i < M; i += P) v[i] = Lk[i];
+        __syncthreads();
+        mu = seq_sum(v, M) / (float)M;
+    }
+    const float cv = wave_tail_mean(
+        [&](int i) {
+            const float x = Lk[i];
+            return scale_risk ? __fmaf_rn(B, x - mu, mu) : x;
+        },
+        (uint32_t)lane, M, P, n_tail);
+    if (k < K && (lane & (P - 1)) == 0) cvar_out[k] = cv;
+}
+
+// The CVaR pass of the flattened two-launch step (M > 256) for longer tails:
+// one sample per workgroup of P threads, P the power of two at or above M (at most 1024).
 // The M stored risk costs are scaled as cvar_epilogue scales them (the mean
 // summed by one thread in draw order), padded to P with -inf, sorted by the
 // same bitonic stages (larger first, equal costs by smaller draw index), and
@@ -299,6 +328,15 @@ size_t update_lds_bytes(int T, int G) {
     return 4 * (256 + (slices > merge ? slices : merge));
 }
 
+static hipError_t launch_cvar_wave(const float* L, int K, int M, int n_tail, int scale_risk, float B, float* out,
+                                   hipStream_t stream) {
+    const int P = tail_lanes(M), per = 4 * (64 / P);  // samples per workgroup
+    const size_t lds = scale_risk ? sizeof(float) * (size_t)per * M : 0;
+    hipLaunchKernelGGL(k_cvar_wave, dim3((K + per - 1) / per), dim3(256), lds, stream, L, K, M, P, n_tail, scale_risk,
+                       B, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_step(const StepConst& c, const StepBuffers& b, int block, size_t lds_rollout, int G,
                        size_t lds_update, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_mid,
                        const FuseArgs* fa) {
@@ -311,7 +349,9 @@ hipError_t launch_step(const StepConst& c, const StepBuffers& b, int block, size
         if (ev_mid) (void)hipEventRecord(ev_mid, stream);
     } else {
         launch_rollout_t<false>(c, b, grid, block, lds_rollout, stream, nullptr, nullptr, nullptr);
-        if (c.flat) {  // each sample's CVaR from the stored risk costs (one sample per workgroup)
+        if (c.flat && c.n_tail <= kWaveTail) {  // each sample's CVaR from the stored risk costs
+            (void)launch_cvar_wave(b.L, c.K, c.M, c.n_tail, c.scale_risk, c.B, b.cvar, stream);
+        } else if (c.flat) {
             int P = 64;
             while (P < c.M) P <<= 1;
             hipLaunchKernelGGL(k_cvar_sorted, dim3(c.K), dim3(P), 2 * sizeof(float) * (size_t)P, stream, b.L, c.M,
@@ -341,6 +381,7 @@ hipError_t launch_normals(uint64_t seed, const uint32_t* ctr, float* out, int64_
 
 hipError_t launch_cvar(const float* L, int K, int M, int spb, int block, int n_tail, int scale_risk, float B,
                        float* out, hipStream_t stream) {
+    if (n_tail <= kWaveTail) return launch_cvar_wave(L, K, M, n_tail, scale_risk, B, out, stream);
     const int blocks = (K + spb - 1) / spb;
     const size_t lds = sizeof(float) * (size_t)(2 * spb * M + spb);
     hipLaunchKernelGGL(k_cvar, dim3(blocks), dim3(block), lds, stream, L, K, M, spb, n_tail, scale_risk, B, out);
