@@ -458,125 +458,125 @@ __device__ __forceinline__ float lane_f32(float v, int lane) {
 // together (the M draws of one sample).  Broad phase: a box around the
 // wave's points of all S steps, [xc - Rx, xc + Rx] x [yc - Ry, yc + Ry] with
 // (xc, yc) the first lane's first point and Rx, Ry the largest distances of
-// the lanes' points from it along x and y, against every disc, lane j
-// testing entry 64 g + j of the table staged in LDS (otab, n_grp groups of
-// 64): d2 = squared distance from the disc centre to the box, candidate iff
-// d2 - 2^-15 P^2 < q (evaluated as dx^2 + (dy^2 - 2^-15 P^2), two fused
-// multiply-adds), where P^2 = (|xc| + Rx)^2 + (|yc| + Ry)^2 bounds |p|^2
-// over the box.  The margin exceeds the rounding error of both this test and
-// the exact test (each a few units in the last place of r^2 + |c|^2 + |p|^2,
-// the box edges a few units in the last place of P) by more than twenty
-// times, so a disc that is not a candidate fails the exact test at every
-// point of every lane.  Narrow phase: the exact test of each candidate at
-// the S points, its entry broadcast from lane j.  One box serves S steps,
-// which divides the cost of the box and the group tests by S; the count is
-// an integer, so the grouping leaves it exact.  Every lane of the wave must
-// be active.  n_cand counts the exact tests per lane (candidates times
-// points, wave-uniform).  The caller holds
-// lane j's entry of the first group in registers (e0, read once per
-// rollout: the table does not change within a step); later groups are read
-// from LDS at every call.
+// the lanes' points from it along x and y (widened by kBoxWiden against the
+// rounding of those distances), against every disc, lane j testing entry
+// 64 g + j of the table staged in LDS (otab, n_grp groups of 64): candidate
+// iff the squared distance from the disc centre to the box is below q.
+//
+// Why no hit is lost: with u = 2^-24, D the distance of a point p from a
+// centre c and the exact test's rounding errors added up (each operation's
+// is u times its terms, |p|^2 <= 2 |c|^2 + 2 D^2), a point that passes the
+// exact test has D^2 < (1 + 15 u) r^2 + 19 u |c|^2.  The box edges are off by
+// at most u |p| at that point and the squared distance by 9 u D^2 + 2 u
+// |c|^2, so it stays below (1 + 25 u) r^2 + 21 u |c|^2, while q is
+// (1 + 256 u) r^2 + 512 u |c|^2: more than ten times the margin.  The bound
+// holds for boxes of any size; no term of the box's own reach is needed.
+//
+// Narrow phase: the exact test of each candidate at the S points, its entry
+// broadcast from LDS.  (The same test of four candidates at once on the
+// matrix unit, a chain of 4x4x1 MFMAs with the bits of the two fused
+// multiply-adds, cost more than it saved: each such instruction holds the
+// SIMD for about 16 clocks, 627 -> 705 us on the large step's rollouts.)
+//
+// One box serves S steps, which divides the cost of the box and the group
+// tests by S; the count is an integer, so the grouping leaves it exact.
+// Every lane of the wave must be active.  n_cand counts the exact tests per
+// lane (candidates times points, wave-uniform).  Bound by vector instructions:
+// per run about 45 for the box, 10 per group test and 17 to 29 per candidate
+// (a term of the box's reach in the margin, |p|^2 for waves without a
+// candidate and guarded counts made them 60, 10 and 19 to 36; K = 16384,
+// T = 100, M = 128, 200 obstacles: rollouts and update 629 -> 615 us,
+// K = 2048, T = 50, M = 64, 50 obstacles: 37.6 -> 37.3 us).
+constexpr float kBoxWiden = 1.0f + 0x1p-21f;
+
 template <int S>
 __device__ __forceinline__ void cull_group(const float4 e, const float4* grp, float bx0, float bx1, float by0,
-                                           float by1, float p2, const float (&px)[S], const float (&py)[S],
-                                           const float (&rho)[S], int n, int& cnt, int& n_cand) {
+                                           float by1, const float (&px)[S], const float (&py)[S], int n, int& cnt,
+                                           int& n_cand) {
     const float cx = -0.5f * e.x, cy = -0.5f * e.y;
     const float dx = fmaxf(fmaxf(bx0 - cx, cx - bx1), 0.0f);
     const float dy = fmaxf(fmaxf(by0 - cy, cy - by1), 0.0f);
-    uint64_t cand = __builtin_amdgcn_ballot_w64(__fmaf_rn(dx, dx, __fmaf_rn(dy, dy, -p2)) < e.w);
-    while (cand) {
+    uint64_t cand = __builtin_amdgcn_ballot_w64(__fmaf_rn(dx, dx, dy * dy) < e.w);
+    if (cand == 0ull) return;
+    n_cand += n * (int)__builtin_popcountll(cand);
+    // |p|^2, needed by waves that have a candidate only; points past n repeat
+    // a valid one and are put outside every disc
+    float rho[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) rho[u] = __fmaf_rn(px[u], px[u], py[u] * py[u]);
+    if (n < S) {
+#pragma unroll
+        for (int u = 0; u < S; ++u) rho[u] = u < n ? rho[u] : __builtin_inff();
+    }
+    do {
         const int j = __builtin_ctzll(cand);
         cand &= cand - 1;
-        n_cand += n;
         // the candidate's entry read from LDS at one address for the whole
         // wave: it arrives in vector registers, so that the tests below
         // read no scalar register (see in_vgpr)
         const float4 ej = grp[j];
         const float a = ej.x, b = ej.y, z = ej.z;
-        // one compare of the smallest of the S test values tells whether the
-        // lane is inside the disc at any point (points past n repeat a valid
-        // point, so they add no false alarm); only then are the points
-        // compared one by one and counted, and the wave skips that when no
-        // lane is inside (most candidates of the box test are near misses)
+        // one compare of the smallest of the S test values tells whether any
+        // lane is inside the disc at any point; only then are the points
+        // compared one by one and counted (many candidates of the box test
+        // are near misses)
         float d[S];
 #pragma unroll
         for (int u = 0; u < S; ++u) d[u] = __fmaf_rn(a, px[u], __fmaf_rn(b, py[u], rho[u]));
         float dmin = d[0];
 #pragma unroll
         for (int u = 1; u < S; ++u) dmin = fminf(dmin, d[u]);
-        if (dmin < z) {
+        if (__builtin_amdgcn_ballot_w64(dmin < z)) {
 #pragma unroll
-            for (int u = 0; u < S; ++u) cnt += (u < n && d[u] < z) ? 1 : 0;
+            for (int u = 0; u < S; ++u) cnt += d[u] < z ? 1 : 0;
         }
-    }
+    } while (cand);
 }
 
 // Group skip of the broad phase (tables of more than one group).  Each group
 // of 64 table entries has a bounding box: the union of its discs' squares
-// |x - cx|, |y - cy| <= sqrt(q), widened by kGroupPad on every side
-// (group_bounds).  A wave box that does not meet it is farther than
-// sqrt(q) + kGroupPad from every centre of the group in x or in y, so each
-// disc's squared distance exceeds (sqrt(q) + kGroupPad)^2 > q + 2^-15 P^2
-// as long as 2^-7.5 P <= kGroupPad - 0.086 (P <= 256 m; beyond that every
-// group is tested): the broad phase would reject the whole group, and the
-// wave skips its test.  With the table sorted by angle around the
-// obstacles' centroid (the host does that), a box along a track meets one or
-// two groups.  The boxes are tested four compares per box for all groups at
-// once: lane g holds group g's box (gb), lanes past the last group an empty
-// one.
-constexpr float kGroupPad = 1.5f;
-constexpr float kGroupPadP2 = 65536.0f;  // P^2 up to which kGroupPad covers the broad-phase margin
-
-// px, py: the S points (entries past n repeat a valid point).  gbox: the 64
-// group boxes in LDS (see kGroupPad; boxes past n_grp meet nothing), read at
-// every call rather than held in registers through the rollout; n_grp == 1
-// tests the one group directly.  n_gtest counts the group tests run
-// (wave-uniform).
+// |x - cx|, |y - cy| <= sqrt(q) (group_bounds).  A wave box that does not
+// meet it is farther than sqrt(q) from every centre of the group in x or in
+// y (up to a rounding error of u (sqrt(q) + |c|), far inside q's margin), so
+// no point of it hits a disc of the group and the wave skips its test.  With
+// the table sorted by angle around the obstacles' centroid (the host does
+// that), a box along a track meets one or two groups.  The boxes are tested
+// four compares per box for all groups at once: lane g holds group g's box
+// in `first`, lanes past the last group an empty one.
+//
+// px, py: the S points (entries past n repeat a valid point).  first: this
+// lane's entry of the only group (n_grp == 1) or its group box, read by the
+// caller once per rollout (neither changes within a step).  n_gtest counts the group tests run (wave-uniform).
 template <int S>
-__device__ __forceinline__ int obstacle_hits_culled(const float4* __restrict__ otab, const float4* gbox, int n_grp,
-                                                    float4 e0, const float (&px)[S], const float (&py)[S], int n,
-                                                    int& n_cand, int& n_gtest) {
+__device__ __forceinline__ int obstacle_hits_culled(const float4* __restrict__ otab, int n_grp, const float4& first,
+                                                    const float (&px)[S], const float (&py)[S], int n, int& n_cand,
+                                                    int& n_gtest) {
+    const int lane = threadIdx.x & 63;
     const float xc = in_vgpr(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(px[0]))));
     const float yc = in_vgpr(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(py[0]))));
     float mx = fabsf(px[0] - xc), my = fabsf(py[0] - yc);
-    float rho[S];
 #pragma unroll
-    for (int u = 0; u < S; ++u) {
-        if (u > 0) {
-            mx = fmaxf(mx, fabsf(px[u] - xc));
-            my = fmaxf(my, fabsf(py[u] - yc));
-        }
-        rho[u] = __fmaf_rn(px[u], px[u], py[u] * py[u]);
+    for (int u = 1; u < S; ++u) {
+        mx = fmaxf(mx, fabsf(px[u] - xc));
+        my = fmaxf(my, fabsf(py[u] - yc));
     }
     const float rx = __uint_as_float(wave_max_u32(__float_as_uint(mx)));
     const float ry = __uint_as_float(wave_max_u32(__float_as_uint(my)));
-    const float bx0 = xc - rx, bx1 = xc + rx, by0 = yc - ry, by1 = yc + ry;
-    const float ax = fabsf(xc) + rx, ay = fabsf(yc) + ry;
-    const float P2 = __fmaf_rn(ax, ax, ay * ay);
-    const float p2 = 3.0517578125e-05f * P2;  // 2^-15 P^2
-    const int lane = threadIdx.x & 63;
+    const float bx0 = __fmaf_rn(-kBoxWiden, rx, xc), bx1 = __fmaf_rn(kBoxWiden, rx, xc);
+    const float by0 = __fmaf_rn(-kBoxWiden, ry, yc), by1 = __fmaf_rn(kBoxWiden, ry, yc);
     int cnt = 0;
     if (n_grp == 1) {
-        cull_group<S>(e0, otab, bx0, bx1, by0, by1, p2, px, py, rho, n, cnt, n_cand);
+        cull_group<S>(first, otab, bx0, bx1, by0, by1, px, py, n, cnt, n_cand);
         ++n_gtest;
         return cnt;
     }
-    const float4 gb = gbox[lane];  // 64 entries, empty past n_grp
     // four compare masks combined on the scalar unit
-    uint64_t gm = __builtin_amdgcn_ballot_w64(gb.x <= bx1) & __builtin_amdgcn_ballot_w64(gb.y >= bx0) &
-                  __builtin_amdgcn_ballot_w64(gb.z <= by1) & __builtin_amdgcn_ballot_w64(gb.w >= by0);
-    // (P2 is the same in every lane: the ballot makes that known, so that
-    // the mask stays in scalar registers)
-    if (__builtin_amdgcn_ballot_w64(P2 > kGroupPadP2) != 0ull) gm = (n_grp >= 64) ? ~0ull : ((1ull << n_grp) - 1ull);
-    if (gm & 1ull) {
-        cull_group<S>(e0, otab, bx0, bx1, by0, by1, p2, px, py, rho, n, cnt, n_cand);
-        ++n_gtest;
-    }
-    gm &= ~1ull;
+    uint64_t gm = __builtin_amdgcn_ballot_w64(first.x <= bx1) & __builtin_amdgcn_ballot_w64(first.y >= bx0) &
+                  __builtin_amdgcn_ballot_w64(first.z <= by1) & __builtin_amdgcn_ballot_w64(first.w >= by0);
     while (gm) {
         const int g = __builtin_ctzll(gm);
         gm &= gm - 1ull;
-        cull_group<S>(otab[g * 64 + lane], otab + g * 64, bx0, bx1, by0, by1, p2, px, py, rho, n, cnt, n_cand);
+        cull_group<S>(otab[g * 64 + lane], otab + g * 64, bx0, bx1, by0, by1, px, py, n, cnt, n_cand);
         ++n_gtest;
     }
     return cnt;

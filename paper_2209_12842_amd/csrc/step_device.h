@@ -32,9 +32,9 @@ __device__ __forceinline__ float4 obstacle_entry(const float4* __restrict__ obs,
     return make_float4(0.0f, 0.0f, -__builtin_inff(), -__builtin_inff());
 }
 
-// The group boxes of the broad phase's group skip (kGroupPad): for each group
-// g of 64 table entries, the union of its discs' squares |x - cx|, |y - cy|
-// <= sqrt(q) widened by kGroupPad, as (x0, x1, y0, y1) in gbox[g]; entries
+// The group boxes of the broad phase's group skip: for each group g of 64
+// table entries, the union of its discs' squares |x - cx|, |y - cy|
+// <= sqrt(q), as (x0, x1, y0, y1) in gbox[g]; entries
 // n_grp..63 get a box that meets nothing.  One whole wave computes them
 // (lane j takes entry 64 g + j, computed as obstacle_entry computes it),
 // before the barrier that precedes the rollouts.
@@ -51,7 +51,7 @@ __device__ __forceinline__ void group_bounds(const float4* __restrict__ obs, int
         const float R = valid ? __builtin_amdgcn_sqrtf(e.w) : 0.0f;
         const float x0 = wave_min(valid ? cx - R : inf), x1 = wave_maxf(valid ? cx + R : -inf);
         const float y0 = wave_min(valid ? cy - R : inf), y1 = wave_maxf(valid ? cy + R : -inf);
-        if (lane == 0) gbox[g] = make_float4(x0 - kGroupPad, x1 + kGroupPad, y0 - kGroupPad, y1 + kGroupPad);
+        if (lane == 0) gbox[g] = make_float4(x0, x1, y0, y1);
     }
 }
 
@@ -227,7 +227,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
         const bool act = k < c.K;
         const bool store = act && c.store_u;
         const int kc = act ? k : c.K - 1;
-        const float4 e0 = n_grp > 0 ? otab[tid & 63] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[tid & 63] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         State s{0.0f, 0.0f, c.psi0, c.v0};
         float acc = 0.0f, ctrl = 0.0f;
         int cnt = 0;
@@ -275,7 +275,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
                     }
                 }
             }
-            if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, gbox, n_grp, e0, px, py, n, n_cand, n_gtest);
+            if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
         }
         float S = __fmaf_rn(c.c_obs, (float)cnt, acc);
         if (c.use_ctrl) S += ctrl;
@@ -339,7 +339,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
         // lanes past the workgroup's last sample repeat its controls, and the
         // results of inactive lanes are dropped
         const float2* ck = ctl + min(sl, n_smp - 1) * T;
-        const float4 e0 = n_grp > 0 ? otab[tid & 63] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[tid & 63] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         State s{0.0f, 0.0f, c.psi0, c.v0};
         float acc = 0.0f;
         int cnt = 0;
@@ -387,7 +387,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
                     }
                 }
             }
-            if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, gbox, n_grp, e0, px, py, n, n_cand, n_gtest);
+            if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
         }
         L = __fmaf_rn(c.c_obs, (float)cnt, acc);
     }
