@@ -88,19 +88,42 @@ constexpr uint32_t kMaxServeIdleMs = 60000;
 
 // Launch geometry derived from the sizes.
 struct Geometry {
-    int spb, block, n_nom_wg, G;
+    int spb, block, n_nom_wg, nom_groups, G;
     size_t lds_rollout, lds_update;
 };
+
+// Nominal workgroups of `groups` times 64 samples each.
+void set_nominal(Geometry* g, int K, int groups) {
+    g->nom_groups = groups;
+    g->n_nom_wg = (K + 64 * groups - 1) / (64 * groups);
+}
 
 Geometry geometry(const mppi_params* p) {
     Geometry g;
     g.spb = p->M >= 256 ? 1 : 256 / p->M;
     g.block = (g.spb * p->M + 63) / 64 * 64;
-    g.n_nom_wg = (p->K + g.block - 1) / g.block;
+    set_nominal(&g, p->K, 1);
     g.G = (p->K + kPartBlock - 1) / kPartBlock;
     g.lds_rollout = rollout_lds_bytes(g.spb, p);
     g.lds_update = ramppi::update_lds_bytes(p->T, g.G);
     return g;
+}
+
+// Workgroups of the one-launch step.
+int64_t one_launch_grid(const Geometry& g, int K) { return g.n_nom_wg + ((int64_t)K + g.spb - 1) / g.spb; }
+
+// Picks the nominal workgroups of a one-launch step on a device that holds
+// `resident` workgroups at once: 64 samples each (the shortest), or where
+// that grid does not fit, as many samples as the workgroup has threads (the
+// fewest workgroups).  Returns whether the grid fits.
+bool fit_nominal(Geometry* g, int K, int64_t resident) {
+    set_nominal(g, K, 1);
+    if (one_launch_grid(*g, K) <= resident) return true;
+    Geometry wide = *g;
+    set_nominal(&wide, K, g->block / 64);
+    if (one_launch_grid(wide, K) > resident) return false;
+    *g = wide;
+    return true;
 }
 
 // Integer tail size and warm count, computed in double precision.
@@ -183,6 +206,7 @@ void fill_static(ramppi::StepConst* cp, const mppi_params& p, const Geometry& g,
     c.n_obs = p.n_obs;
     c.spb = g.spb;
     c.n_nom_wg = g.n_nom_wg;
+    c.nom_groups = g.nom_groups;
     c.n_warm = n_warm;
     c.n_tail = n_tail;
     c.dt = p.dt;
@@ -462,8 +486,7 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
         e = ramppi::fused_rollout_capacity((int)p->noise_kind, h->g.block,
                                            std::max(h->g.lds_rollout, h->g.lds_update), &per_cu);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-        const int64_t grid = h->g.n_nom_wg + ((int64_t)p->K + h->g.spb - 1) / h->g.spb;
-        h->fuse = e == hipSuccess && (int64_t)per_cu * n_cu >= grid;
+        h->fuse = e == hipSuccess && fit_nominal(&h->g, p->K, (int64_t)per_cu * n_cu);
         fa.chunk_ctr = reinterpret_cast<unsigned*>(h->ws + l.chunk);
         fa.counter = reinterpret_cast<unsigned*>(h->ws + l.counter);
         fa.S_tilde = reinterpret_cast<float*>(h->ws + l.S_tilde);
@@ -486,7 +509,6 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
     if (h->flat) {
         h->g.spb = 2;
         h->g.block = 256;
-        h->g.n_nom_wg = (p->K + 255) / 256;
         h->g.lds_rollout = rollout_lds_bytes(2, p);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -692,16 +714,15 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
         return fail(MPPI_EINVAL, "idle_ms = %u outside [1, %u]", idle_ms, kMaxServeIdleMs);
     if (!h->fuse) return fail(MPPI_EUNSUPPORTED, "the step does not run as one launch, so it cannot be served");
     const mppi_params& p = h->p;
-    const Geometry& g = h->g;
+    Geometry g = h->g;
     const size_t lds = std::max(g.lds_rollout, g.lds_update);
     int per_cu = 0, n_cu = 0;
     hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, lds, &per_cu);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device);
     if (e != hipSuccess) return hip_fail(e, "serving occupancy");
-    const int64_t grid = g.n_nom_wg + ((int64_t)p.K + g.spb - 1) / g.spb;
-    if ((int64_t)per_cu * n_cu < grid)
+    if (!fit_nominal(&g, p.K, (int64_t)per_cu * n_cu))
         return fail(MPPI_EUNSUPPORTED, "the serving grid (%lld workgroups) cannot be resident at once",
-                    (long long)grid);
+                    (long long)one_launch_grid(g, p.K));
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     ramppi::StepConst c;
@@ -972,7 +993,6 @@ Geometry batch_geometry(const mppi_params* p) {
     Geometry g = geometry(p);
     g.spb = p->M >= kBatchBlock ? 1 : kBatchBlock / p->M;
     g.block = kBatchBlock;
-    g.n_nom_wg = (p->K + kBatchBlock - 1) / kBatchBlock;
     g.lds_rollout = rollout_lds_bytes(g.spb, p);
     return g;
 }

@@ -59,18 +59,19 @@ __device__ __forceinline__ void batch_rollout_item(const BatchCtl* __restrict__ 
     const float4* obs = as_global(b.obs);
     const float* V = as_global(b.V);
     float2* u = as_global(b.u);
-    float* S = as_global(b.S);
-    float* cvar = as_global(b.cvar);
-    float* L = as_global(b.L);
+    const auto late = [&] {
+        const BatchCtl* e = late_ptr<BatchCtl>(&b);
+        return RolloutLate{&e->c, as_global(e->S), as_global(e->cvar), as_global(e->L), nullptr, nullptr, work};
+    };
     if constexpr (kNoise >= 0) {
-        rollout_body<kNoise>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+        rollout_body<kNoise>(c, obs, V, u, w, bsmem, late);
     } else {
         if (c.noise_kind == 1)
-            rollout_body<1>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+            rollout_body<1>(c, obs, V, u, w, bsmem, late);
         else if (c.noise_kind == 2)
-            rollout_body<2>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+            rollout_body<2>(c, obs, V, u, w, bsmem, late);
         else
-            rollout_body<0>(c, obs, V, u, S, cvar, L, w, bsmem, nullptr, nullptr, work);
+            rollout_body<0>(c, obs, V, u, w, bsmem, late);
     }
 }
 

@@ -195,6 +195,7 @@ struct StepConst {
     int32_t K, T, M, n_obs;
     int32_t spb;         // samples per disturbed workgroup
     int32_t n_nom_wg;    // nominal workgroups: items 0 .. n_nom_wg - 1 (rollout_item orders the grid)
+    int32_t nom_groups;  // groups of 64 samples per nominal workgroup
     int32_t n_warm;      // samples k < n_warm keep the mean sequence
     int32_t n_tail;      // M - ceil(alpha M) + 1
     float dt, inv_wheelbase;
@@ -247,24 +248,6 @@ __device__ __forceinline__ StepConst with_vector_constants(const StepConst& c) {
     v.sw3 = in_vgpr(c.sw3);
     return v;
 }
-
-// with_vector_constants plus the fields of the nominal rollouts' steps
-// (control sampling, clamp and control cost).
-__device__ __forceinline__ StepConst with_vector_constants_nominal(const StepConst& c) {
-    StepConst v = with_vector_constants(c);
-    v.se0 = in_vgpr(c.se0);
-    v.se1 = in_vgpr(c.se1);
-    v.u_lo0 = in_vgpr(c.u_lo0);
-    v.u_lo1 = in_vgpr(c.u_lo1);
-    v.u_hi0 = in_vgpr(c.u_hi0);
-    v.u_hi1 = in_vgpr(c.u_hi1);
-    v.inv_var0 = in_vgpr(c.inv_var0);
-    v.inv_var1 = in_vgpr(c.inv_var1);
-    v.gamma = in_vgpr(c.gamma);
-    v.inv_wheelbase = in_vgpr(c.inv_wheelbase);
-    return v;
-}
-
 
 template <int kNoise>
 __device__ __forceinline__ float4 disturbance(const StepConst& c, uint4 r) {
@@ -604,14 +587,6 @@ __device__ __forceinline__ float2 sample_control_from(const StepConst& c, const 
 __device__ __forceinline__ float2 sample_control(const StepConst& c, const float* __restrict__ V, int k, int t) {
     const uint4 r = philox4x32_10((uint32_t)t, kCtrlWord, (uint32_t)k, c.step_idx, c.key0, c.key1);
     return sample_control_from(c, V, k, t, r, 0x7Fu);
-}
-
-// The same draw with the Philox keys and the exponent word in vector
-// registers (the nominal rollouts' steps).
-__device__ __forceinline__ float2 sample_control(const StepConst& c, const float* __restrict__ V, int k, int t,
-                                                 const PhiloxVKeys& vk, uint32_t exp_word) {
-    const uint4 r = philox4x32_10((uint32_t)t, kCtrlWord, (uint32_t)k, c.step_idx, c.key0, c.key1, vk);
-    return sample_control_from(c, V, k, t, r, exp_word);
 }
 
 // Angle wrap to (-pi, pi].

@@ -38,23 +38,19 @@ __device__ __forceinline__ int rollout_item(const StepConst& c) {
 }
 
 template <int kNoise, bool kFuse>
-__device__ __forceinline__ void rollout_launch_body(const StepConst& c, const float4* __restrict__ obs,
-                                                    const float* __restrict__ V, float2* __restrict__ u_out,
-                                                    float* __restrict__ S_out, float* __restrict__ cvar_out,
-                                                    float* __restrict__ L_out, int* __restrict__ ranks,
-                                                    int* __restrict__ tail_idx, unsigned long long* __restrict__ work,
-                                                    const FuseArgs* __restrict__ fa) {
+__device__ __forceinline__ void rollout_launch_body(const RolloutArgs& a) {
     extern __shared__ float2 smem[];
-    const int item = kFuse ? (int)blockIdx.x : rollout_item(c);
-    rollout_body<kNoise>(c, obs, V, u_out, S_out, cvar_out, L_out, item, smem, ranks, tail_idx, work);
+    const int item = kFuse ? (int)blockIdx.x : rollout_item(a.c);
+    rollout_body<kNoise>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
     if constexpr (kFuse) {
         __shared__ float red[16];
         __shared__ int flag_sh;
         __shared__ int fin_sh[8];
-        const FuseArgs f = global_view(*fa);
+        const RolloutArgs* e = late_args();
+        const FuseArgs f = global_view(*e->fa);
         // V is read by the rollouts and rewritten by the merge, which runs
         // only after every rollout of the step has finished
-        fused_update(c, f, blockIdx.x, S_out, cvar_out, u_out, const_cast<float*>(V),
+        fused_update(e->c, f, blockIdx.x, e->S, e->cvar, e->u, const_cast<float*>(e->V),
                      reinterpret_cast<float*>(smem), red, &flag_sh, fin_sh);
     }
 }
@@ -66,23 +62,15 @@ __device__ __forceinline__ void rollout_launch_body(const StepConst& c, const fl
 // one-launch kernel, whose grid holds two or three waves per SIMD, runs
 // faster with the registers it needs).
 template <int kNoise>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
-    k_rollout(StepConst c, const float4* __restrict__ obs, const float* __restrict__ V, float2* __restrict__ u_out,
-              float* __restrict__ S_out, float* __restrict__ cvar_out, float* __restrict__ L_out,
-              int* __restrict__ ranks, int* __restrict__ tail_idx, unsigned long long* __restrict__ work,
-              const FuseArgs* __restrict__ fa) {
-    rollout_launch_body<kNoise, false>(c, obs, V, u_out, S_out, cvar_out, L_out, ranks, tail_idx, work, fa);
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) k_rollout(RolloutArgs a) {
+    rollout_launch_body<kNoise, false>(a);
 }
 
 // The one-launch step: rollouts, then the update in the workgroups that
 // finish each chunk.
 template <int kNoise>
-__global__ void __launch_bounds__(1024)
-    k_rollout_fused(StepConst c, const float4* __restrict__ obs, const float* __restrict__ V,
-                    float2* __restrict__ u_out, float* __restrict__ S_out, float* __restrict__ cvar_out,
-                    float* __restrict__ L_out, int* __restrict__ ranks, int* __restrict__ tail_idx,
-                    unsigned long long* __restrict__ work, const FuseArgs* __restrict__ fa) {
-    rollout_launch_body<kNoise, true>(c, obs, V, u_out, S_out, cvar_out, L_out, ranks, tail_idx, work, fa);
+__global__ void __launch_bounds__(1024) k_rollout_fused(RolloutArgs a) {
+    rollout_launch_body<kNoise, true>(a);
 }
 
 // Persistent serving: the one-launch step in a loop, one iteration per
@@ -90,10 +78,7 @@ __global__ void __launch_bounds__(1024)
 // the requests from host memory; the others wait on its device-memory word.
 // Every wait is bounded, so every wave leaves even if no request comes.
 template <int kNoise>
-__global__ void __launch_bounds__(1024) k_serve(StepConst c0, const float4* __restrict__ obs, float* V,
-                                                float2* __restrict__ u_out, float* __restrict__ S_out,
-                                                float* __restrict__ cvar_out, float* __restrict__ L_out,
-                                                const FuseArgs* __restrict__ fa, ServeArgs sa_arg) {
+__global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg) {
     extern __shared__ float2 smem[];
     const ServeArgs sa = global_view(sa_arg);
     __shared__ float red[16];
@@ -104,16 +89,12 @@ __global__ void __launch_bounds__(1024) k_serve(StepConst c0, const float4* __re
         if (threadIdx.x == 0) leave_sh = blockIdx.x == 0 ? serve_wait_leader(sa, seq) : serve_wait_member(sa, seq);
         __syncthreads();
         if (leave_sh) break;
-        // Every word of the step constants passes through an empty asm per
-        // request: the compiler then derives what the step needs (the
-        // Philox round keys, ...) inside the loop instead of keeping it live
-        // across requests, which spilled it into VGPR lanes of the hot loop.
-        StepConst c = c0;
-        {
-            uint32_t* wc = reinterpret_cast<uint32_t*>(&c);
-#pragma unroll
-            for (int i = 0; i < (int)(sizeof(StepConst) / 4); ++i) asm volatile("" : "+s"(wc[i]));
-        }
+        // The arguments are read again for every request (late_args): the
+        // compiler then derives what the step needs (the Philox round keys,
+        // ...) inside the loop instead of keeping it live across requests,
+        // which spilled it into VGPR lanes of the hot loop.
+        const RolloutArgs* p = late_args();
+        StepConst c = p->c;
         const ServeReq* r = sa.req_dev;
         c.fx = r->fx;
         c.fy = r->fy;
@@ -123,11 +104,14 @@ __global__ void __launch_bounds__(1024) k_serve(StepConst c0, const float4* __re
         c.psi0 = r->psi0;
         c.v0 = r->v0;
         c.step_idx = r->step_idx;
-        c.u0_seq = seq;
-        rollout_body<kNoise>(c, obs, V, u_out, S_out, cvar_out, L_out, blockIdx.x, smem);
-        const FuseArgs f = global_view(*fa);
-        fused_update(c, f, blockIdx.x, S_out, cvar_out, u_out, V, reinterpret_cast<float*>(smem), red, &flag_sh,
-                     fin_sh);
+        rollout_body<kNoise>(c, p->obs, p->V, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
+        const RolloutArgs* e = late_args();
+        StepConst ce = e->c;
+        ce.step_idx = c.step_idx;
+        ce.u0_seq = seq;
+        const FuseArgs f = global_view(*e->fa);
+        fused_update(ce, f, blockIdx.x, e->S, e->cvar, e->u, const_cast<float*>(e->V),
+                     reinterpret_cast<float*>(smem), red, &flag_sh, fin_sh);
         __syncthreads();  // LDS and leave_sh are reused by the next request
     }
 }
@@ -257,29 +241,29 @@ __global__ void __launch_bounds__(1024) k_cvar_sorted(const float* __restrict__ 
 
 // ---- launchers ----
 
+static RolloutArgs rollout_args(const StepConst& c, const StepBuffers& b, int* ranks, int* tail_idx,
+                                const FuseArgs* fa) {
+    return RolloutArgs{c, b.obs, b.V, b.u, b.S, b.cvar, b.L, ranks, tail_idx, b.work, fa};
+}
+
 template <bool kFuse>
 static void launch_rollout_t(const StepConst& c, const StepBuffers& b, dim3 grid, int block, size_t lds,
                              hipStream_t stream, int* ranks, int* tail_idx, const FuseArgs* fa) {
+    const RolloutArgs a = rollout_args(c, b, ranks, tail_idx, fa);
     if constexpr (kFuse) {
         if (c.noise_kind == 1)
-            hipLaunchKernelGGL(k_rollout_fused<1>, grid, dim3(block), lds, stream, c, b.obs, b.V, b.u, b.S, b.cvar,
-                               b.L, ranks, tail_idx, b.work, fa);
+            hipLaunchKernelGGL(k_rollout_fused<1>, grid, dim3(block), lds, stream, a);
         else if (c.noise_kind == 2)
-            hipLaunchKernelGGL(k_rollout_fused<2>, grid, dim3(block), lds, stream, c, b.obs, b.V, b.u, b.S, b.cvar,
-                               b.L, ranks, tail_idx, b.work, fa);
+            hipLaunchKernelGGL(k_rollout_fused<2>, grid, dim3(block), lds, stream, a);
         else
-            hipLaunchKernelGGL(k_rollout_fused<0>, grid, dim3(block), lds, stream, c, b.obs, b.V, b.u, b.S, b.cvar,
-                               b.L, ranks, tail_idx, b.work, fa);
+            hipLaunchKernelGGL(k_rollout_fused<0>, grid, dim3(block), lds, stream, a);
     } else {
         if (c.noise_kind == 1)
-            hipLaunchKernelGGL(k_rollout<1>, grid, dim3(block), lds, stream, c, b.obs, b.V, b.u, b.S, b.cvar, b.L,
-                               ranks, tail_idx, b.work, fa);
+            hipLaunchKernelGGL(k_rollout<1>, grid, dim3(block), lds, stream, a);
         else if (c.noise_kind == 2)
-            hipLaunchKernelGGL(k_rollout<2>, grid, dim3(block), lds, stream, c, b.obs, b.V, b.u, b.S, b.cvar, b.L,
-                               ranks, tail_idx, b.work, fa);
+            hipLaunchKernelGGL(k_rollout<2>, grid, dim3(block), lds, stream, a);
         else
-            hipLaunchKernelGGL(k_rollout<0>, grid, dim3(block), lds, stream, c, b.obs, b.V, b.u, b.S, b.cvar, b.L,
-                               ranks, tail_idx, b.work, fa);
+            hipLaunchKernelGGL(k_rollout<0>, grid, dim3(block), lds, stream, a);
     }
 }
 
@@ -307,15 +291,13 @@ hipError_t serve_capacity(int noise_kind, int block, size_t lds, int* blocks_per
 hipError_t launch_serve(const StepConst& c, const StepBuffers& b, int block, size_t lds, const FuseArgs* fa,
                         const ServeArgs& sa, hipStream_t stream) {
     const dim3 grid(c.n_nom_wg + (c.K + c.spb - 1) / c.spb);
+    const RolloutArgs a = rollout_args(c, b, nullptr, nullptr, fa);
     if (c.noise_kind == 1)
-        hipLaunchKernelGGL(k_serve<1>, grid, dim3(block), lds, stream, c, b.obs, b.Vout, b.u, b.S, b.cvar, b.L, fa,
-                           sa);
+        hipLaunchKernelGGL(k_serve<1>, grid, dim3(block), lds, stream, a, sa);
     else if (c.noise_kind == 2)
-        hipLaunchKernelGGL(k_serve<2>, grid, dim3(block), lds, stream, c, b.obs, b.Vout, b.u, b.S, b.cvar, b.L, fa,
-                           sa);
+        hipLaunchKernelGGL(k_serve<2>, grid, dim3(block), lds, stream, a, sa);
     else
-        hipLaunchKernelGGL(k_serve<0>, grid, dim3(block), lds, stream, c, b.obs, b.Vout, b.u, b.S, b.cvar, b.L, fa,
-                           sa);
+        hipLaunchKernelGGL(k_serve<0>, grid, dim3(block), lds, stream, a, sa);
     return hipGetLastError();
 }
 

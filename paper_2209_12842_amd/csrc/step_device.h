@@ -55,6 +55,67 @@ __device__ __forceinline__ void group_bounds(const float4* __restrict__ obs, int
     }
 }
 
+// Time steps whose points share one broad-phase box (obstacle_hits_culled):
+// a longer run divides the box and group tests over more steps but widens
+// the box by the distance travelled; 6 gave the shortest steps on the 50- and
+// 200-obstacle tracks (horizons 50 and 100).
+constexpr int kCullSteps = 6;
+// LDS floats of a nominal workgroup before the obstacle table (aligned to 16
+// bytes): two buffers of one run of sampled controls for 64 samples, (dt a,
+// tan(delta) / wheelbase) and the control-cost term of each.
+constexpr int kNomBuf = 3 * 64 * kCullSteps;
+
+// Arguments of a rollout kernel: one struct, the kernel's first parameter, so
+// that a workgroup can read it again from the kernel-argument segment after
+// its rollouts (RolloutLate).
+struct RolloutArgs {
+    StepConst c;
+    const float4* obs;
+    const float* V;
+    float2* u;
+    float* S;
+    float* cvar;
+    float* L;
+    int* ranks;
+    int* tail_idx;
+    unsigned long long* work;  // broad-phase counters, or null
+    const struct FuseArgs* fa;  // the update's buffers (one-launch step)
+};
+
+// What a workgroup needs after its rollouts.  The compiler loads every kernel
+// argument when the kernel begins and keeps in scalar registers, or spilled
+// into vector-register lanes, whatever the end of the kernel uses; read again
+// through a pointer it cannot see through (late_ptr), these values need no
+// register while the rollouts run (scalar spills of the one-launch kernel
+// 118 -> 69, of k_serve 188 -> 91).
+struct RolloutLate {
+    const StepConst* c;
+    float* S;
+    float* cvar;
+    float* L;
+    int* ranks;
+    int* tail_idx;
+    unsigned long long* work;
+};
+
+// p as a pointer into constant memory of unknown origin (the loads through it
+// are scalar loads and stay after this point).
+template <class T>
+__device__ __forceinline__ const T* late_ptr(const void* p) {
+    uint64_t v = (uint64_t)(uintptr_t)p;
+    asm volatile("" : "+s"(v));
+    return (const T*)(const __attribute__((address_space(4))) T*)(uintptr_t)v;
+}
+
+// The kernel's own arguments, read again.
+__device__ __forceinline__ const RolloutArgs* late_args() {
+    return late_ptr<RolloutArgs>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
+__device__ __forceinline__ RolloutLate late_view(const RolloutArgs* a) {
+    return RolloutLate{&a->c, a->S, a->cvar, a->L, a->ranks, a->tail_idx, a->work};
+}
+
 // LDS layout of k_rollout (dynamic shared memory, in this order):
 //   float2 ctl[spb * T]   (dt a, tan(delta) / wheelbase) of the WG's samples
 //   float  vals[spb * M]  risk costs of the WG's samples
@@ -63,10 +124,13 @@ __device__ __forceinline__ void group_bounds(const float4* __restrict__ obs, int
 //   float4 otab[64 n_grp] the obstacle table, padded to groups of 64 entries
 //                         (16-byte aligned; n_grp = ceil(n_obs / 64))
 //   float4 gbox[64]       the groups' boxes for the group skip (group_bounds)
-// rollout_otab_offset gives the offset of otab in floats.  Every workgroup
-// writes otab and gbox from the raw obstacles before its rollouts.
+// Nominal workgroups keep their runs of sampled controls (2 kNomBuf floats)
+// before otab instead.  rollout_otab_offset gives the offset of otab in
+// floats.  Every workgroup writes otab and gbox from the raw obstacles before
+// its rollouts.
 __host__ __device__ __forceinline__ int rollout_otab_offset(int spb, int T, int M) {
-    return (2 * spb * T + 2 * spb * M + spb + 3) & ~3;
+    const int dist = (2 * spb * T + 2 * spb * M + spb + 3) & ~3;
+    return dist > 2 * kNomBuf ? dist : 2 * kNomBuf;
 }
 
 __host__ __device__ __forceinline__ int rollout_n_grp(int n_obs) { return (n_obs + 63) >> 6; }
@@ -85,11 +149,6 @@ constexpr BoolFalse kFalse{};
 // (16 i + w) mod kWorkSlots, spreading the atomics): exact tests in
 // work[0..kWorkSlots), group tests in work[kWorkSlots..2 kWorkSlots).
 constexpr int kWorkSlots = 256;
-// Time steps whose points share one broad-phase box (obstacle_hits_culled):
-// a longer run divides the box and group tests over more steps but widens
-// the box by the distance travelled; 6 gave the shortest steps on the 50- and
-// 200-obstacle tracks (horizons 50 and 100).
-constexpr int kCullSteps = 6;
 // Scal, Max and Average of Algorithm 1 for the spb samples of a workgroup.
 // vals holds the raw risk costs (thread tid owns slot tid for tid < spb * M);
 // returns the CVaR in the m == 0 lane of each sample.  The descending order
@@ -189,21 +248,132 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
     }
 }
 
+// The nominal rollouts of a workgroup: c.nom_groups groups of 64 samples, one
+// after the other; in each, the first wave rolls the 64 samples out (one per
+// lane; lanes past K repeat the last sample, since the obstacle test works on
+// whole waves, and write nothing) while the other waves sample the controls
+// of the next run of kCullSteps steps into LDS, one barrier per run.  The
+// rollouts are a chain of T steps bound by latency and by the issue slots
+// that the disturbed waves leave, and drawing the controls (Philox,
+// Box-Muller, the steering tangent) is 60 % of a nominal step's
+// instructions: moved off the chain, the nominal rollouts of K = 2048, T = 50,
+// M = 64 end at 27 us of the launch instead of 35 us and no longer finish
+// last (step 37.2 -> 33.4 us with RolloutLate).  On grids of many rounds the
+// three waves that wait cost about 1 % of the step (K = 16384, T = 100,
+// M = 128: 614 -> 621 us).
+template <class Late>
+__device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float* __restrict__ V,
+                                                 float2* __restrict__ u_out, int item, float2* smem,
+                                                 const float4* otab, const float4* gbox, int n_grp, int& n_cand,
+                                                 int& n_gtest, Late late) {
+    float* buf = reinterpret_cast<float*>(smem);
+    const int T = c.T;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n_waves = (int)blockDim.x >> 6;  // at least 3 (spb M > 128)
+    const int n_runs = (T + kCullSteps - 1) / kCullSteps;
+    for (int g = 0; g < c.nom_groups; ++g) {
+        const int k0 = (item * c.nom_groups + g) * 64;
+        if (k0 >= c.K) break;  // uniform
+        const int k = k0 + lane;
+        const bool act = k < c.K;
+        const int kc = act ? k : c.K - 1;
+        // the controls of run r, its steps shared out over `count` waves
+        const auto produce = [&](int r, int first, int count) {
+            float* b = buf + (r & 1) * kNomBuf;
+            for (int i = first; i < kCullSteps; i += count) {
+                const int t = r * kCullSteps + i;
+                if (t >= T) break;  // uniform
+                const float2 u = sample_control(c, V, kc, t);
+                if (c.store_u && act) u_out[(size_t)t * c.K + k] = u;
+                reinterpret_cast<float2*>(b)[i * 64 + lane] = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
+                b[2 * 64 * kCullSteps + i * 64 + lane] =
+                    __fmaf_rn(V[2 * t] * c.inv_var0, u.x, V[2 * t + 1] * c.inv_var1 * u.y);
+            }
+        };
+        produce(0, wave, n_waves);
+        __syncthreads();  // the first run's controls, and the table, staged
+        if (wave != 0) {
+            for (int r = 1; r <= n_runs; ++r) {
+                if (r < n_runs) produce(r, wave - 1, n_waves - 1);
+                __syncthreads();
+            }
+            continue;
+        }
+        const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        State s{0.0f, 0.0f, c.psi0, c.v0};
+        float acc = 0.0f, ctrl = 0.0f;
+        int cnt = 0;
+        const StepConst cn = with_vector_constants(c);
+        const float gamma = in_vgpr(c.gamma);
+        for (int r = 0; r < n_runs; ++r) {
+            const float* b = buf + (r & 1) * kNomBuf;
+            // one nominal state step: running and control costs at x_t (the
+            // control cost is summed in every case and used when asked, so
+            // that the step holds no branch), then x_{t+1}
+            auto step = [&](auto bdry, int i, float& px, float& py) {
+                acc = smooth_cost_acc<decltype(bdry)::value>(cn, s, acc);
+                px = s.x;
+                py = s.y;
+                const float2 cu = reinterpret_cast<const float2*>(b)[i * 64 + lane];
+                ctrl = __fmaf_rn(gamma, b[2 * 64 * kCullSteps + i * 64 + lane], ctrl);
+                bicycle_step(s, cu.x, cu.y, cn.dt);
+            };
+            float px[kCullSteps], py[kCullSteps];
+            if ((r + 1) * kCullSteps <= T) {  // a whole run of steps with no branch between them
+                if (c.use_bdry) {
+#pragma unroll
+                    for (int i = 0; i < kCullSteps; ++i) step(kTrue, i, px[i], py[i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kCullSteps; ++i) step(kFalse, i, px[i], py[i]);
+                }
+                if (n_grp > 0)
+                    cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, kCullSteps, n_cand, n_gtest);
+            } else {
+                const int n = T - r * kCullSteps;
+#pragma unroll
+                for (int i = 0; i < kCullSteps; ++i) {
+                    if (i < n) {
+                        if (c.use_bdry)
+                            step(kTrue, i, px[i], py[i]);
+                        else
+                            step(kFalse, i, px[i], py[i]);
+                    } else {
+                        px[i] = px[i > 0 ? i - 1 : 0];
+                        py[i] = py[i > 0 ? i - 1 : 0];
+                    }
+                }
+                if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
+            }
+            __syncthreads();  // the next run's controls are in, this run's are read
+        }
+        const RolloutLate e = late();
+        float S = __fmaf_rn(e.c->c_obs, (float)cnt, acc);
+        if (e.c->use_ctrl) S += ctrl;
+        if (e.c->use_term) S += terminal_cost(c, s);
+        if (act) e.S[k] = S;
+    }
+}
+
+// Adds a wave's broad-phase work to its slot of the counters (timing mode).
+__device__ __forceinline__ void count_work(unsigned long long* work, int item, int n_cand, int n_gtest) {
+    if (work && (threadIdx.x & 63) == 0) {
+        const int slot = (item * 16 + ((int)threadIdx.x >> 6)) & (kWorkSlots - 1);
+        atomicAdd(&work[slot], (unsigned long long)n_cand);
+        atomicAdd(&work[kWorkSlots + slot], (unsigned long long)n_gtest);
+    }
+}
+
 // One workgroup's share of the rollouts of a step: item < n_nom_wg is a
 // nominal workgroup (one lane per sample), otherwise a disturbed workgroup
 // (spb samples of M lanes).  Ends with every lane past its last LDS access
 // (the caller may reuse the LDS after a barrier).
-template <int kNoise>
+template <int kNoise, class Late>
 __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* __restrict__ obs,
-                                             const float* __restrict__ V, float2* __restrict__ u_out,
-                                             float* __restrict__ S_out, float* __restrict__ cvar_out,
-                                             float* __restrict__ L_out, int item, float2* smem,
-                                             int* __restrict__ ranks = nullptr, int* __restrict__ tail_idx = nullptr,
-                                             unsigned long long* __restrict__ work = nullptr) {
+                                             const float* __restrict__ V, float2* __restrict__ u_out, int item,
+                                             float2* smem, Late late) {
     float2* ctl = smem;
-    float* vals = reinterpret_cast<float*>(ctl + (size_t)c.spb * c.T);
-    float* tail = vals + c.spb * c.M;
-    float* means = tail + c.spb * c.M;
     const int tid = threadIdx.x;
     const int spb = c.spb, M = c.M, T = c.T;
     const int n_grp = rollout_n_grp(c.n_obs);
@@ -215,77 +385,8 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
     int n_gtest = 0;  // broad-phase group tests of this wave (wave-uniform)
 
     if (item < c.n_nom_wg) {
-        // ---- nominal rollouts: one lane per sample; lanes past K repeat
-        // the last sample (the obstacle test works on whole waves) and write
-        // nothing.  V is staged into LDS (the controls' region, unused here),
-        // so that no step waits for a global load ----
-        __builtin_amdgcn_s_setprio(0);
-        float* vsh = reinterpret_cast<float*>(ctl);  // 2T floats <= 2 spb T
-        for (int i = tid; i < 2 * T; i += blockDim.x) vsh[i] = V[i];
-        __syncthreads();  // otab and V staged
-        const int k = item * blockDim.x + tid;
-        const bool act = k < c.K;
-        const bool store = act && c.store_u;
-        const int kc = act ? k : c.K - 1;
-        const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[tid & 63] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        State s{0.0f, 0.0f, c.psi0, c.v0};
-        float acc = 0.0f, ctrl = 0.0f;
-        int cnt = 0;
-        const StepConst cn = with_vector_constants_nominal(c);
-        const PhiloxVKeys vk = philox_vkeys(c.key0, c.key1);
-        const uint32_t exp_word = in_vgpr_u(0x7Fu);
-        // one nominal state step: the sampled control, running and control
-        // costs at x_t (the control cost is summed in every case and used
-        // when asked, so that the step holds no branch), then x_{t+1}
-        auto step = [&](auto bdry, int t, float& px, float& py) {
-            const float2 u = sample_control(cn, vsh, kc, t, vk, exp_word);
-            if (store) u_out[(size_t)t * c.K + k] = u;
-            acc = smooth_cost_acc<decltype(bdry)::value>(cn, s, acc);
-            px = s.x;
-            py = s.y;
-            const float term = __fmaf_rn(vsh[2 * t] * cn.inv_var0, u.x, vsh[2 * t + 1] * cn.inv_var1 * u.y);
-            ctrl = __fmaf_rn(cn.gamma, term, ctrl);
-            bicycle_step(s, cn.dt * u.x, tan_steer(u.y) * cn.inv_wheelbase, cn.dt);
-        };
-        for (int t0 = 0; t0 < T; t0 += kCullSteps) {  // the obstacle test runs once per kCullSteps points
-            float px[kCullSteps], py[kCullSteps];
-            int n = kCullSteps;
-            if (t0 + kCullSteps <= T) {  // a whole run of steps with no branch between them
-                if (c.use_bdry) {
-#pragma unroll
-                    for (int i = 0; i < kCullSteps; ++i) step(kTrue, t0 + i, px[i], py[i]);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < kCullSteps; ++i) step(kFalse, t0 + i, px[i], py[i]);
-                }
-            } else {
-                n = 0;
-#pragma unroll
-                for (int i = 0; i < kCullSteps; ++i) {
-                    const int t = t0 + i;
-                    if (t < T) {
-                        if (c.use_bdry)
-                            step(kTrue, t, px[i], py[i]);
-                        else
-                            step(kFalse, t, px[i], py[i]);
-                        n = i + 1;
-                    } else {
-                        px[i] = px[i > 0 ? i - 1 : 0];
-                        py[i] = py[i > 0 ? i - 1 : 0];
-                    }
-                }
-            }
-            if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
-        }
-        float S = __fmaf_rn(c.c_obs, (float)cnt, acc);
-        if (c.use_ctrl) S += ctrl;
-        if (c.use_term) S += terminal_cost(c, s);
-        if (act) S_out[k] = S;
-        if (work && (tid & 63) == 0) {
-            const int slot = (item * 16 + (tid >> 6)) & (kWorkSlots - 1);
-            atomicAdd(&work[slot], (unsigned long long)n_cand);
-            atomicAdd(&work[kWorkSlots + slot], (unsigned long long)n_gtest);
-        }
+        nominal_rollouts(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
+        count_work(late().work, item, n_cand, n_gtest);
         return;
     }
 
@@ -331,6 +432,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
         k = wg * spb + sl;
     }
     float L = 0.0f;
+    int hits = 0;
     {
         const StepConst cv = with_vector_constants(c);
         const PhiloxVKeys vk = philox_vkeys(c.key0, c.key1);
@@ -358,7 +460,6 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
         };
         for (int t0 = 0; t0 < T; t0 += kCullSteps) {  // the obstacle test runs once per kCullSteps points
             float px[kCullSteps], py[kCullSteps];
-            int n = kCullSteps;
             if (t0 + kCullSteps < T) {
                 // a whole run of steps with no branch between them, so that
                 // the noise of later steps can be computed beside the
@@ -370,78 +471,76 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
 #pragma unroll
                     for (int i = 0; i < kCullSteps; ++i) step(kFalse, t0 + i, true, px[i], py[i]);
                 }
+                if (n_grp > 0)
+                    cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, kCullSteps, n_cand, n_gtest);
             } else {
-                n = 0;
+                const int n = T - t0;
 #pragma unroll
                 for (int i = 0; i < kCullSteps; ++i) {
-                    const int t = t0 + i;
-                    if (t < T) {
+                    if (i < n) {
                         if (c.use_bdry)
-                            step(kTrue, t, t + 1 < T, px[i], py[i]);
+                            step(kTrue, t0 + i, i + 1 < n, px[i], py[i]);
                         else
-                            step(kFalse, t, t + 1 < T, px[i], py[i]);
-                        n = i + 1;
+                            step(kFalse, t0 + i, i + 1 < n, px[i], py[i]);
                     } else {
                         px[i] = px[i > 0 ? i - 1 : 0];
                         py[i] = py[i > 0 ? i - 1 : 0];
                     }
                 }
+                if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
             }
-            if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
         }
-        L = __fmaf_rn(c.c_obs, (float)cnt, acc);
+        L = acc;
+        hits = cnt;
     }
-    if (c.flat) {
+    // From here on the arguments are read again (RolloutLate), and the lane's
+    // sample and draw are derived again from a copy of the thread index that
+    // the compiler cannot tie to the one above, so that nothing but the cost
+    // needs a register through the rollout (the kernel runs at its register
+    // limit).
+    const RolloutLate e = late();
+    const StepConst& ce = *e.c;
+    int tid_e = tid;
+    asm volatile("" : "+v"(tid_e));
+    L = __fmaf_rn(ce.c_obs, (float)hits, L);
+    if (ce.flat) {
         // the risk costs go to memory; a separate pass forms each sample's
-        // CVaR from them (k_cvar_sorted, the same order); the pair index again
-        // from a copy of the thread index (see below)
-        int tid_f = tid;
-        asm volatile("" : "+v"(tid_f));
-        const uint32_t g = (uint32_t)wg * blockDim.x + (uint32_t)tid_f;
-        if (g < KM) L_out[g] = L;
-        if (work && (tid & 63) == 0) {
-            const int slot = (item * 16 + (tid >> 6)) & (kWorkSlots - 1);
-            atomicAdd(&work[slot], (unsigned long long)n_cand);
-            atomicAdd(&work[kWorkSlots + slot], (unsigned long long)n_gtest);
-        }
+        // CVaR from them (k_cvar_wave, k_cvar_sorted: the same order)
+        const uint32_t g = (uint32_t)wg * blockDim.x + (uint32_t)tid_e;
+        if (g < (uint32_t)ce.K * (uint32_t)ce.M) e.L[g] = L;
+        count_work(e.work, item, n_cand, n_gtest);
         return;
     }
-    // The lane's sample and draw again, from copies of the thread index and
-    // of M that the compiler cannot tie to the ones above: the values derived
-    // before the rollout (the quotient, the divisor's reciprocal) then need
-    // no register through it (the rollout kernel runs at its register limit,
-    // and keeping them cost scratch-memory spills).
-    int tid_e = tid, M_e = M;
-    asm volatile("" : "+v"(tid_e), "+s"(M_e));
+    const int M_e = ce.M, spb_e = ce.spb;
     const int sl_e = tid_e / M_e;
     const int m_e = tid_e - sl_e * M_e;
-    const int k_e = wg * spb + sl_e;
-    const bool active_e = (sl_e < spb) && (k_e < c.K);
-    if (active_e && c.debug) L_out[(size_t)k_e * M + m_e] = L;
-    if (!c.grad && c.n_tail <= kWaveTail) {
-        if (sl_e < spb) vals[tid_e] = active_e ? L : 0.0f;
-        cvar_waves(vals, spb, M_e, c.n_tail, c.scale_risk, c.B, tid_e, [&](int s, float cv) {
-            const int ks = wg * spb + s;
-            if (ks < c.K) cvar_out[ks] = cv;
+    const int k_e = wg * spb_e + sl_e;
+    const bool active_e = (sl_e < spb_e) && (k_e < ce.K);
+    if (active_e && ce.debug) e.L[(size_t)k_e * M_e + m_e] = L;
+    float* vals = reinterpret_cast<float*>(smem + (size_t)spb_e * ce.T);
+    float* tail = vals + spb_e * M_e;
+    float* means = tail + spb_e * M_e;
+    if (!ce.grad && ce.n_tail <= kWaveTail) {
+        if (sl_e < spb_e) vals[tid_e] = active_e ? L : 0.0f;
+        cvar_waves(vals, spb_e, M_e, ce.n_tail, ce.scale_risk, ce.B, tid_e, [&](int q, float cv) {
+            const int ks = wg * spb_e + q;
+            if (ks < ce.K) e.cvar[ks] = cv;
         });
     } else {
-        if (sl_e < spb) {
+        if (sl_e < spb_e) {
             vals[tid_e] = active_e ? L : 0.0f;
             tail[tid_e] = __builtin_nanf("");
         }
-        int pos = M, id = m_e;
-        const float cv = cvar_epilogue(vals, tail, means, spb, M_e, c.n_tail, c.scale_risk, c.B, &pos, &id, tid_e);
-        if (active_e && m_e == 0) cvar_out[k_e] = cv;
-        if (c.grad && active_e) {  // tail membership for the gradient
-            ranks[(size_t)k_e * M + id] = pos;
-            if (pos < c.n_tail) tail_idx[(size_t)k_e * c.n_tail + pos] = id;
+        int pos = M_e, id = m_e;
+        const float cv =
+            cvar_epilogue(vals, tail, means, spb_e, M_e, ce.n_tail, ce.scale_risk, ce.B, &pos, &id, tid_e);
+        if (active_e && m_e == 0) e.cvar[k_e] = cv;
+        if (ce.grad && active_e) {  // tail membership for the gradient
+            e.ranks[(size_t)k_e * M_e + id] = pos;
+            if (pos < ce.n_tail) e.tail_idx[(size_t)k_e * ce.n_tail + pos] = id;
         }
     }
-    if (work && (tid & 63) == 0) {
-        const int slot = (item * 16 + (tid >> 6)) & (kWorkSlots - 1);
-        atomicAdd(&work[slot], (unsigned long long)n_cand);
-        atomicAdd(&work[kWorkSlots + slot], (unsigned long long)n_gtest);
-    }
+    count_work(e.work, item, n_cand, n_gtest);
 }
 
 // Sum and minimum of 256 values held in LDS (v[0..255]) in a fixed order that
@@ -987,10 +1086,11 @@ __device__ __forceinline__ bool serve_wait_member(const ServeArgs& sa, unsigned 
 }
 
 // Workgroups of a rollout launch whose samples fall in chunk b: the nominal
-// workgroups (block samples each) and the disturbed ones (spb samples each).
-__device__ __forceinline__ unsigned chunk_contributors(const StepConst& c, int b, int block) {
+// workgroups (64 nom_groups samples each) and the disturbed ones (spb each).
+__device__ __forceinline__ unsigned chunk_contributors(const StepConst& c, int b) {
     const int klo = 256 * b, khi = min(c.K, klo + 256) - 1;
-    return (unsigned)((khi / block - klo / block + 1) + (khi / c.spb - klo / c.spb + 1));
+    const int nom = 64 * c.nom_groups;
+    return (unsigned)((khi / nom - klo / nom + 1) + (khi / c.spb - klo / c.spb + 1));
 }
 
 // After a rollout workgroup has stored its results: it counts itself in the
@@ -1003,8 +1103,8 @@ __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs&
                                              int* flag_sh, int* fin_sh) {
     int lo, hi;
     if (item < c.n_nom_wg) {
-        lo = item * (int)blockDim.x;
-        hi = min(c.K, lo + (int)blockDim.x);
+        lo = item * 64 * c.nom_groups;
+        hi = min(c.K, lo + 64 * c.nom_groups);
     } else {
         lo = (item - c.n_nom_wg) * c.spb;
         hi = min(c.K, lo + c.spb);
@@ -1013,7 +1113,7 @@ __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs&
     if (threadIdx.x == 0) {
         int nf = 0;
         for (int b = lo >> 8; b <= (hi - 1) >> 8; ++b) {
-            const unsigned target = chunk_contributors(c, b, (int)blockDim.x);
+            const unsigned target = chunk_contributors(c, b);
             // a release increment; only the workgroup that completes the
             // chunk acquires, so the others keep their caches
             const unsigned done =
