@@ -83,6 +83,13 @@ std::vector<int> obstacle_order(const float* o, int n) {
 // Mapped pinned bytes per handle: the first command (2 floats), its
 // completion word, one spare word, then the serving request.
 constexpr size_t kPinnedBytes = 16 + sizeof(ramppi::ServeReq);
+// A call that awaits a completion word asks the stream for an error every
+// kQueryMask + 1 polls, about two milliseconds: a stream query takes some 10
+// us of host time, and one that falls into the last microseconds of a step
+// delays its command by as much (asked every 1024 polls, about 30 us, a step
+// of K = 1000, T = 45, M = 48 with a 24 us kernel returned after 46 us, now
+// after 33).
+constexpr uint64_t kQueryMask = 65535;
 // Longest idle limit of a serving launch.
 constexpr uint32_t kMaxServeIdleMs = 60000;
 
@@ -576,12 +583,12 @@ mppi_status mppi_step(mppi_handle* h, const float x0[4], float* V_dev, uint32_t 
     if (u0_host) {
         // the update kernel stores the command and then the completion word
         // into the mapped pinned buffer: poll the word (asking the stream now
-        // and then, so that a failed step still returns) rather than waiting
-        // for the whole stream
+        // and then, kQueryMask, so that a failed step still returns) rather
+        // than waiting for the whole stream
         const uint32_t* word = reinterpret_cast<const uint32_t*>(h->u0_pinned + 2);
         for (uint64_t spin = 1;; ++spin) {
             if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == h->u0_seq) break;
-            if ((spin & 1023) == 0) {
+            if ((spin & kQueryMask) == 0) {
                 const hipError_t q = hipStreamQuery(s);
                 if (q == hipSuccess) {  // the step is complete, so is its word
                     if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == h->u0_seq) break;
@@ -785,7 +792,7 @@ mppi_status mppi_serve_step(mppi_handle* h, const float x0[4], uint32_t step_idx
     const uint32_t* word = reinterpret_cast<const uint32_t*>(h->u0_pinned + 2);
     for (uint64_t spin = 1;; ++spin) {
         if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == h->serve_seq) break;
-        if ((spin & 1023) == 0) {
+        if ((spin & kQueryMask) == 0) {
             const hipError_t q = hipStreamQuery(h->serve_stream);
             if (q == hipSuccess) {  // the serving launch has left (its idle limit passed)
                 if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == h->serve_seq) break;
