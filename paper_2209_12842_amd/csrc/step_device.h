@@ -352,7 +352,7 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float
         float S = __fmaf_rn(e.c->c_obs, (float)cnt, acc);
         if (e.c->use_ctrl) S += ctrl;
         if (e.c->use_term) S += terminal_cost(c, s);
-        if (act) e.S[k] = S;
+        if (act) agent_store(&e.S[k], S);
     }
 }
 
@@ -524,7 +524,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
         if (sl_e < spb_e) vals[tid_e] = active_e ? L : 0.0f;
         cvar_waves(vals, spb_e, M_e, ce.n_tail, ce.scale_risk, ce.B, tid_e, [&](int q, float cv) {
             const int ks = wg * spb_e + q;
-            if (ks < ce.K) e.cvar[ks] = cv;
+            if (ks < ce.K) agent_store(&e.cvar[ks], cv);
         });
     } else {
         if (sl_e < spb_e) {
@@ -534,7 +534,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float4* _
         int pos = M_e, id = m_e;
         const float cv =
             cvar_epilogue(vals, tail, means, spb_e, M_e, ce.n_tail, ce.scale_risk, ce.B, &pos, &id, tid_e);
-        if (active_e && m_e == 0) e.cvar[k_e] = cv;
+        if (active_e && m_e == 0) agent_store(&e.cvar[k_e], cv);
         if (ce.grad && active_e) {  // tail membership for the gradient
             e.ranks[(size_t)k_e * M_e + id] = pos;
             if (pos < ce.n_tail) e.tail_idx[(size_t)k_e * ce.n_tail + pos] = id;
@@ -581,7 +581,9 @@ __device__ __forceinline__ float seg_min_256(const float* v, float* red) {
 //     beta_b, its weights exp(-(S~ - beta_b)/lambda) and their sum Z_b;
 //  2. (update_chunk) the chunk's weighted control sums N_b[t] = sum_k w_k
 //     u_{k,t}, item (t, part) summing a contiguous slice of the chunk, the
-//     slices then added in order; (beta_b, Z_b, N_b) go to part[b];
+//     slices then added in order; (beta_b, Z_b, N_b) go to part[b], or, when
+//     the chunk is the only one (`single`), to red[0], red[1] and the LDS
+//     array that the call returns;
 //  3. (update_merge, run by whoever finishes the last chunk) beta = min
 //     beta_b, scale_b = exp(-(beta_b - beta)/lambda), V+ = sum_b scale_b N_b /
 //     sum_b scale_b Z_b; then V (shifted when asked), the first command and,
@@ -605,10 +607,10 @@ __device__ __forceinline__ float seg_min_256(const float* v, float* red) {
 // two forms in debug mode also checks that the drawn controls are the stored
 // ones.
 template <int kB, bool kRegen = false>
-__device__ __forceinline__ void update_chunk(const StepConst& c, int b, int parts, const float* __restrict__ S,
-                                             const float* __restrict__ cvar, const float2* __restrict__ u,
-                                             float* __restrict__ S_tilde, float* __restrict__ part, float* ush,
-                                             float* red, const float* __restrict__ V = nullptr) {
+__device__ __forceinline__ float* update_chunk(const StepConst& c, int b, int parts, const float* S,
+                                               const float* cvar, const float2* __restrict__ u, float* S_tilde,
+                                               float* part, float* ush, float* red, bool single,
+                                               const float* __restrict__ V = nullptr) {
     const int T = c.T, K = c.K;
     const int tid = threadIdx.x, nt = blockDim.x;
     float* wsh = ush;
@@ -646,8 +648,8 @@ __device__ __forceinline__ void update_chunk(const StepConst& c, int b, int part
 #pragma unroll
         for (int sg = 0; sg < 4; ++sg) {
             const int i = min(64 * sg + tid, n - 1);
-            cvl[sg] = cvar[k0 + i];
-            sl[sg] = S[k0 + i];
+            cvl[sg] = agent_load(&cvar[k0 + i]);
+            sl[sg] = agent_load(&S[k0 + i]);
         }
         float w[4];
 #pragma unroll
@@ -658,7 +660,7 @@ __device__ __forceinline__ void update_chunk(const StepConst& c, int b, int part
                 const float cv = cvl[sg];
                 const float jc = (cv > c.C_u) ? c.A * cv : 0.0f;  // Eq. 14-15
                 st = sl[sg] + jc;                                  // Eq. 16
-                S_tilde[k0 + i] = st;
+                agent_store(&S_tilde[k0 + i], st);
             }
             w[sg] = st;
         }
@@ -742,17 +744,30 @@ __device__ __forceinline__ void update_chunk(const StepConst& c, int b, int part
         psh[(size_t)pr * 2 * T + 2 * t + 1] = ay;
     }
     __syncthreads();
+    if (single) {  // the only chunk: its sums stay in LDS (in vsh, read for the last time above) for the merge
+        for (int j = tid; j < 2 * T; j += nt) {
+            float acc = 0.0f;
+            for (int pr = 0; pr < parts; ++pr) acc += psh[(size_t)pr * 2 * T + j];
+            vsh[j] = acc;
+        }
+        if (tid == 0) {
+            red[0] = beta_b;
+            red[1] = Z_b;
+        }
+        __syncthreads();
+        return vsh;
+    }
     float* pb = part + (size_t)b * stride;
     for (int j = tid; j < 2 * T; j += nt) {
         float acc = 0.0f;
         for (int pr = 0; pr < parts; ++pr) acc += psh[(size_t)pr * 2 * T + j];
-        pb[2 + j] = acc;
+        agent_store(&pb[2 + j], acc);
     }
     if (tid == 0) {
-        pb[0] = beta_b;
-        pb[1] = Z_b;
+        agent_store(&pb[0], beta_b);
+        agent_store(&pb[1], Z_b);
     }
-    __syncthreads();  // LDS free for the caller
+    return nullptr;
 }
 
 // The merge's last part, once vp (2T) holds V+ in LDS and beta, Z (and
@@ -760,9 +775,9 @@ __device__ __forceinline__ void update_chunk(const StepConst& c, int b, int part
 // completion word, w_hat in debug mode; in gradient mode J, every w_hat and
 // the samples of non-zero weight instead, V unchanged.
 __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, float Z, float invZ, const float* vp,
-                                             const float* __restrict__ S_tilde, float* __restrict__ V,
-                                             float* __restrict__ u0, float* __restrict__ u0_host,
-                                             float* __restrict__ w_hat, float* red, const GradOut* go) {
+                                             const float* S_tilde, float* __restrict__ V, float* __restrict__ u0,
+                                             float* __restrict__ u0_host, float* __restrict__ w_hat, float* red,
+                                             const GradOut* go) {
     const int T = c.T, K = c.K;
     const int tid = threadIdx.x, nt = blockDim.x;
     __syncthreads();
@@ -779,7 +794,7 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
         const int ka = min(K, tid * q), kb = min(K, ka + q);
         int cnt = 0;
         for (int k = ka; k < kb; ++k) {
-            const float wk = expf(-(S_tilde[k] - beta) / c.lambda) * invZ;
+            const float wk = expf(-(agent_load(&S_tilde[k]) - beta) / c.lambda) * invZ;
             w_hat[k] = wk;
             cnt += wk > 0.0f;
         }
@@ -805,29 +820,31 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
     for (int j = tid; j < 2 * T; j += nt) {
         int src = j;
         if (shift) src = min(j + 2, 2 * T - 2 + (j & 1));
-        V[j] = vp[src];
+        agent_store(&V[j], vp[src]);
     }
     if (tid < 2) u0[tid] = vp[tid];
-    // The completion word may release the next served step, whose workgroups
-    // read V: every wave's stores of V must precede thread 0's release, so
-    // the workgroup meets at a barrier first (with T > 32 the stores come
-    // from more than one wave).
-    if (u0_host) __syncthreads();
-    if (tid == 0 && u0_host) {  // mapped pinned host memory
-        u0_host[0] = vp[0];
-        u0_host[1] = vp[1];
-        if (c.u0_seq)  // completion word, ordered after the command at system scope
-            __hip_atomic_store(reinterpret_cast<unsigned*>(u0_host + 2), c.u0_seq, __ATOMIC_RELEASE,
+    if (u0_host) {
+        // mapped pinned host memory: the command first, then the completion
+        // word, each at system scope.  The word may release the next served
+        // step, whose workgroups read V: every wave waits for its stores of V
+        // (written through to the memory that the XCDs share; the next step's
+        // readers invalidate their caches when they see their request), and
+        // the workgroup meets at a barrier before the word is stored.
+        if (tid < 2) __hip_atomic_store(&u0_host[tid], vp[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        stores_done();
+        __syncthreads();
+        if (tid == 0 && c.u0_seq)
+            __hip_atomic_store(reinterpret_cast<unsigned*>(u0_host + 2), c.u0_seq, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (c.debug) {
-        for (int k = tid; k < K; k += nt) w_hat[k] = expf(-(S_tilde[k] - beta) / c.lambda) * invZ;
+        for (int k = tid; k < K; k += nt) w_hat[k] = expf(-(agent_load(&S_tilde[k]) - beta) / c.lambda) * invZ;
     }
 }
 
 template <int kB>
-__device__ __forceinline__ void update_merge(const StepConst& c, int G, const float* __restrict__ part,
-                                             const float* __restrict__ S_tilde, float* __restrict__ V,
+__device__ __forceinline__ void update_merge(const StepConst& c, int G, const float* part, const float* S_tilde,
+                                             float* __restrict__ V,
                                              float* __restrict__ u0, float* __restrict__ u0_host,
                                              float* __restrict__ w_hat, float* ush, float* red,
                                              const GradOut* go = nullptr) {
@@ -848,7 +865,7 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
     const bool has_pre = tid < 2 * T;
     if (has_pre) {
 #pragma unroll
-        for (int i = 0; i < kP; ++i) pre[i] = i < n_pre ? part[(size_t)i * stride + 2 + tid] : 0.0f;
+        for (int i = 0; i < kP; ++i) pre[i] = i < n_pre ? agent_load(&part[(size_t)i * stride + 2 + tid]) : 0.0f;
     }
     float beta, Z;
     if (G <= 64) {
@@ -858,8 +875,8 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
         // positive Z, so the bits are the same); one barrier publishes them
         if (tid < 64) {
             const bool in = tid < G;
-            const float be = in ? part[(size_t)tid * stride] : __builtin_inff();
-            const float z0 = in ? part[(size_t)tid * stride + 1] : 0.0f;
+            const float be = in ? agent_load(&part[(size_t)tid * stride]) : __builtin_inff();
+            const float z0 = in ? agent_load(&part[(size_t)tid * stride + 1]) : 0.0f;
             const float bmin = wave_min(be);
             const float sc = in ? expf(-(be - bmin) / c.lambda) : 0.0f;
             const float zs = wave_sum(__fmaf_rn(z0, sc, 0.0f));
@@ -878,9 +895,9 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
         for (int i = tid; i < 256; i += nt) {
             float m = __builtin_inff();
             for (int bb = i; bb < G; bb += 256) {
-                const float be = part[(size_t)bb * stride];
+                const float be = agent_load(&part[(size_t)bb * stride]);
                 scale[bb] = be;
-                zb[bb] = part[(size_t)bb * stride + 1];
+                zb[bb] = agent_load(&part[(size_t)bb * stride + 1]);
                 m = fminf(m, be);
             }
             vsh[i] = m;
@@ -910,7 +927,7 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
         for (; bb + kB <= G; bb += kB) {  // kB loads in flight, then the sums in order
             float pv[kB];
 #pragma unroll
-            for (int i = 0; i < kB; ++i) pv[i] = part[(size_t)(bb + i) * stride + 2 + j];
+            for (int i = 0; i < kB; ++i) pv[i] = agent_load(&part[(size_t)(bb + i) * stride + 2 + j]);
 #pragma unroll
             for (int i = 0; i < kB; ++i) acc = __fmaf_rn(pv[i], scale[bb + i], acc);
         }
@@ -919,7 +936,7 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
 #pragma unroll
             for (int i = 0; i < kB; ++i) {
                 const bool in = bb + i < G;
-                pv[i] = in ? part[(size_t)(bb + i) * stride + 2 + j] : 0.0f;
+                pv[i] = in ? agent_load(&part[(size_t)(bb + i) * stride + 2 + j]) : 0.0f;
                 sv[i] = in ? scale[bb + i] : 0.0f;
             }
 #pragma unroll
@@ -931,43 +948,36 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
 }
 
 // The merge when there is one chunk (K <= 256), run by the workgroup that
-// has just written its partial record: beta = beta_0, every scale is
-// exp(0) = 1 and Z = Z_0, so V+ = N_0 / Z_0 -- the bits of update_merge
-// with G = 1, without the counter, the reductions or a device-scope wait.
-__device__ __forceinline__ void update_merge_single(const StepConst& c, const float* part,
-                                                    const float* __restrict__ S_tilde, float* __restrict__ V,
-                                                    float* __restrict__ u0, float* __restrict__ u0_host,
-                                                    float* __restrict__ w_hat, float* ush, float* red,
-                                                    const GradOut* go = nullptr) {
-    const float beta = part[0];
-    const float Z = part[1];
+// has just formed it (nb: its sums, in LDS; beta and Z in red): beta =
+// beta_0, every scale is exp(0) = 1 and Z = Z_0, so V+ = N_0 / Z_0 -- the
+// bits of update_merge with G = 1, without the counter, the reductions or a
+// trip through memory.
+__device__ __forceinline__ void update_merge_single(const StepConst& c, float* nb, const float* S_tilde,
+                                                    float* __restrict__ V, float* __restrict__ u0,
+                                                    float* __restrict__ u0_host, float* __restrict__ w_hat,
+                                                    float* red, const GradOut* go = nullptr) {
+    const float beta = red[0];
+    const float Z = red[1];
     const float invZ = 1.0f / Z;
-    float* vp = ush + 256 + 2;  // the place update_merge gives it for G = 1
-    for (int j = threadIdx.x; j < 2 * c.T; j += blockDim.x) vp[j] = part[2 + j] * invZ;
-    merge_finish(c, beta, Z, invZ, vp, S_tilde, V, u0, u0_host, w_hat, red, go);
+    for (int j = threadIdx.x; j < 2 * c.T; j += blockDim.x) nb[j] *= invZ;
+    if (c.debug || go) stores_done();  // S~, read back below by other waves of this workgroup
+    merge_finish(c, beta, Z, invZ, nb, S_tilde, V, u0, u0_host, w_hat, red, go);
 }
 
-// Thread 0 adds one to a device-scope counter with acquire-release order
-// (after the barrier that orders the workgroup's earlier stores before it);
-// returns to every thread whether this made it reach `target`, in which case
-// the counter is reset to zero and every thread has acquired what the other
-// increments published.
+// Counts the workgroup in at a device-scope counter, after every wave's
+// stores (see agent_store); returns to every thread whether this made it
+// reach `target`, in which case the counter is reset to zero and whatever the
+// other workgroups stored before counting in may be loaded by agent_load.
 __device__ __forceinline__ bool arrive_last(unsigned* counter, unsigned target, int* flag_sh) {
+    stores_done();
     __syncthreads();
     if (threadIdx.x == 0) {
-        // a release increment; only the last arrival acquires (the others
-        // leave their caches as they are)
-        const unsigned done = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned done = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *flag_sh = (done == target - 1u);
-        if (*flag_sh) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (*flag_sh) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    const bool last = *flag_sh != 0;
-    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return last;
+    return *flag_sh != 0;
 }
 
 // Loads in flight per thread in the update run inside the rollout launch,
@@ -1109,17 +1119,15 @@ __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs&
         lo = (item - c.n_nom_wg) * c.spb;
         hi = min(c.K, lo + c.spb);
     }
-    __syncthreads();  // the workgroup's stores precede thread 0's release; LDS free
+    stores_done();
+    __syncthreads();  // every wave's stores of S and CVaR are done; LDS free
     if (threadIdx.x == 0) {
         int nf = 0;
         for (int b = lo >> 8; b <= (hi - 1) >> 8; ++b) {
             const unsigned target = chunk_contributors(c, b);
-            // a release increment; only the workgroup that completes the
-            // chunk acquires, so the others keep their caches
             const unsigned done =
-                __hip_atomic_fetch_add(&f.chunk_ctr[b], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(&f.chunk_ctr[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (done == target - 1u) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 __hip_atomic_store(&f.chunk_ctr[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 fin_sh[nf++] = b;
             }
@@ -1129,11 +1137,11 @@ __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs&
     __syncthreads();
     const int nf = fin_sh[7];
     if (nf == 0) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     for (int i = 0; i < nf; ++i) {
-        update_chunk<kFuseBatch, true>(c, fin_sh[i], f.parts, S, cvar, u, f.S_tilde, f.part, ush, red, V);
-        if (f.G == 1)  // its own record, visible to the workgroup after update_chunk's barrier
-            update_merge_single(c, f.part, f.S_tilde, V, f.u0, c.u0_seq ? f.u0_host : nullptr, f.w_hat, ush, red);
+        float* nb = update_chunk<kFuseBatch, true>(c, fin_sh[i], f.parts, S, cvar, u, f.S_tilde, f.part, ush, red,
+                                                   f.G == 1, V);
+        if (f.G == 1)
+            update_merge_single(c, nb, f.S_tilde, V, f.u0, c.u0_seq ? f.u0_host : nullptr, f.w_hat, red);
         else if (arrive_last(f.counter, (unsigned)f.G, flag_sh))
             update_merge<kFuseBatch>(c, f.G, f.part, f.S_tilde, V, f.u0, c.u0_seq ? f.u0_host : nullptr, f.w_hat,
                                      ush, red);
@@ -1143,20 +1151,18 @@ __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs&
 // One chunk of the update, and the merge when it is the last chunk to finish
 // (a separate launch of G workgroups, one chunk each).  No workgroup waits
 // for another, and every sum runs in a fixed order.
-__device__ __forceinline__ void update_body(const StepConst& c, int b, int G, int parts, const float* __restrict__ S,
-                                            const float* __restrict__ cvar, const float2* __restrict__ u,
-                                            float* __restrict__ S_tilde, float* part, unsigned* counter,
+__device__ __forceinline__ void update_body(const StepConst& c, int b, int G, int parts, const float* S,
+                                            const float* cvar, const float2* __restrict__ u, float* S_tilde,
+                                            float* part, unsigned* counter,
                                             float* __restrict__ V, float* __restrict__ u0,
                                             float* __restrict__ u0_host, float* __restrict__ w_hat, float* ush,
                                             float* red, int* flag_sh, const GradOut* go = nullptr) {
     // the stored controls when the rollouts stored them (debug and
     // gradient modes), else the same controls drawn again
-    if (c.store_u)
-        update_chunk<16>(c, b, parts, S, cvar, u, S_tilde, part, ush, red);
-    else
-        update_chunk<16, true>(c, b, parts, S, cvar, u, S_tilde, part, ush, red, V);
+    float* nb = c.store_u ? update_chunk<16>(c, b, parts, S, cvar, u, S_tilde, part, ush, red, G == 1)
+                          : update_chunk<16, true>(c, b, parts, S, cvar, u, S_tilde, part, ush, red, G == 1, V);
     if (G == 1) {
-        update_merge_single(c, part, S_tilde, V, u0, u0_host, w_hat, ush, red, go);
+        update_merge_single(c, nb, S_tilde, V, u0, u0_host, w_hat, red, go);
         return;
     }
     if (!arrive_last(counter, (unsigned)G, flag_sh)) return;
