@@ -188,7 +188,7 @@ Layout layout(const mppi_params* p) {
         l.states = o;   o += align_up(16 * (size_t)p->T * l.stride);
         l.rows = o;     o += align_up(4 * 2 * (size_t)p->T * l.stride);
         l.rpart = o;    o += align_up(4 * 2 * (size_t)p->T * l.n_lane_blocks);
-        l.gcounter = o; o += align_up(4);
+        l.gcounter = o; o += align_up(4 * 2 * (size_t)p->T);
     }
     l.total = o;
     return l;
@@ -482,7 +482,8 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + l.counter, 0, 4, s);
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + l.work, 0, 16 * (size_t)ramppi::kWorkSlots, s);
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + l.chunk, 0, 4 * (size_t)h->g.G, s);
-    if (e == hipSuccess && (p->flags & MPPI_F_GRAD)) e = hipMemsetAsync(h->ws + l.gcounter, 0, 4, s);
+    if (e == hipSuccess && (p->flags & MPPI_F_GRAD))
+        e = hipMemsetAsync(h->ws + l.gcounter, 0, 4 * 2 * (size_t)p->T, s);
     // one launch per step when every workgroup of the step can be resident at
     // once (the update then runs in the workgroups that finish each chunk)
     h->fuse = false;
@@ -858,6 +859,7 @@ mppi_status mppi_grad(mppi_handle* h, const float x0[4], const float* V_dev, uin
     a.rows = reinterpret_cast<float*>(h->ws + l.rows);
     a.rpart = reinterpret_cast<float*>(h->ws + l.rpart);
     a.counter = reinterpret_cast<unsigned*>(h->ws + l.gcounter);
+    a.n_blocks = l.n_lane_blocks;
     a.grad_out = grad_dev;
     a.R = l.R;
     a.stride = l.stride;

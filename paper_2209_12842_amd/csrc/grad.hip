@@ -4,15 +4,18 @@
 //   dS~_k = dS_k + A 1[CVaR_k > C_u] (1/n_tail) sum_tail (B dL_m + (1 - B) dLbar).
 // After the forward rollout (which records each draw's rank in its sample)
 // and the update in gradient mode (which writes J, w_hat and the list of
-// samples of non-zero weight), k_grad_rollouts gives one lane to every
-// (weighted sample, rollout that reaches its gradient): the nominal rollout
-// and the tail draws (every draw when B != 1).  The lane recomputes its
-// rollout from the same Philox counters, keeping the states of this rollout
-// only, runs the adjoint (backward) recursion of the Euler steps, and writes
-// its coefficient times dCost/dV as one row.  k_grad_reduce adds the rows in
-// a fixed order.  Indicators (collisions, the C_u test, tail membership) have
+// samples of non-zero weight), k_grad_rollouts takes every (weighted sample,
+// rollout that reaches its gradient): the nominal rollout and the tail draws
+// (every draw when B != 1).  Each is recomputed from the same Philox
+// counters, keeping its states, the adjoint (backward) recursion of the Euler
+// steps runs over them, and the coefficient times dCost/dV is written as one
+// row: by one lane per rollout, or where the rollouts are few, with their
+// steps shared out over lanes (grad_rows_by_time).  k_grad_reduce adds the
+// rows in a fixed order.  Indicators (collisions, the C_u test, tail membership) have
 // zero gradient almost everywhere; du/dv is 1 strictly inside the box for
 // warm samples and 0 otherwise.
+#include <algorithm>
+
 #include "launch.h"
 #include "step_device.h"
 
@@ -33,34 +36,269 @@ __device__ __forceinline__ float2 control_jacobian(const StepConst& c, float2 v,
                        (warm && d > c.u_lo1 && d < c.u_hi1) ? 1.0f : 0.0f);
 }
 
+// What a row (weighted sample, rollout) is: its sample, its draw (-1: the
+// nominal rollout) and its coefficient.
+struct GradRow {
+    int k, m;
+    float coef;
+};
+
+__device__ __forceinline__ GradRow grad_row(const StepConst& c, const GradArgs& a, int l) {
+    const int slot = l / a.R;
+    const int j = l - slot * a.R;
+    GradRow r;
+    r.k = a.act_list[slot];
+    const float wk = a.w_hat[r.k];
+    r.m = -1;
+    if (j == 0) {
+        r.coef = wk;
+    } else {
+        const bool risk = (a.cvar[r.k] > c.C_u) && (c.A != 0.0f);
+        if (!c.scale_risk) {
+            r.m = a.tail_idx[(size_t)r.k * c.n_tail + (j - 1)];
+            r.coef = risk ? wk * c.A / (float)c.n_tail : 0.0f;
+        } else {
+            r.m = j - 1;
+            const bool in_tail = a.ranks[(size_t)r.k * c.M + r.m] < c.n_tail;
+            r.coef =
+                risk ? wk * c.A * ((in_tail ? c.B / (float)c.n_tail : 0.0f) + (1.0f - c.B) / (float)c.M) : 0.0f;
+        }
+    }
+    return r;
+}
+
+// ---- few rows: the steps of a rollout side by side ----
+//
+// A rollout is a chain of T steps forward and T back, but little of a step
+// belongs to the chain: the draws, controls and steering tangents do not
+// depend on the state at all; heading and speed form a chain of their own (a
+// few fused multiply-adds per step); sines and cosines of the headings are
+// then independent; the positions are a second chain; cost gradients and the
+// coefficients of the adjoint are independent again; the adjoint is a third
+// chain; the control Jacobians and outputs are independent.  A workgroup
+// takes kTimeRows rows and kTimeTile steps at a time: what is independent
+// runs over (row, step) pairs in all lanes, the chains in one lane per row,
+// values in LDS.  Every value is formed by the operations of the one-lane
+// form in the same order.  With one lane per row and a few hundred rows the
+// launch waits on the latency of 2 T whole steps (T = 50: 33.4 us for 8 rows
+// as for 10 thousand; here 12.2 us for 8 rows, about 13 for 4 thousand).
+constexpr int kTimeRows = 8;
+constexpr int kTimeTile = 64;
+constexpr int kTimeStride = kTimeTile + 1;  // LDS row stride: rows on different banks
+// LDS fields per (row, step); a field's later contents follow its first
+// ones: forward (kFpsi, kFv: the state's heading and speed; P_i, Q_i: the
+// disturbance of component i is P_i Q_i), then the coefficients of the
+// adjoint, then its heading and speed components.
+enum {
+    kFda, kFkap, kFp2, kFq2, kFp3, kFq3, kFp0, kFq0, kFp1, kFq1, kFpsi, kFv, kTimeFields,
+    kFsn = kFda, kFcs = kFkap, kFx = kFp2, kFy = kFp3,
+    kFc4 = kFda, kFc3 = kFkap, kFgx = kFp2, kFgy = kFp3, kFc5 = kFp0, kFgw = kFq0, kFgd = kFp1, kFc1 = kFpsi,
+    kFc2 = kFv, kFlw = kFq1, kFlz = kFq2
+};
+// Largest grid of the row-by-time form, eight workgroups per compute unit;
+// more rows than that fill the device with one lane each (T = 50, whole
+// gradient: 8.8 thousand rows 74 us here, 85 us by lanes; 17 thousand 107 us
+// either way; 33 thousand 131 us here, 112 us by lanes).
+constexpr int kTimeGrid = 2048;
+
+template <int kNoise>
+__device__ __forceinline__ void grad_rows_by_time(const StepConst& c, const GradArgs& a, int n_rows) {
+    __shared__ float f[kTimeFields][kTimeRows * kTimeStride];
+    __shared__ int rk[kTimeRows], rm[kTimeRows];
+    __shared__ float rcoef[kTimeRows], endx[2 * kTimeRows];
+    const int tid = threadIdx.x;
+    const int l0 = blockIdx.x * kTimeRows;
+    if (l0 >= n_rows) return;  // uniform
+    if (tid < kTimeRows) {
+        const GradRow r = grad_row(c, a, min(l0 + tid, n_rows - 1));  // rows past the last repeat it, unwritten
+        rk[tid] = r.k;
+        rm[tid] = r.m;
+        rcoef[tid] = r.coef;
+    }
+    __syncthreads();
+    const int T = c.T, K = c.K;
+    const int n_tiles = (T + kTimeTile - 1) / kTimeTile;
+    const float dt = c.dt;
+    // the chains' lanes: row crow; axis 0 and 1 for the positions
+    const int crow = tid & (kTimeRows - 1), axis = tid >> 3;
+    const int cb = crow * kTimeStride;
+    float psi = c.psi0, v = c.v0, pos = 0.0f;
+    for (int tile = 0; tile < n_tiles; ++tile) {
+        const int t0 = tile * kTimeTile, nt = min(kTimeTile, T - t0);
+        // controls and disturbances (a wave per row)
+        for (int i = tid; i < kTimeRows * kTimeTile; i += 256) {
+            const int row = i >> 6, tt = i & 63, t = t0 + tt;
+            if (tt >= nt) continue;
+            const int q = row * kTimeStride + tt;
+            const int k = rk[row], m = rm[row];
+            const float2 uu = a.u[(size_t)t * K + k];
+            f[kFda][q] = dt * uu.x;
+            f[kFkap][q] = tan_steer(uu.y) * c.inv_wheelbase;
+            float4 P = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Q = P;
+            if (m >= 0 && t + 1 < T) {
+                const uint4 r = philox4x32_10((uint32_t)t, (uint32_t)m, (uint32_t)k, c.step_idx, c.key0, c.key1);
+                const float4 d = disturbance_draw<kNoise>(c, r, 0x7Fu);
+                if (kNoise == 0) {
+                    P = make_float4(c.sw0 * d.x, c.sw1 * d.x, c.sw2 * d.y, c.sw3 * d.y);
+                    Q = make_float4(__builtin_amdgcn_cosf(d.z), __builtin_amdgcn_sinf(d.z), __builtin_amdgcn_cosf(d.w),
+                                    __builtin_amdgcn_sinf(d.w));
+                } else if (kNoise == 1) {
+                    P = make_float4(c.sw0, c.sw1, c.sw2, c.sw3);
+                    Q = d;
+                } else {
+                    P = make_float4(d.x, d.x, 0.0f, 0.0f);
+                    Q = make_float4(__builtin_amdgcn_cosf(d.y), __builtin_amdgcn_sinf(d.y), 0.0f, 0.0f);
+                }
+            }
+            f[kFp0][q] = P.x;
+            f[kFq0][q] = Q.x;
+            f[kFp1][q] = P.y;
+            f[kFq1][q] = Q.y;
+            f[kFp2][q] = P.z;
+            f[kFq2][q] = Q.z;
+            f[kFp3][q] = P.w;
+            f[kFq3][q] = Q.w;
+        }
+        __syncthreads();
+        if (tid < kTimeRows) {  // heading and speed
+#pragma unroll 4
+            for (int tt = 0; tt < nt; ++tt) {
+                const int q = cb + tt;
+                f[kFpsi][q] = psi;
+                f[kFv][q] = v;
+                psi = __fmaf_rn(dt * v, f[kFkap][q], psi);
+                {
+#pragma clang fp contract(off)
+                    v = v + f[kFda][q];
+                }
+                psi = __fmaf_rn(f[kFp2][q], f[kFq2][q], psi);
+                v = __fmaf_rn(f[kFp3][q], f[kFq3][q], v);
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < kTimeRows * kTimeTile; i += 256) {
+            const int q = (i >> 6) * kTimeStride + (i & 63);
+            if ((i & 63) >= nt) continue;
+            const float r = f[kFpsi][q] * 0.159154943091895335769f;  // as in bicycle_step
+            f[kFsn][q] = __builtin_amdgcn_sinf(r);
+            f[kFcs][q] = __builtin_amdgcn_cosf(r);
+        }
+        __syncthreads();
+        if (tid < 2 * kTimeRows) {  // positions: lanes 0..7 x, 8..15 y
+            const float* dir = f[axis ? kFsn : kFcs];
+            const float* P = f[axis ? kFp1 : kFp0];
+            const float* Q = f[axis ? kFq1 : kFq0];
+            float* out = f[axis ? kFy : kFx];
+#pragma unroll 4
+            for (int tt = 0; tt < nt; ++tt) {
+                const int q = cb + tt;
+                const float d = dir[q], pp = P[q], qq = Q[q], dv = dt * f[kFv][q];
+                out[q] = pos;
+                pos = __fmaf_rn(dv, d, pos);
+                pos = __fmaf_rn(pp, qq, pos);
+            }
+            if (tile + 1 == n_tiles) endx[axis * kTimeRows + crow] = pos;
+        }
+        __syncthreads();
+        if (n_tiles > 1) {  // the states of every tile, for the way back
+            for (int i = tid; i < kTimeRows * nt; i += 256) {
+                const int row = i & (kTimeRows - 1), tt = i >> 3, q = row * kTimeStride + tt;
+                if (l0 + row < n_rows)
+                    a.states[(size_t)(t0 + tt) * a.stride + l0 + row] =
+                        make_float4(f[kFx][q], f[kFy][q], f[kFpsi][q], f[kFv][q]);
+            }
+            __syncthreads();
+        }
+    }
+    // backward: lam = dCost/dx_t, seeded with the terminal cost (nominal only)
+    float4 lam = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (tid < kTimeRows && rm[tid] < 0 && c.use_term)
+        lam = terminal_cost_grad(c, State{endx[tid], endx[kTimeRows + tid], 0.0f, 0.0f});
+    for (int tile = n_tiles - 1; tile >= 0; --tile) {
+        const int t0 = tile * kTimeTile, nt = min(kTimeTile, T - t0);
+        for (int i = tid; i < kTimeRows * kTimeTile; i += 256) {
+            const int row = i >> 6, tt = i & 63, t = t0 + tt;
+            if (tt >= nt) continue;
+            const int q = row * kTimeStride + tt;
+            State x;
+            float sn, cs;
+            if (n_tiles > 1) {
+                const float4 xv = a.states[(size_t)t * a.stride + min(l0 + row, n_rows - 1)];
+                x = State{xv.x, xv.y, xv.z, xv.w};
+                const float r = x.psi * 0.159154943091895335769f;
+                sn = __builtin_amdgcn_sinf(r);
+                cs = __builtin_amdgcn_cosf(r);
+            } else {
+                x = State{f[kFx][q], f[kFy][q], f[kFpsi][q], f[kFv][q]};
+                sn = f[kFsn][q];
+                cs = f[kFcs][q];
+            }
+            const float tnd = tan_steer(a.u[(size_t)t * K + rk[row]].y);
+            const float dv = dt * x.v;
+            const float4 gq = smooth_cost_grad(c, x);
+            f[kFc1][q] = -dv * sn;
+            f[kFc2][q] = dv * cs;
+            f[kFc3][q] = dt * cs;
+            f[kFc4][q] = dt * sn;
+            f[kFc5][q] = dt * tnd * c.inv_wheelbase;
+            f[kFgx][q] = gq.x;
+            f[kFgy][q] = gq.y;
+            f[kFgw][q] = gq.w;
+            f[kFgd][q] = dv * __fmaf_rn(tnd, tnd, 1.0f) * c.inv_wheelbase;
+        }
+        __syncthreads();
+        if (tid < kTimeRows) {  // the adjoint
+#pragma unroll 4
+            for (int tt = nt - 1; tt >= 0; --tt) {
+                const int q = cb + tt;
+                f[kFlw][q] = lam.w;
+                f[kFlz][q] = lam.z;
+                float4 nl;
+                nl.x = f[kFgx][q] + lam.x;
+                nl.y = f[kFgy][q] + lam.y;
+                nl.z = __fmaf_rn(f[kFc1][q], lam.x, __fmaf_rn(f[kFc2][q], lam.y, lam.z));
+                nl.w = f[kFgw][q] + __fmaf_rn(f[kFc3][q], lam.x,
+                                              __fmaf_rn(f[kFc4][q], lam.y, __fmaf_rn(f[kFc5][q], lam.z, lam.w)));
+                lam = nl;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < kTimeRows * nt; i += 256) {
+            const int row = i & (kTimeRows - 1), tt = i >> 3, t = t0 + tt, q = row * kTimeStride + tt;
+            if (l0 + row >= n_rows) continue;
+            const int k = rk[row];
+            const float coef = rcoef[row];
+            const float2 vt = make_float2(a.V[2 * t], a.V[2 * t + 1]);
+            const float2 dudv = control_jacobian(c, vt, k, t);
+            float g0 = dt * f[kFlw][q] * dudv.x, g1 = f[kFgd][q] * f[kFlz][q] * dudv.y;
+            if (rm[row] < 0 && c.use_ctrl) {  // d/dv of gamma v^T Sigma^-1 u(v), nominal rollout only
+                const float2 uu = a.u[(size_t)t * K + k];
+                g0 = __fmaf_rn(c.gamma * c.inv_var0, __fmaf_rn(vt.x, dudv.x, uu.x), g0);
+                g1 = __fmaf_rn(c.gamma * c.inv_var1, __fmaf_rn(vt.y, dudv.y, uu.y), g1);
+            }
+            a.rows[(size_t)(2 * t) * a.stride + l0 + row] = coef == 0.0f ? 0.0f : coef * g0;
+            a.rows[(size_t)(2 * t + 1) * a.stride + l0 + row] = coef == 0.0f ? 0.0f : coef * g1;
+        }
+        __syncthreads();  // the fields are refilled
+    }
+}
+
 // Steps by which the gradient rollouts load ahead of their use.
 constexpr int kGradAhead = 4;
 
 template <int kNoise>
 __global__ void __launch_bounds__(256) k_grad_rollouts(StepConst c, GradArgs a) {
-    const int l = blockIdx.x * 256 + threadIdx.x;
     const int n_rows = *a.n_act * a.R;
-    if (l >= n_rows) return;  // no barrier in this kernel
-    const int T = c.T, K = c.K, M = c.M;
-    const int slot = l / a.R;
-    const int j = l - slot * a.R;
-    const int k = a.act_list[slot];
-    const float wk = a.w_hat[k];
-    float coef;
-    int m = -1;
-    if (j == 0) {
-        coef = wk;
-    } else {
-        const bool risk = (a.cvar[k] > c.C_u) && (c.A != 0.0f);
-        if (!c.scale_risk) {
-            m = a.tail_idx[(size_t)k * c.n_tail + (j - 1)];
-            coef = risk ? wk * c.A / (float)c.n_tail : 0.0f;
-        } else {
-            m = j - 1;
-            const bool in_tail = a.ranks[(size_t)k * M + m] < c.n_tail;
-            coef = risk ? wk * c.A * ((in_tail ? c.B / (float)c.n_tail : 0.0f) + (1.0f - c.B) / (float)M) : 0.0f;
-        }
+    if (n_rows <= kTimeRows * kTimeGrid) {
+        grad_rows_by_time<kNoise>(c, a, n_rows);
+        return;
     }
+    const int l = blockIdx.x * 256 + threadIdx.x;
+    if (l >= n_rows) return;  // no barrier below
+    const int T = c.T, K = c.K;
+    const GradRow row = grad_row(c, a, l);
+    const int k = row.k, m = row.m;
+    const float coef = row.coef;
     if (coef == 0.0f) {
         for (int q = 0; q < 2 * T; ++q) a.rows[(size_t)q * a.stride + l] = 0.0f;
         return;
@@ -158,56 +396,70 @@ __global__ void __launch_bounds__(256) k_grad_rollouts(StepConst c, GradArgs a) 
     }
 }
 
-// Sum of the gradient rows: block b adds rows [256 b, 256 b + 256), wave w
-// taking outputs q = w, w + 4, ... (lane i adds rows i, i + 64, i + 128,
-// i + 192, then the wave adds its lanes).  Only the nb blocks that hold rows
-// work (the others would add zeros): with one, its sums are dJ/dV; else the
-// last of them to finish adds the block sums in block order, writes dJ/dV
-// and resets its counter.  Either way the bits are those of adding every
-// block's sum in order.
-__global__ void __launch_bounds__(256) k_grad_reduce(int T, int G3, GradArgs a) {
-    __shared__ int is_last;
+// Sum of the gradient rows: output q in workgroups (q, 0), (q, 1), ...  The
+// rows are added in blocks of 256 (lane i of a wave adds rows i, i + 64,
+// i + 128, i + 192 of a block, then the wave adds its lanes), each wave taking
+// every fourth block of its workgroup's, and one thread adds the block sums
+// in block order.  Up to kReduceBlocks blocks one workgroup does it all, its
+// block sums in LDS; more blocks are split over the workgroups of the output,
+// which hand their sums over in memory to the last of them.  (A workgroup per
+// block of rows, its waves going through the outputs one by one, waited on
+// memory once per output: 8.5 us for a few rows and 17 us for 17 thousand at
+// T = 50, now 4.6 and 5.)
+constexpr int kReduceAhead = 4;   // blocks whose loads a wave has in flight
+constexpr int kReduceBlocks = 64;  // block sums of one workgroup
+
+__global__ void __launch_bounds__(256) k_grad_reduce(GradArgs a) {
+    __shared__ float sums[kReduceBlocks];
+    __shared__ int flag_sh;
     const int n_rows = *a.n_act * a.R;
-    const int nb = max(1, min(G3, (n_rows + 255) / 256));
-    const int b = blockIdx.x, tid = threadIdx.x;
-    if (b >= nb) return;  // uniform per block
+    const int nb = max(1, (n_rows + 255) / 256);
+    const int q = blockIdx.x, tid = threadIdx.x;
     const int lane = tid & 63, wv = tid >> 6;
-    const int l0 = b * 256;
-    float* out = nb == 1 ? a.grad_out : a.rpart + (size_t)b * 2 * T;
-    for (int q = wv; q < 2 * T; q += 4) {
-        const float* rq = a.rows + (size_t)q * a.stride + l0;
-        float acc = 0.0f;
+    const float* rq = a.rows + (size_t)q * a.stride;
+    const bool alone = nb <= kReduceBlocks;
+    const int per = alone ? nb : (nb + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int b0 = (int)blockIdx.y * per, b1 = min(nb, b0 + per);
+    if (b0 >= b1) return;  // uniform
+    float* part = a.rpart + (size_t)q * a.n_blocks;
+    for (int b = b0 + wv; b < b1; b += 4 * kReduceAhead) {
+        float r[kReduceAhead][4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int l = lane + 64 * i;
-            if (l0 + l < n_rows) acc += rq[l];
+        for (int i = 0; i < kReduceAhead; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int l = (b + 4 * i) * 256 + lane + 64 * j;
+                r[i][j] = (b + 4 * i < b1 && l < n_rows) ? rq[l] : 0.0f;
+            }
+#pragma unroll
+        for (int i = 0; i < kReduceAhead; ++i) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc += r[i][j];
+            acc = wave_sum(acc);
+            if (lane == 0 && b + 4 * i < b1) {
+                if (alone)
+                    sums[b + 4 * i] = acc;
+                else
+                    agent_store(&part[b + 4 * i], acc);
+            }
         }
-        acc = wave_sum(acc);
-        if (lane == 0) out[q] = acc;
     }
-    if (nb == 1) return;
-    __syncthreads();
-    if (tid == 0) {
-        const unsigned done = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        is_last = (done == (unsigned)(nb - 1));
-        if (is_last) __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (alone) {
+        __syncthreads();
+    } else {
+        // the workgroups of this output that hold blocks
+        if (!arrive_last(&a.counter[q], (unsigned)((nb + per - 1) / per), &flag_sh)) return;
     }
-    __syncthreads();
-    if (!is_last) return;
-    __atomic_thread_fence(__ATOMIC_ACQUIRE);
-    for (int q = tid; q < 2 * T; q += 256) {
-        float acc = 0.0f;
-        int bb = 0;
-        for (; bb + 16 <= nb; bb += 16) {  // 16 loads in flight, then the sums in order
-            float pv[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) pv[i] = a.rpart[(size_t)(bb + i) * 2 * T + q];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc += pv[i];
-        }
-        for (; bb < nb; ++bb) acc += a.rpart[(size_t)bb * 2 * T + q];
-        a.grad_out[q] = acc;
+    // one wave adds the block sums in order, 64 of them at a time from its lanes
+    if (wv != 0) return;
+    float total = 0.0f;
+    for (int s0 = 0; s0 < nb; s0 += 64) {
+        const float x = s0 + lane < nb ? (alone ? sums[lane] : agent_load(&part[s0 + lane])) : 0.0f;
+        const int n = min(64, nb - s0);
+        for (int i = 0; i < n; ++i) total += lane_f32(x, i);
     }
+    if (lane == 0) a.grad_out[q] = nb == 1 ? sums[0] : total;
 }
 
 __global__ void __launch_bounds__(256) k_update_grad(StepConst c, int G, int parts, const float* __restrict__ S,
@@ -227,14 +479,16 @@ hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs&
     (void)launch_rollout(c, b, block, lds_rollout, n_dist_wg, stream, a.ranks_w, a.tail_w);
     hipLaunchKernelGGL(k_update_grad, dim3(G), dim3(256), lds_update, stream, c, G, update_parts(c.T), b.S, b.cvar,
                        b.u, b.S_tilde, b.part, b.counter, b.w_hat, go);
-    const dim3 grid(n_lane_blocks);
+    const int n_time = (int)std::min<int64_t>(kTimeGrid, ((int64_t)c.K * a.R + kTimeRows - 1) / kTimeRows);
+    const dim3 grid(std::max(n_lane_blocks, n_time));
     if (c.noise_kind == 1)
         hipLaunchKernelGGL(k_grad_rollouts<1>, grid, dim3(256), 0, stream, c, a);
     else if (c.noise_kind == 2)
         hipLaunchKernelGGL(k_grad_rollouts<2>, grid, dim3(256), 0, stream, c, a);
     else
         hipLaunchKernelGGL(k_grad_rollouts<0>, grid, dim3(256), 0, stream, c, a);
-    hipLaunchKernelGGL(k_grad_reduce, dim3(n_lane_blocks), dim3(256), 0, stream, c.T, n_lane_blocks, a);
+    const int split = std::min(16, (n_lane_blocks + kReduceBlocks - 1) / kReduceBlocks);
+    hipLaunchKernelGGL(k_grad_reduce, dim3(2 * c.T, split), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -85,9 +85,10 @@ struct GradArgs {
     int* tail_w;
     float4* states;     // T x stride recomputed states
     float* rows;        // 2T x stride gradient rows
-    float* rpart;       // blocks x 2T
-    unsigned* counter;
+    float* rpart;       // 2T x n_blocks sums of 256 rows each
+    unsigned* counter;  // 2T workgroup counters (zero between launches)
     float* grad_out;    // T x 2
+    int n_blocks;       // blocks of 256 rows at most
     int R;              // lanes per weighted sample: nominal + tail (or + all draws)
     int stride;         // lane capacity K R
 };
