@@ -328,7 +328,8 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params *p, const float *cons
  * any shift; the call then waits for the step).  The step is three kernels:
  * per-controller set-up, one rollout launch with a workgroup for every item
  * of a (controller, workgroup) list, and one update launch over every
- * controller's chunks; with the graph on (the default) they are replayed from
+ * controller's chunks (before it, where draw counts leave many lanes of the
+ * rollouts idle, a CVaR pass over rollouts laid out without gaps); with the graph on (the default) they are replayed from
  * a HIP graph captured on the first step.  Controller i's results equal those
  * of mppi_step with the same parameters and inputs.  Before writing the inputs
  * the call waits for the previous step of this batch. */

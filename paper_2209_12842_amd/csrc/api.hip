@@ -96,6 +96,7 @@ constexpr uint32_t kMaxServeIdleMs = 60000;
 // Launch geometry derived from the sizes.
 struct Geometry {
     int spb, block, n_nom_wg, nom_groups, G;
+    bool flat;  // disturbed workgroups take 256 consecutive (sample, draw) pairs
     size_t lds_rollout, lds_update;
 };
 
@@ -110,10 +111,43 @@ Geometry geometry(const mppi_params* p) {
     g.spb = p->M >= 256 ? 1 : 256 / p->M;
     g.block = (g.spb * p->M + 63) / 64 * 64;
     set_nominal(&g, p->K, 1);
+    g.flat = false;
     g.G = (p->K + kPartBlock - 1) / kPartBlock;
     g.lds_rollout = rollout_lds_bytes(g.spb, p);
     g.lds_update = ramppi::update_lds_bytes(p->T, g.G);
     return g;
+}
+
+// The flattened layout of a step's disturbed lanes: workgroups of 256
+// consecutive (sample, draw) pairs, whose risk costs go to memory for a
+// separate CVaR pass, instead of whole samples per workgroup.
+void set_flat(Geometry* g, const mppi_params* p) {
+    g->flat = true;
+    g->block = 256;
+    g->spb = (256 + p->M - 2) / p->M + 1;  // samples that 256 pairs can touch
+    g->lds_rollout = rollout_lds_bytes(g->spb, p);
+}
+
+// Microseconds of a full device that the lanes without a draw of the
+// per-sample layout cost: 3.4e5 disturbed state steps per microsecond
+// (K = 16384, T = 100, M = 128 in 0.61 ms).
+double idle_lane_us(const Geometry& g, const mppi_params* p) {
+    const double used = (double)g.spb * p->M / g.block;
+    return (double)p->K * p->M * p->T * (1.0 / used - 1.0) / 3.4e5;
+}
+
+// Whether a two-launch step takes the flattened layout: more than 256 draws
+// (a sample then needs five or more waves, and only three such workgroups
+// start on a compute unit at once), or draw counts that leave enough lanes
+// idle to pay for the CVaR pass and its launch, about 6 us (K = 4000, T = 60,
+// M = 100, 200 of 256 lanes: step 93 -> 83 us).  The gradient keeps the per-sample layout
+// (its tail ranks come from the rollout's own CVaR pass).
+bool flat_pays(const Geometry& g, const mppi_params* p) {
+    if (p->flags & MPPI_F_GRAD) return false;
+    if (p->M > 256) return true;
+    Geometry f = g;
+    set_flat(&f, p);
+    return idle_lane_us(g, p) > 8.0 && f.lds_rollout <= kMaxLdsBytes;
 }
 
 // Workgroups of the one-launch step.
@@ -269,7 +303,7 @@ void fill_static(ramppi::StepConst* cp, const mppi_params& p, const Geometry& g,
     c.flags = p.flags;
     c.debug = (p.flags & MPPI_F_DEBUG) != 0;
     c.store_u = c.debug;  // the update draws the controls it needs again
-    c.flat = 0;
+    c.flat = g.flat;
 }
 
 // Per-launch constants that depend on the measured state and the call index
@@ -299,7 +333,6 @@ struct mppi_handle {
     float* u0_pinned_dev;  // its device address
     uint32_t u0_seq;       // last completion value requested
     bool fuse;             // one launch per step (the whole grid is resident at once)
-    bool flat;             // two launches with the flattened disturbed layout (M > 256)
     bool serving;          // a persistent serving launch is resident (mppi_serve_start)
     uint32_t serve_seq;    // last request posted in the session
     hipStream_t serve_stream;
@@ -506,19 +539,7 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
         fa.parts = ramppi::update_parts(p->T);
         if (e == hipSuccess) e = hipMemcpyAsync(h->ws + l.fuse, &fa, sizeof fa, hipMemcpyHostToDevice, s);
     }
-    // Two-launch steps whose samples need more than four waves (M > 256):
-    // the disturbed workgroups of five or more waves start only three to a
-    // compute unit at once, so their lanes are laid out instead as 256
-    // consecutive (sample, draw) pairs per workgroup (at most two samples,
-    // four waves) and each sample's CVaR is formed by a separate pass from
-    // the stored risk costs.  The gradient keeps the per-sample layout (its
-    // tail ranks come from the rollout's own CVaR pass).
-    h->flat = !h->fuse && p->M > 256 && !(p->flags & MPPI_F_GRAD);
-    if (h->flat) {
-        h->g.spb = 2;
-        h->g.block = 256;
-        h->g.lds_rollout = rollout_lds_bytes(2, p);
-    }
+    if (!h->fuse && flat_pays(h->g, p)) set_flat(&h->g, p);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipHostFree(h->u0_pinned);
@@ -555,7 +576,6 @@ mppi_status mppi_step(mppi_handle* h, const float x0[4], float* V_dev, uint32_t 
     ramppi::StepConst c;
     fill_static(&c, p, g, h->n_tail, h->n_warm);
     fill_dynamic(&c, p, x0, step_idx);
-    c.flat = h->flat;
 
     ramppi::StepBuffers bufs = step_buffers(h, V_dev);
     bufs.u0_host = u0_host ? h->u0_pinned_dev : nullptr;
@@ -676,7 +696,8 @@ mppi_status mppi_step_noalloc(const mppi_params* p, const float* obstacles_dev, 
     st = scratch_address(dev, &ws);
     if (st != MPPI_OK) return st;
 
-    const Geometry g = geometry(p);
+    Geometry g = geometry(p);
+    if (flat_pays(g, p)) set_flat(&g, p);
     int n_tail = 0, n_warm = 0;
     derived_counts(p, &n_tail, &n_warm);
     ramppi::StepConst c;
@@ -997,24 +1018,54 @@ namespace {
 constexpr int kBatchBlock = 256;
 constexpr int kMaxBatch = 65535;
 
-// Rollout geometry of a controller inside a batch: workgroups of 256 lanes.
-Geometry batch_geometry(const mppi_params* p) {
+// Rollout geometry of a controller inside a batch: workgroups of 256 lanes,
+// in the flattened layout where that saves lanes and the batch has a CVaR
+// pass (`flat`; tails that the pass's waves can take).
+Geometry batch_geometry(const mppi_params* p, bool flat) {
     Geometry g = geometry(p);
     g.spb = p->M >= kBatchBlock ? 1 : kBatchBlock / p->M;
     g.block = kBatchBlock;
     g.lds_rollout = rollout_lds_bytes(g.spb, p);
+    int n_tail, n_warm;
+    derived_counts(p, &n_tail, &n_warm);
+    if (flat && g.spb * p->M < 249 && n_tail <= ramppi::kWaveTail) {
+        Geometry f = g;
+        set_flat(&f, p);
+        if (f.lds_rollout <= kMaxLdsBytes) g = f;
+    }
     return g;
 }
 
-int n_dist_wg(const mppi_params* p, const Geometry& g) { return (p->K + g.spb - 1) / g.spb; }
+// Whether a batch has a CVaR pass for flattened controllers: where the idle
+// lanes of its controllers cost more than the pass and its launch (48
+// controllers up to K = 8192, T = 100, M = 128, 13 % of the lanes: step 2.48
+// -> 2.18 ms).
+bool batch_flat(int32_t n, const mppi_params* p) {
+    double us = 0.0;
+    for (int i = 0; i < n; ++i) us += idle_lane_us(batch_geometry(&p[i], false), &p[i]);
+    return us > 20.0;
+}
+
+int n_dist_wg(const mppi_params* p, const Geometry& g) {
+    if (g.flat) return (int)(((int64_t)p->K * p->M + g.block - 1) / g.block);
+    return (p->K + g.spb - 1) / g.spb;
+}
+
+// Workgroups of a controller's CVaR pass.
+int n_cvar_wg(const mppi_params* p, const Geometry& g) {
+    if (!g.flat) return 0;
+    const int per = ramppi::cvar_samples_per_wg(p->M);
+    return (p->K + per - 1) / per;
+}
 
 struct BatchLayout {
-    size_t ctls, items, uitems, vbackup, work;
+    size_t ctls, items, citems, uitems, vbackup, work;
     std::vector<size_t> ctl_base;
     size_t total;
-    int n_items, n_uitems;
+    bool flat;  // some controllers may take the flattened layout
+    int n_items, n_citems, n_uitems;
     int noise_kind;  // the disturbance form of every controller, or -1 when they differ
-    size_t lds_rollout, lds_update;
+    size_t lds_rollout, lds_cvar, lds_update;
 };
 
 mppi_status batch_check(int32_t n, const mppi_params* p) {
@@ -1028,7 +1079,7 @@ mppi_status batch_check(int32_t n, const mppi_params* p) {
         }
         if (p[i].M > kBatchBlock)
             return fail(MPPI_EUNSUPPORTED, "controller %d: M = %d exceeds %d in a batch", i, p[i].M, kBatchBlock);
-        const Geometry g = batch_geometry(&p[i]);
+        const Geometry g = batch_geometry(&p[i], false);
         if (g.lds_rollout > kMaxLdsBytes)
             return fail(MPPI_EUNSUPPORTED, "controller %d: rollout LDS need %zu B exceeds %zu B", i, g.lds_rollout,
                         kMaxLdsBytes);
@@ -1039,15 +1090,20 @@ mppi_status batch_check(int32_t n, const mppi_params* p) {
 BatchLayout batch_layout(int32_t n, const mppi_params* p) {
     BatchLayout bl;
     bl.n_items = 0;
+    bl.n_citems = 0;
     bl.n_uitems = 0;
+    bl.flat = batch_flat(n, p);
+    bl.lds_cvar = 0;
     bl.lds_rollout = 0;
     bl.lds_update = 0;
     bl.noise_kind = (int)p[0].noise_kind;
     size_t vback = 0;
     for (int i = 0; i < n; ++i) {
         if ((int)p[i].noise_kind != bl.noise_kind) bl.noise_kind = -1;
-        const Geometry g = batch_geometry(&p[i]);
+        const Geometry g = batch_geometry(&p[i], bl.flat);
         bl.n_items += g.n_nom_wg + n_dist_wg(&p[i], g);
+        bl.n_citems += n_cvar_wg(&p[i], g);
+        if (g.flat) bl.lds_cvar = std::max(bl.lds_cvar, ramppi::cvar_lds_bytes(p[i].M, p[i].B != 1.0f));
         bl.n_uitems += g.G;
         bl.lds_rollout = std::max(bl.lds_rollout, g.lds_rollout);
         bl.lds_update = std::max(bl.lds_update, g.lds_update);
@@ -1056,6 +1112,7 @@ BatchLayout batch_layout(int32_t n, const mppi_params* p) {
     size_t o = 0;
     bl.ctls = o;    o += align_up(sizeof(ramppi::BatchCtl) * (size_t)n);
     bl.items = o;   o += align_up(8 * (size_t)bl.n_items);
+    bl.citems = o;  o += align_up(8 * (size_t)std::max(bl.n_citems, 1));
     bl.uitems = o;  o += align_up(8 * (size_t)bl.n_uitems);
     bl.work = o;    o += align_up(16 * (size_t)ramppi::kWorkSlots);
     bl.vbackup = o; o += vback;
@@ -1099,10 +1156,13 @@ ramppi::BatchLaunch batch_launch_args(const mppi_batch* b) {
     L.ctls = reinterpret_cast<ramppi::BatchCtl*>(b->ws + b->bl.ctls);
     L.inputs = b->in_dev;
     L.items = reinterpret_cast<const int2*>(b->ws + b->bl.items);
+    L.citems = reinterpret_cast<const int2*>(b->ws + b->bl.citems);
     L.uitems = reinterpret_cast<const int2*>(b->ws + b->bl.uitems);
     L.work = nullptr;
     L.n_ctl = b->n;
     L.n_items = b->bl.n_items;
+    L.n_citems = b->bl.n_citems;
+    L.lds_cvar = b->bl.lds_cvar;
     L.n_uitems = b->bl.n_uitems;
     L.noise_kind = b->bl.noise_kind;
     L.lds_rollout = b->bl.lds_rollout;
@@ -1228,9 +1288,9 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
     b->ctl.resize(n);
     std::vector<std::pair<double, int2>> cost_items;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    std::vector<int2> uitems;
+    std::vector<int2> uitems, citems;
     for (int i = 0; i < n; ++i) {
-        const Geometry g = batch_geometry(&p[i]);
+        const Geometry g = batch_geometry(&p[i], bl.flat);
         const Layout l = layout(&p[i]);
         int n_tail, n_warm;
         derived_counts(&p[i], &n_tail, &n_warm);
@@ -1261,6 +1321,7 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
             b->items[0].push_back(make_int2(i, w));
             cost_items.push_back({cost, make_int2(i, w)});
         }
+        for (int w = 0; w < n_cvar_wg(&p[i], g); ++w) citems.push_back(make_int2(i, w));
         for (int ch = 0; ch < g.G; ++ch) uitems.push_back(make_int2(i, ch));
         std::vector<float> staged(4 * (size_t)(p[i].n_obs > 0 ? p[i].n_obs : 1), 0.0f);
         const std::vector<int> order = obstacle_order(obstacles_host[i], p[i].n_obs);
@@ -1280,6 +1341,8 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
     if (e == hipSuccess) e = upload_items(b, b->order, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->ws + bl.uitems, uitems.data(), 8 * uitems.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && !citems.empty())
+        e = hipMemcpyAsync(b->ws + bl.citems, citems.data(), 8 * citems.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemsetAsync(b->ws + bl.work, 0, 16 * (size_t)ramppi::kWorkSlots, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {

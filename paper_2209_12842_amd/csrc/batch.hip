@@ -1,5 +1,5 @@
 // Batched serving: one step of many independent controllers (uneven K, T, M
-// and obstacle counts) in three launches that a HIP graph can hold:
+// and obstacle counts) in three or four launches that a HIP graph can hold:
 //   k_batch_prep     one thread per controller: reads the controller's
 //                    measured state and call index from mapped host memory
 //                    and completes its per-step constants;
@@ -7,6 +7,8 @@
 //                    that the host orders (by default longest first; the
 //                    hardware starts workgroups in list order), running the
 //                    same rollout body as the single-controller kernel;
+//   k_batch_cvar     where the batch has controllers in the flattened layout:
+//                    the CVaR of their samples from the stored risk costs;
 //   k_batch_update   one workgroup per (controller, chunk) item, the same
 //                    update body as the single-controller kernel, merged per
 //                    controller by its last chunk.
@@ -92,6 +94,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
     batch_rollout_item<kNoise>(ctls, items, work);
 }
 
+// The CVaR pass of the controllers in the flattened layout: one workgroup per
+// (controller, workgroup) item.
+__global__ void __launch_bounds__(256) k_batch_cvar(const BatchCtl* __restrict__ ctls,
+                                                    const int2* __restrict__ citems) {
+    extern __shared__ float bush[];
+    const int2 cw = citems[blockIdx.x];
+    const BatchCtl& b = ctls[__builtin_amdgcn_readfirstlane(cw.x)];
+    const StepConst& c = b.c;
+    cvar_pass(as_global(b.L), c.K, c.M, tail_lanes(c.M), c.n_tail, c.scale_risk, c.B, as_global(b.cvar),
+              __builtin_amdgcn_readfirstlane(cw.y), bush);
+}
+
 __global__ void __launch_bounds__(256) k_batch_update(const BatchCtl* __restrict__ ctls,
                                                       const int2* __restrict__ uitems) {
     extern __shared__ float bush[];
@@ -123,6 +137,9 @@ hipError_t launch_batch(const BatchLaunch& L, hipStream_t stream, hipEvent_t ev_
         else
             hipLaunchKernelGGL(k_batch_rollout, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
     }
+    for (int i0 = 0; i0 < L.n_citems; i0 += kMaxItemsPerLaunch)
+        hipLaunchKernelGGL(k_batch_cvar, dim3(std::min(L.n_citems - i0, kMaxItemsPerLaunch)), dim3(256), L.lds_cvar,
+                           stream, L.ctls, L.citems + i0);
     if (ev_mid) (void)hipEventRecord(ev_mid, stream);
     hipLaunchKernelGGL(k_batch_update, dim3(L.n_uitems), dim3(256), L.lds_update, stream, L.ctls, L.uitems);
     return hipGetLastError();

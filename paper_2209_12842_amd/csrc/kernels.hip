@@ -165,33 +165,13 @@ __global__ void __launch_bounds__(1024) k_cvar(const float* __restrict__ L, int 
     if (active && m == 0) cvar_out[k] = cv;
 }
 
-// CVaR of stored risk costs for tails of at most kWaveTail values: a wave per
-// sample, or for M <= 32 a segment of a wave (wave_tail_mean); the mean for
-// the risk scaling from the sample's costs staged in LDS.  The stage entry
-// point and the CVaR pass of the flattened two-launch step (M > 256) use it
+// The stage entry point and the CVaR pass of the flattened two-launch step
 // (K = 1024, M = 300: 10.7 -> 5.6 us against one 512-thread workgroup per
 // sample, whose exchanges across waves meet at barriers).
 __global__ void __launch_bounds__(256) k_cvar_wave(const float* __restrict__ L, int K, int M, int P, int n_tail,
                                                    int scale_risk, float B, float* __restrict__ cvar_out) {
-    extern __shared__ float wsh[];  // 4 waves x 64 / P samples x M, with scale_risk only
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, per = 64 / P;
-    const int seg = lane / P;
-    const int k = (blockIdx.x * 4 + wv) * per + seg;
-    const float* Lk = L + (size_t)min(k, K - 1) * M;
-    float mu = 0.0f;
-    if (scale_risk) {
-        float* v = wsh + (size_t)(wv * per + seg) * M;
-        for (int i = lane & (P - 1); i < M; i += P) v[i] = Lk[i];
-        __syncthreads();
-        mu = seq_sum(v, M) / (float)M;
-    }
-    const float cv = wave_tail_mean(
-        [&](int i) {
-            const float x = Lk[i];
-            return scale_risk ? __fmaf_rn(B, x - mu, mu) : x;
-        },
-        (uint32_t)lane, M, P, n_tail);
-    if (k < K && (lane & (P - 1)) == 0) cvar_out[k] = cv;
+    extern __shared__ float wsh[];
+    cvar_pass(L, K, M, P, n_tail, scale_risk, B, cvar_out, (int)blockIdx.x, wsh);
 }
 
 // The CVaR pass of the flattened two-launch step (M > 256) for longer tails:
@@ -312,10 +292,9 @@ size_t update_lds_bytes(int T, int G) {
 
 static hipError_t launch_cvar_wave(const float* L, int K, int M, int n_tail, int scale_risk, float B, float* out,
                                    hipStream_t stream) {
-    const int P = tail_lanes(M), per = 4 * (64 / P);  // samples per workgroup
-    const size_t lds = scale_risk ? sizeof(float) * (size_t)per * M : 0;
-    hipLaunchKernelGGL(k_cvar_wave, dim3((K + per - 1) / per), dim3(256), lds, stream, L, K, M, P, n_tail, scale_risk,
-                       B, out);
+    const int P = tail_lanes(M), per = cvar_samples_per_wg(M);
+    hipLaunchKernelGGL(k_cvar_wave, dim3((K + per - 1) / per), dim3(256), cvar_lds_bytes(M, scale_risk), stream, L, K,
+                       M, P, n_tail, scale_risk, B, out);
     return hipGetLastError();
 }
 

@@ -60,11 +60,12 @@ struct BatchLaunch {
     BatchCtl* ctls;
     const BatchInput* inputs;  // device address of the mapped inputs
     const int2* items;         // rollout items (controller, workgroup), in the order they start
+    const int2* citems;        // items of the CVaR pass (controller, workgroup)
     const int2* uitems;        // update items (controller, chunk)
     unsigned long long* work;  // kWorkSlots broad-phase candidate counters, or null
-    int n_ctl, n_items, n_uitems;
+    int n_ctl, n_items, n_citems, n_uitems;
     int noise_kind;            // the disturbance form of every controller, or -1 when they differ
-    size_t lds_rollout, lds_update;
+    size_t lds_rollout, lds_cvar, lds_update;
 };
 
 hipError_t launch_batch(const BatchLaunch& L, hipStream_t stream, hipEvent_t ev_start = nullptr,
@@ -92,6 +93,13 @@ struct GradArgs {
     int R;              // lanes per weighted sample: nominal + tail (or + all draws)
     int stride;         // lane capacity K R
 };
+
+// The CVaR pass (cvar_pass): samples per workgroup of 256 threads, and its
+// dynamic LDS.
+inline int cvar_samples_per_wg(int M) { return 4 * (64 / tail_lanes(M)); }
+inline size_t cvar_lds_bytes(int M, bool scale_risk) {
+    return scale_risk ? sizeof(float) * (size_t)cvar_samples_per_wg(M) * M : 0;
+}
 
 int update_parts(int T);
 size_t update_lds_bytes(int T, int G);

@@ -60,6 +60,32 @@ __device__ __forceinline__ void group_bounds(const float4* __restrict__ obs, int
 // the box by the distance travelled; 6 gave the shortest steps on the 50- and
 // 200-obstacle tracks (horizons 50 and 100).
 constexpr int kCullSteps = 6;
+// CVaR of stored risk costs for tails of at most kWaveTail values, by
+// workgroup wg of 256 threads: a wave per sample, or for M <= 32 a segment of
+// P lanes of a wave (wave_tail_mean); the mean for the risk scaling from the
+// sample's costs staged in LDS (wsh: cvar_lds_bytes).
+__device__ __forceinline__ void cvar_pass(const float* __restrict__ L, int K, int M, int P, int n_tail,
+                                          int scale_risk, float B, float* __restrict__ cvar_out, int wg, float* wsh) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, per = 64 / P;
+    const int seg = lane / P;
+    const int k = (wg * 4 + wv) * per + seg;
+    const float* Lk = L + (size_t)min(k, K - 1) * M;
+    float mu = 0.0f;
+    if (scale_risk) {
+        float* v = wsh + (size_t)(wv * per + seg) * M;
+        for (int i = lane & (P - 1); i < M; i += P) v[i] = Lk[i];
+        __syncthreads();
+        mu = seq_sum(v, M) / (float)M;
+    }
+    const float cv = wave_tail_mean(
+        [&](int i) {
+            const float x = Lk[i];
+            return scale_risk ? __fmaf_rn(B, x - mu, mu) : x;
+        },
+        (uint32_t)lane, M, P, n_tail);
+    if (k < K && (lane & (P - 1)) == 0) cvar_out[k] = cv;
+}
+
 // LDS floats of a nominal workgroup before the obstacle table (aligned to 16
 // bytes): two buffers of one run of sampled controls for 64 samples, (dt a,
 // tan(delta) / wheelbase) and the control-cost term of each.
