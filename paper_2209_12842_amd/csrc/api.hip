@@ -346,7 +346,7 @@ namespace {
 
 ramppi::StepBuffers step_buffers(const mppi_handle* h, float* V_dev) {
     ramppi::StepBuffers bufs;
-    bufs.obs = reinterpret_cast<const float4*>(h->ws + h->l.obs);
+    bufs.obs = reinterpret_cast<const float*>(h->ws + h->l.obs);
     bufs.V = V_dev;
     bufs.Vout = V_dev;
     bufs.u = reinterpret_cast<float2*>(h->ws + h->l.u);
@@ -360,7 +360,7 @@ ramppi::StepBuffers step_buffers(const mppi_handle* h, float* V_dev) {
     bufs.counter = reinterpret_cast<unsigned*>(h->ws + h->l.counter);
     bufs.u0_host = nullptr;
     bufs.work = nullptr;
-    bufs.chunk_ctr = reinterpret_cast<unsigned*>(h->ws + h->l.chunk);
+    bufs.clear = nullptr;
     return bufs;
 }
 
@@ -504,14 +504,14 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
         return hip_fail(e, "hipHostGetDevicePointer");
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    std::vector<float> staged(4 * (size_t)(p->n_obs > 0 ? p->n_obs : 1), 0.0f);
+    std::vector<float> staged(3 * (size_t)(p->n_obs > 0 ? p->n_obs : 1), 0.0f);
     const std::vector<int> order = obstacle_order(obstacles_host, p->n_obs);
     for (int i = 0; i < p->n_obs; ++i) {
-        staged[4 * i + 0] = obstacles_host[3 * order[i] + 0];
-        staged[4 * i + 1] = obstacles_host[3 * order[i] + 1];
-        staged[4 * i + 2] = obstacles_host[3 * order[i] + 2];
+        staged[3 * i + 0] = obstacles_host[3 * order[i] + 0];
+        staged[3 * i + 1] = obstacles_host[3 * order[i] + 1];
+        staged[3 * i + 2] = obstacles_host[3 * order[i] + 2];
     }
-    e = hipMemcpyAsync(h->ws + l.obs, staged.data(), 16 * (size_t)p->n_obs, hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(h->ws + l.obs, staged.data(), 12 * (size_t)p->n_obs, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + l.counter, 0, 4, s);
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + l.work, 0, 16 * (size_t)ramppi::kWorkSlots, s);
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + l.chunk, 0, 4 * (size_t)h->g.G, s);
@@ -658,17 +658,6 @@ mppi_status scratch_address(int dev, char** out) {
     return MPPI_OK;
 }
 
-// Stages the caller's obstacles (n_obs x 3 floats) as the table's float4
-// entries and zeroes the update's counters, which must start at zero (a fill
-// kernel rather than a memset, so that the call can be captured in a graph).
-__global__ void k_noalloc_prep(const float* __restrict__ obs3, int n_obs, float4* __restrict__ obs4,
-                               unsigned* __restrict__ counter, unsigned* __restrict__ chunk_ctr, int G) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_obs) obs4[i] = make_float4(obs3[3 * i], obs3[3 * i + 1], obs3[3 * i + 2], 0.0f);
-    if (i < G) chunk_ctr[i] = 0u;
-    if (i == 0) *counter = 0u;
-}
-
 }  // namespace
 
 extern "C" {
@@ -705,8 +694,10 @@ mppi_status mppi_step_noalloc(const mppi_params* p, const float* obstacles_dev, 
     fill_dynamic(&c, *p, x0, step_idx);
     c.u0_seq = 0;
 
+    // the rollouts read the caller's obstacles where they are, and set the
+    // update's counter to zero (other steps keep other values at its place)
     ramppi::StepBuffers bufs;
-    bufs.obs = reinterpret_cast<const float4*>(ws + l.obs);
+    bufs.obs = obstacles_dev;
     bufs.V = V_dev;
     bufs.Vout = V_dev;
     bufs.u = reinterpret_cast<float2*>(ws + l.u);
@@ -720,17 +711,13 @@ mppi_status mppi_step_noalloc(const mppi_params* p, const float* obstacles_dev, 
     bufs.counter = reinterpret_cast<unsigned*>(ws + l.counter);
     bufs.u0_host = nullptr;
     bufs.work = nullptr;
-    bufs.chunk_ctr = reinterpret_cast<unsigned*>(ws + l.chunk);
+    bufs.clear = bufs.counter;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int n_prep = std::max(std::max(p->n_obs, g.G), 1);
-    hipLaunchKernelGGL(k_noalloc_prep, dim3((n_prep + 255) / 256), dim3(256), 0, s, obstacles_dev, p->n_obs,
-                       reinterpret_cast<float4*>(ws + l.obs), bufs.counter, bufs.chunk_ctr, g.G);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "obstacle staging launch");
     // always the two-launch form (rollouts, then the update): it needs no
     // occupancy query and gives the same bits as the one-launch step
-    e = ramppi::launch_step(c, bufs, g.block, g.lds_rollout, g.G, g.lds_update, s, nullptr, nullptr, nullptr);
+    const hipError_t e =
+        ramppi::launch_step(c, bufs, g.block, g.lds_rollout, g.G, g.lds_update, s, nullptr, nullptr, nullptr);
     if (e != hipSuccess) return hip_fail(e, "step launch");
     return MPPI_OK;
 }
@@ -1298,7 +1285,7 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
         std::memset(&c, 0, sizeof c);
         fill_static(&c.c, p[i], g, n_tail, n_warm);
         char* base = b->ws + bl.ctl_base[i];
-        c.obs = reinterpret_cast<const float4*>(base + l.obs);
+        c.obs = reinterpret_cast<const float*>(base + l.obs);
         c.V = V_dev[i];
         c.u = reinterpret_cast<float2*>(base + l.u);
         c.S = reinterpret_cast<float*>(base + l.S);
@@ -1323,12 +1310,12 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params* p, const float* cons
         }
         for (int w = 0; w < n_cvar_wg(&p[i], g); ++w) citems.push_back(make_int2(i, w));
         for (int ch = 0; ch < g.G; ++ch) uitems.push_back(make_int2(i, ch));
-        std::vector<float> staged(4 * (size_t)(p[i].n_obs > 0 ? p[i].n_obs : 1), 0.0f);
+        std::vector<float> staged(3 * (size_t)(p[i].n_obs > 0 ? p[i].n_obs : 1), 0.0f);
         const std::vector<int> order = obstacle_order(obstacles_host[i], p[i].n_obs);
         for (int j = 0; j < p[i].n_obs; ++j)
-            for (int q = 0; q < 3; ++q) staged[4 * j + q] = obstacles_host[i][3 * order[j] + q];
+            for (int q = 0; q < 3; ++q) staged[3 * j + q] = obstacles_host[i][3 * order[j] + q];
         if (e == hipSuccess && p[i].n_obs > 0)
-            e = hipMemcpyAsync(base + l.obs, staged.data(), 16 * (size_t)p[i].n_obs, hipMemcpyHostToDevice, s);
+            e = hipMemcpyAsync(base + l.obs, staged.data(), 12 * (size_t)p[i].n_obs, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipMemsetAsync(base + l.counter, 0, 4, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);  // staged is a local buffer
     }

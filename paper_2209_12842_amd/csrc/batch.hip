@@ -58,7 +58,7 @@ __device__ __forceinline__ void batch_rollout_item(const BatchCtl* __restrict__ 
     const StepConst c = b.c;
     // the controller's buffers, read from device memory: in the global
     // address space (as_global)
-    const float4* obs = as_global(b.obs);
+    const float* obs = as_global(b.obs);
     const float* V = as_global(b.V);
     float2* u = as_global(b.u);
     const auto late = [&] {

@@ -41,6 +41,7 @@ template <int kNoise, bool kFuse>
 __device__ __forceinline__ void rollout_launch_body(const RolloutArgs& a) {
     extern __shared__ float2 smem[];
     const int item = kFuse ? (int)blockIdx.x : rollout_item(a.c);
+    if (!kFuse && a.clear && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0u;  // the update launch follows
     rollout_body<kNoise>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
     if constexpr (kFuse) {
         __shared__ float red[16];
@@ -223,7 +224,7 @@ __global__ void __launch_bounds__(1024) k_cvar_sorted(const float* __restrict__ 
 
 static RolloutArgs rollout_args(const StepConst& c, const StepBuffers& b, int* ranks, int* tail_idx,
                                 const FuseArgs* fa) {
-    return RolloutArgs{c, b.obs, b.V, b.u, b.S, b.cvar, b.L, ranks, tail_idx, b.work, fa};
+    return RolloutArgs{c, b.obs, b.V, b.u, b.S, b.cvar, b.L, ranks, tail_idx, b.work, fa, b.clear};
 }
 
 template <bool kFuse>

@@ -12,7 +12,7 @@ namespace ramppi {
 
 // Device buffers of one step (all inside the caller's workspace except V).
 struct StepBuffers {
-    const float4* obs;  // n_obs x (cx, cy, r, 0)
+    const float* obs;   // n_obs x (cx, cy, r)
     const float* V;     // T x 2, the mean sequence (read by k_rollout)
     float* Vout;        // T x 2, V+ (written by k_merge; the same memory as V)
     float2* u;          // T x K sampled controls, time-major
@@ -26,14 +26,14 @@ struct StepBuffers {
     float* u0;          // 2
     float* u0_host;     // 2 floats of mapped pinned host memory, or null
     unsigned long long* work;  // kWorkSlots broad-phase candidate counters, or null
-    unsigned* chunk_ctr;       // G per-chunk contributor counters (zero between launches)
+    unsigned* clear;           // counter that the rollout launch sets to zero, or null
 };
 
 // One controller of a batch, in device memory: its step constants (the static
 // part written at creation, the per-step part by k_batch_prep) and buffers.
 struct BatchCtl {
     StepConst c;
-    const float4* obs;
+    const float* obs;
     float* V;
     float2* u;
     float* S;

@@ -19,15 +19,17 @@ struct GradOut {
 // (-2 cx, -2 cy, r^2 - cx^2 - cy^2, q), q = (1 + 2^-16) r^2 + 2^-15 (cx^2 + cy^2)
 // the squared reach of the broad-phase test (obstacle_hits_culled); entries
 // i >= n_obs are padding that no point can hit, (0, 0, -inf, -inf).
-__device__ __forceinline__ float4 obstacle_entry(const float4* __restrict__ obs, int n_obs, int i, float fx,
+// The obstacles are three floats apart, as the caller of the step without a
+// handle holds them: that step reads them where they are.
+__device__ __forceinline__ float4 obstacle_entry(const float* __restrict__ obs, int n_obs, int i, float fx,
                                                  float fy) {
     if (i < n_obs) {
-        const float4 o = obs[i];  // cx, cy, r, unused
-        const float cx = o.x - fx;
-        const float cy = o.y - fy;
+        const float cx = obs[3 * i] - fx;
+        const float cy = obs[3 * i + 1] - fy;
+        const float r = obs[3 * i + 2];
         const float c2 = __fmaf_rn(cx, cx, cy * cy);
-        const float q = __fmaf_rn(1.0000152587890625f * o.z, o.z, 3.0517578125e-05f * c2);
-        return make_float4(-2.0f * cx, -2.0f * cy, __fmaf_rn(o.z, o.z, -c2), q);
+        const float q = __fmaf_rn(1.0000152587890625f * r, r, 3.0517578125e-05f * c2);
+        return make_float4(-2.0f * cx, -2.0f * cy, __fmaf_rn(r, r, -c2), q);
     }
     return make_float4(0.0f, 0.0f, -__builtin_inff(), -__builtin_inff());
 }
@@ -38,7 +40,7 @@ __device__ __forceinline__ float4 obstacle_entry(const float4* __restrict__ obs,
 // n_grp..63 get a box that meets nothing.  One whole wave computes them
 // (lane j takes entry 64 g + j, computed as obstacle_entry computes it),
 // before the barrier that precedes the rollouts.
-__device__ __forceinline__ void group_bounds(const float4* __restrict__ obs, int n_obs, int n_grp, float fx,
+__device__ __forceinline__ void group_bounds(const float* __restrict__ obs, int n_obs, int n_grp, float fx,
                                              float fy, float4* gbox) {
     const int lane = threadIdx.x & 63;
     const float inf = __builtin_inff();
@@ -96,7 +98,7 @@ constexpr int kNomBuf = 3 * 64 * kCullSteps;
 // its rollouts (RolloutLate).
 struct RolloutArgs {
     StepConst c;
-    const float4* obs;
+    const float* obs;
     const float* V;
     float2* u;
     float* S;
@@ -106,6 +108,8 @@ struct RolloutArgs {
     int* tail_idx;
     unsigned long long* work;  // broad-phase counters, or null
     const struct FuseArgs* fa;  // the update's buffers (one-launch step)
+    unsigned* clear;  // the update's counter, set to zero by a two-launch step
+                      // whose workspace other steps use too, or null
 };
 
 // What a workgroup needs after its rollouts.  The compiler loads every kernel
@@ -396,7 +400,7 @@ __device__ __forceinline__ void count_work(unsigned long long* work, int item, i
 // (spb samples of M lanes).  Ends with every lane past its last LDS access
 // (the caller may reuse the LDS after a barrier).
 template <int kNoise, class Late>
-__device__ __forceinline__ void rollout_body(const StepConst& c, const float4* __restrict__ obs,
+__device__ __forceinline__ void rollout_body(const StepConst& c, const float* __restrict__ obs,
                                              const float* __restrict__ V, float2* __restrict__ u_out, int item,
                                              float2* smem, Late late) {
     float2* ctl = smem;
