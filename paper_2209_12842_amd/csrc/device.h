@@ -716,40 +716,47 @@ __device__ __forceinline__ void lane_pair(float v, float& a, float& b) {
     }
 }
 
-// One exchange at distance kJ of a bitonic sort: the lower lane of a pair
-// keeps the larger value and the upper one the smaller, the other way round
-// where the top bit of `flip` is set, as the median of the two values and
-// +-infinity.  The sign comes from the lane number by arithmetic: constant
-// lane masks would fill the scalar registers of the rollout kernels.
-template <int kJ>
-__device__ __forceinline__ float sort_cx(float v, uint32_t lane, uint32_t flip) {
-    float a, b;
-    lane_pair<kJ>(v, a, b);
+// One exchange at distance kJ of a bitonic sort, in kC columns of one value
+// per lane: the lower lane of a pair keeps the larger value and the upper one
+// the smaller, the other way round where the top bit of `flip` is set and
+// again in every odd column, as the median of the two values and +-infinity.
+// The sign comes from the lane number by arithmetic: constant lane masks
+// would fill the scalar registers of the rollout kernels.
+template <int kJ, int kC>
+__device__ __forceinline__ void sort_cx(float (&v)[kC], uint32_t lane, uint32_t flip) {
     const uint32_t t = (lane << (31 - __builtin_ctz(kJ))) ^ flip;
-    return __builtin_amdgcn_fmed3f(a, b, __uint_as_float((t & 0x80000000u) | 0x7F800000u));
+    const uint32_t lim = (t & 0x80000000u) | 0x7F800000u;
+#pragma unroll
+    for (int j = 0; j < kC; ++j) {
+        float a, b;
+        lane_pair<kJ>(v[j], a, b);
+        v[j] = __builtin_amdgcn_fmed3f(a, b, __uint_as_float(j & 1 ? lim ^ 0x80000000u : lim));
+    }
 }
 
 // Merge block k (a power of two up to 64, the same in every lane) of a
-// bitonic sort of one value per lane.
-__device__ __forceinline__ float sort_block(float v, uint32_t lane, int k, uint32_t flip) {
-    if (k > 32) v = sort_cx<32>(v, lane, flip);
-    if (k > 16) v = sort_cx<16>(v, lane, flip);
-    if (k > 8) v = sort_cx<8>(v, lane, flip);
-    if (k > 4) v = sort_cx<4>(v, lane, flip);
-    if (k > 2) v = sort_cx<2>(v, lane, flip);
-    return sort_cx<1>(v, lane, flip);
+// bitonic sort of kC columns of one value per lane.
+template <int kC>
+__device__ __forceinline__ void sort_block(float (&v)[kC], uint32_t lane, int k, uint32_t flip) {
+    if (k > 32) sort_cx<32>(v, lane, flip);
+    if (k > 16) sort_cx<16>(v, lane, flip);
+    if (k > 8) sort_cx<8>(v, lane, flip);
+    if (k > 4) sort_cx<4>(v, lane, flip);
+    if (k > 2) sort_cx<2>(v, lane, flip);
+    sort_cx<1>(v, lane, flip);
 }
 
 // Sorts the values of each segment of P lanes (a power of two up to 64, the
-// same in every lane), one per lane, without NaN: larger first, or smaller
-// first when the top bit of `flip` is set.  The loop over the merge blocks
-// stays a loop: unrolled, its code takes longer to fetch than to run in a
-// launch that sorts once.
-__device__ __forceinline__ float sort_lanes(float v, uint32_t lane, int P, uint32_t flip) {
+// same in every lane) in kC columns of one value per lane, without NaN:
+// larger first, or smaller first when the top bit of `flip` is set, and the
+// other way round in odd columns.  The loop over the merge blocks stays a
+// loop: unrolled, its code takes longer to fetch than to run in a launch that
+// sorts once.
+template <int kC>
+__device__ __forceinline__ void sort_lanes(float (&v)[kC], uint32_t lane, int P, uint32_t flip) {
     const uint32_t i = lane & (uint32_t)(P - 1);
 #pragma clang loop unroll(disable)
-    for (int k = 2; k <= P; k <<= 1) v = sort_block(v, lane, k, flip ^ ((i & (uint32_t)k) ? 0x80000000u : 0u));
-    return v;
+    for (int k = 2; k <= P; k <<= 1) sort_block(v, lane, k, flip ^ ((i & (uint32_t)k) ? 0x80000000u : 0u));
 }
 
 // Longest tail that wave_tail_mean can take: the lanes of a wave.
@@ -762,29 +769,70 @@ __host__ __device__ __forceinline__ int tail_lanes(int M) {
     return P;
 }
 
+// The 64 largest of the kC (1 or 4) columns of 64 values that start at value
+// c (value i < M for this lane at i = c + its number in its segment, P lanes
+// wide when one column holds all of M), and of `best` when c > 0, sorted in
+// descending order into `best`.  Columns are sorted in turn the one way and
+// the other, so that the larger of two in each lane are the 64 largest of
+// both as a bitonic sequence, which one merge block sorts.
+template <int kC, class Value>
+__device__ __forceinline__ void wave_tail_columns(Value value, int c, uint32_t lane, int M, int P, float (&best)[1],
+                                                  uint64_t& nans) {
+    float w[kC];
+#pragma unroll
+    for (int j = 0; j < kC; ++j) {
+        const int i = c + 64 * j + (int)(lane & (uint32_t)(P - 1));
+        w[j] = i < M ? value(i) : -__builtin_inff();
+    }
+#pragma unroll
+    for (int j = 0; j < kC; ++j) nans |= __builtin_amdgcn_ballot_w64(w[j] != w[j]);
+    const uint32_t turn = c ? 0x80000000u : 0u;
+    float q[1];
+    if constexpr (kC == 1) {
+        sort_lanes(w, lane, P, turn);
+        q[0] = w[0];
+    } else {
+        sort_lanes(w, lane, 64, 0u);
+        float p[2] = {fmaxf(w[0], w[1]), fmaxf(w[2], w[3])};
+        sort_block(p, lane, 64, 0u);
+        q[0] = fmaxf(p[0], p[1]);
+        sort_block(q, lane, 64, turn);
+    }
+    if (c) {
+        best[0] = fmaxf(best[0], q[0]);
+        sort_block(best, lane, 64, 0u);
+    } else {
+        best[0] = q[0];
+    }
+}
+
 // Mean of the n_tail (at most kWaveTail) largest of a sample's M values,
 // summed in descending order -- the bits of tail_rank_scatter and tail_sum --
 // by the lanes of one segment of P = tail_lanes(M) lanes, each segment of the
 // wave a sample of its own.  value(i) is the sample's value i < M for this
-// lane's sample; lane is the lane's number in its wave.  The first P values are sorted across the lanes; every
-// further column of 64 is sorted the other way round, so that the larger of
-// the two in each lane are the 64 largest of both as a bitonic sequence,
-// which one merge block sorts.  A value that is not a number makes the mean
-// one too.  Every lane of the wave must be active; the result is in every
-// lane of the segment.
-template <class Value>
+// lane's sample; lane is the lane's number in its wave.  The exchanges of one
+// column form one serial chain: with kWide four columns of 64 values run side
+// by side where three or more are left (K = 1024, M = 300: the CVaR pass 7.5
+// -> 6.4 us; two columns gain nothing, eight lose as much in padding as they
+// save).  The rollout kernels keep to single columns, since the longer code
+// costs them more to fetch (M = 128: step 622 -> 626 us).  A value that is
+// not a number makes the mean one too.  Every lane of the wave must be
+// active; the result is in every lane of the segment.
+template <bool kWide, class Value>
 __device__ __forceinline__ float wave_tail_mean(Value value, uint32_t lane, int M, int P, int n_tail) {
-    const float ninf = -__builtin_inff();
-    float v = 0.0f;
+    float best[1] = {0.0f};
     uint64_t nans = 0;
 #pragma clang loop unroll(disable)
-    for (int c = 0; c < M; c += 64) {  // one column when M <= 64
-        const int i = c + (int)(lane & (uint32_t)(P - 1));
-        float w = i < M ? value(i) : ninf;
-        nans |= __builtin_amdgcn_ballot_w64(w != w);
-        w = sort_lanes(w, lane, P, c ? 0x80000000u : 0u);
-        v = c ? sort_block(fmaxf(v, w), lane, 64, 0u) : w;
+    for (int c = 0; c < M;) {
+        if (kWide && M - c > 128) {
+            wave_tail_columns<kWide ? 4 : 1>(value, c, lane, M, 64, best, nans);
+            c += 256;
+        } else {
+            wave_tail_columns<1>(value, c, lane, M, P, best, nans);
+            c += 64;
+        }
     }
+    const float v = best[0];
     // the segment's first n_tail lanes, added in order by every lane of it
     const int base = (int)(lane & ~(uint32_t)(P - 1)) << 2;
     float s = 0.0f;

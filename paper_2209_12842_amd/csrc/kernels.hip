@@ -167,8 +167,9 @@ __global__ void __launch_bounds__(1024) k_cvar(const float* __restrict__ L, int 
 }
 
 // The stage entry point and the CVaR pass of the flattened two-launch step
-// (K = 1024, M = 300: 10.7 -> 5.6 us against one 512-thread workgroup per
-// sample, whose exchanges across waves meet at barriers).
+// (K = 1024, M = 300: 10.7 -> 6.4 us against one 512-thread workgroup per
+// sample, whose exchanges across waves meet at barriers; bound by the serial
+// chain of the exchanges, some 3 us of it the launch itself).
 __global__ void __launch_bounds__(256) k_cvar_wave(const float* __restrict__ L, int K, int M, int P, int n_tail,
                                                    int scale_risk, float B, float* __restrict__ cvar_out) {
     extern __shared__ float wsh[];

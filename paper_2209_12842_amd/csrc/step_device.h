@@ -79,7 +79,7 @@ __device__ __forceinline__ void cvar_pass(const float* __restrict__ L, int K, in
         __syncthreads();
         mu = seq_sum(v, M) / (float)M;
     }
-    const float cv = wave_tail_mean(
+    const float cv = wave_tail_mean<true>(
         [&](int i) {
             const float x = Lk[i];
             return scale_risk ? __fmaf_rn(B, x - mu, mu) : x;
@@ -268,7 +268,7 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
         const float* v = vals + sl * M;
         float mu = 0.0f;
         if (scale_risk) mu = seq_sum(v, M) / (float)M;
-        const float cv = wave_tail_mean(
+        const float cv = wave_tail_mean<false>(
             [&](int i) {
                 const float x = v[i];
                 return scale_risk ? __fmaf_rn(B, x - mu, mu) : x;
