@@ -181,9 +181,9 @@ mppi_status mppi_step(mppi_handle *h, const float x0[4], float *V_dev,
  *   V_dev         device, T x 2 floats: in V, out V+ (as for mppi_step).
  *   u0_dev        device, 2 floats receiving the first command before any
  *                 shift, or NULL.
- * Enqueues three kernels on `stream` (obstacle staging and counter reset,
- * rollouts, update) and returns; the results equal those of mppi_step with
- * the same inputs, bit for bit.  Every call on a device shares that device's
+ * Enqueues two kernels on `stream` (rollouts, update; three with a CVaR pass
+ * where the rollouts take the flattened layout) and returns; the results
+ * equal those of mppi_step with the same inputs, bit for bit.  Every call on a device shares that device's
  * scratch, which keeps the last call's contents: calls that overlap on one
  * device (on different streams, or from several threads) race and must be
  * ordered by the caller. */

@@ -192,6 +192,8 @@ Layout layout(const mppi_params* p) {
     const Geometry g = geometry(p);
     Layout l;
     size_t o = 0;
+    // (16 bytes an obstacle, of which the step uses 12: the workspace sizes that
+    // callers know, and what the static scratch holds, stay as they were)
     l.obs = o;     o += align_up(16 * (size_t)(p->n_obs > 0 ? p->n_obs : 1));
     l.u = o;       o += align_up(8 * (size_t)p->K * p->T);
     l.S = o;       o += align_up(4 * (size_t)p->K);
@@ -629,9 +631,9 @@ mppi_status mppi_step(mppi_handle* h, const float x0[4], float* V_dev, uint32_t 
 
 namespace {
 
-// Scratch memory of mppi_step_noalloc: the step's workspace (obstacle table,
-// sampled controls, per-sample costs, chunk partials, counters) in a static
-// device array, so that the call allocates nothing.  Each device that runs
+// Scratch memory of mppi_step_noalloc: the step's workspace (sampled
+// controls, per-sample costs, chunk partials, counters) in a static device
+// array, so that the call allocates nothing.  Each device that runs
 // the call holds its own copy until the process ends.  Host code uses only
 // the device address that hipGetSymbolAddress returns for the current device
 // (g_scratch_dev), never the array's name.

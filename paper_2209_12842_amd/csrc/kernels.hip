@@ -176,8 +176,8 @@ __global__ void __launch_bounds__(256) k_cvar_wave(const float* __restrict__ L, 
     cvar_pass(L, K, M, P, n_tail, scale_risk, B, cvar_out, (int)blockIdx.x, wsh);
 }
 
-// The CVaR pass of the flattened two-launch step (M > 256) for longer tails:
-// one sample per workgroup of P threads, P the power of two at or above M (at most 1024).
+// The CVaR pass of the flattened two-launch step for tails longer than
+// kWaveTail: one sample per workgroup of P threads, P the power of two at or above M (at most 1024).
 // The M stored risk costs are scaled as cvar_epilogue scales them (the mean
 // summed by one thread in draw order), padded to P with -inf, sorted by the
 // same bitonic stages (larger first, equal costs by smaller draw index), and

@@ -1157,9 +1157,9 @@ __device__ __forceinline__ unsigned chunk_contributors(const StepConst& c, int b
 
 // After a rollout workgroup has stored its results: it counts itself in the
 // chunks its samples fall in, and for every chunk it completes runs that
-// chunk's update (its inputs S, CVaR and u are then all stored, published by
-// the other workgroups' releases); the workgroup that completes the last
-// chunk merges them.  No workgroup waits for another.
+// chunk's update (its inputs S, CVaR and u are then all stored, written
+// through by agent_store); the workgroup that completes the last chunk merges
+// them.  No workgroup waits for another.
 __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs& f, int item, const float* S,
                                              const float* cvar, const float2* u, float* V, float* ush, float* red,
                                              int* flag_sh, int* fin_sh) {
