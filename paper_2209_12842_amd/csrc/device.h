@@ -95,6 +95,14 @@ __device__ __forceinline__ float agent_load(const float* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A value of the mean sequence.  Where one launch serves step after step
+// (kServe), the last step's merge wrote it in the same launch.
+template <bool kServe>
+__device__ __forceinline__ float mean_load(const float* p) {
+    if constexpr (kServe) return agent_load(p);
+    return *p;
+}
+
 // Waits until this wave's stores have reached the scope they were made at.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -590,6 +598,7 @@ __device__ __forceinline__ int obstacle_hits_culled(const float4* __restrict__ o
 
 // Sampled control (Eq. 2b-2c with the warm / zero-mean rule of Algorithm 1):
 // u = clamp(base + sqrt(Sigma_eps) z, u_lo, u_hi), base = v_t for k < n_warm.
+template <bool kServe>
 __device__ __forceinline__ float2 sample_control_from(const StepConst& c, const float* __restrict__ V, int k, int t,
                                                      uint4 r, uint32_t exp_word) {
     float z0, z1;
@@ -597,7 +606,7 @@ __device__ __forceinline__ float2 sample_control_from(const StepConst& c, const 
     // every lane reads v_t (t < T, in bounds) and warm samples keep it: a
     // select, not a branch
     const bool warm = k < c.n_warm;
-    const float v0 = V[2 * t], v1 = V[2 * t + 1];
+    const float v0 = mean_load<kServe>(&V[2 * t]), v1 = mean_load<kServe>(&V[2 * t + 1]);
     const float b0 = warm ? v0 : 0.0f;
     const float b1 = warm ? v1 : 0.0f;
     float a = __fmaf_rn(c.se0, z0, b0);
@@ -607,9 +616,10 @@ __device__ __forceinline__ float2 sample_control_from(const StepConst& c, const 
     return make_float2(a, d);
 }
 
+template <bool kServe = false>
 __device__ __forceinline__ float2 sample_control(const StepConst& c, const float* __restrict__ V, int k, int t) {
     const uint4 r = philox4x32_10((uint32_t)t, kCtrlWord, (uint32_t)k, c.step_idx, c.key0, c.key1);
-    return sample_control_from(c, V, k, t, r, 0x7Fu);
+    return sample_control_from<kServe>(c, V, k, t, r, 0x7Fu);
 }
 
 // Angle wrap to (-pi, pi].

@@ -97,21 +97,22 @@ __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg)
         const RolloutArgs* p = late_args();
         StepConst c = p->c;
         const ServeReq* r = sa.req_dev;
-        c.fx = r->fx;
-        c.fy = r->fy;
-        c.tox = r->tox;
-        c.toy = r->toy;
-        c.theta0 = r->theta0;
-        c.psi0 = r->psi0;
-        c.v0 = r->v0;
-        c.step_idx = r->step_idx;
-        rollout_body<kNoise>(c, p->obs, p->V, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
+        c.fx = serve_field(&r->fx);
+        c.fy = serve_field(&r->fy);
+        c.tox = serve_field(&r->tox);
+        c.toy = serve_field(&r->toy);
+        c.theta0 = serve_field(&r->theta0);
+        c.psi0 = serve_field(&r->psi0);
+        c.v0 = serve_field(&r->v0);
+        c.step_idx = (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)__hip_atomic_load(&r->step_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        rollout_body<kNoise, true>(c, p->obs, p->V, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
         const RolloutArgs* e = late_args();
         StepConst ce = e->c;
         ce.step_idx = c.step_idx;
         ce.u0_seq = seq;
         const FuseArgs f = global_view(*e->fa);
-        fused_update(ce, f, blockIdx.x, e->S, e->cvar, e->u, const_cast<float*>(e->V),
+        fused_update<true>(ce, f, blockIdx.x, e->S, e->cvar, e->u, const_cast<float*>(e->V),
                      reinterpret_cast<float*>(smem), red, &flag_sh, fin_sh);
         __syncthreads();  // LDS and leave_sh are reused by the next request
     }

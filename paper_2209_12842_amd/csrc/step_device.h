@@ -291,7 +291,7 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
 // last (step 37.2 -> 33.4 us with RolloutLate).  On grids of many rounds the
 // three waves that wait cost about 1 % of the step (K = 16384, T = 100,
 // M = 128: 614 -> 621 us).
-template <class Late>
+template <bool kServe, class Late>
 __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float* __restrict__ V,
                                                  float2* __restrict__ u_out, int item, float2* smem,
                                                  const float4* otab, const float4* gbox, int n_grp, int& n_cand,
@@ -314,11 +314,12 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float
             for (int i = first; i < kCullSteps; i += count) {
                 const int t = r * kCullSteps + i;
                 if (t >= T) break;  // uniform
-                const float2 u = sample_control(c, V, kc, t);
+                const float2 u = sample_control<kServe>(c, V, kc, t);
                 if (c.store_u && act) u_out[(size_t)t * c.K + k] = u;
                 reinterpret_cast<float2*>(b)[i * 64 + lane] = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
                 b[2 * 64 * kCullSteps + i * 64 + lane] =
-                    __fmaf_rn(V[2 * t] * c.inv_var0, u.x, V[2 * t + 1] * c.inv_var1 * u.y);
+                    __fmaf_rn(mean_load<kServe>(&V[2 * t]) * c.inv_var0, u.x,
+                              mean_load<kServe>(&V[2 * t + 1]) * c.inv_var1 * u.y);
             }
         };
         produce(0, wave, n_waves);
@@ -399,7 +400,7 @@ __device__ __forceinline__ void count_work(unsigned long long* work, int item, i
 // nominal workgroup (one lane per sample), otherwise a disturbed workgroup
 // (spb samples of M lanes).  Ends with every lane past its last LDS access
 // (the caller may reuse the LDS after a barrier).
-template <int kNoise, class Late>
+template <int kNoise, bool kServe = false, class Late>
 __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __restrict__ obs,
                                              const float* __restrict__ V, float2* __restrict__ u_out, int item,
                                              float2* smem, Late late) {
@@ -415,7 +416,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     int n_gtest = 0;  // broad-phase group tests of this wave (wave-uniform)
 
     if (item < c.n_nom_wg) {
-        nominal_rollouts(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
+        nominal_rollouts<kServe>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
         count_work(late().work, item, n_cand, n_gtest);
         return;
     }
@@ -443,7 +444,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
         const int kk = k_first + sl;
         float2 cu = make_float2(0.0f, 0.0f);
         if (kk < c.K) {
-            const float2 u = sample_control(c, V, kk, t);
+            const float2 u = sample_control<kServe>(c, V, kk, t);
             cu = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
         }
         ctl[idx] = cu;
@@ -636,7 +637,7 @@ __device__ __forceinline__ float seg_min_256(const float* v, float* red) {
 // one-launch update still draws them), so the bit-exact comparison of the
 // two forms in debug mode also checks that the drawn controls are the stored
 // ones.
-template <int kB, bool kRegen = false>
+template <int kB, bool kRegen = false, bool kServe = false>
 __device__ __forceinline__ float* update_chunk(const StepConst& c, int b, int parts, const float* S,
                                                const float* cvar, const float2* __restrict__ u, float* S_tilde,
                                                float* part, float* ush, float* red, bool single,
@@ -656,7 +657,7 @@ __device__ __forceinline__ float* update_chunk(const StepConst& c, int b, int pa
     // below, but the thread's first value is loaded now, so that its load and
     // the first wave's loads of S and CVaR wait on memory together
     const bool has_v = kRegen && tid < 2 * T;
-    const float v_first = has_v ? V[tid] : 0.0f;
+    const float v_first = has_v ? mean_load<kServe>(&V[tid]) : 0.0f;
 
     // 1. modified costs, the chunk's minimum beta_b, its weights and their
     // sum Z_b, and the samples of non-zero weight, all by the first wave:
@@ -714,7 +715,7 @@ __device__ __forceinline__ float* update_chunk(const StepConst& c, int b, int pa
     }
     if (kRegen) {
         if (has_v) vsh[tid] = v_first;
-        for (int i = tid + nt; i < 2 * T; i += nt) vsh[i] = V[i];
+        for (int i = tid + nt; i < 2 * T; i += nt) vsh[i] = mean_load<kServe>(&V[i]);
     }
     __syncthreads();  // wsh, nzpos, nzlist and V published
 
@@ -879,9 +880,9 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
         // mapped pinned host memory: the command first, then the completion
         // word, each at system scope.  The word may release the next served
         // step, whose workgroups read V: every wave waits for its stores of V
-        // (written through to the memory that the XCDs share; the next step's
-        // readers invalidate their caches when they see their request), and
-        // the workgroup meets at a barrier before the word is stored.
+        // (written through to the memory that the XCDs share, from which the
+        // next step's readers load: mean_load), and the workgroup meets at a
+        // barrier before the word is stored.
         if (tid < 2) __hip_atomic_store(&u0_host[tid], vp[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         stores_done();
         __syncthreads();
@@ -1077,7 +1078,8 @@ struct ServeReq {
     uint32_t pad0;
     float fx, fy, tox, toy, theta0, psi0, v0, pad1;
 };
-static_assert(sizeof(ServeReq) == 48, "ServeReq is read as three 16-byte words");
+static_assert(sizeof(ServeReq) == 48 && offsetof(ServeReq, stop) == 4,
+              "ServeReq is read as six 8-byte words, stop in the first's upper half");
 
 struct ServeArgs {
     const ServeReq* req_host;  // mapped host memory (device address)
@@ -1099,36 +1101,35 @@ constexpr unsigned kServeExit = 0xFFFFFFFFu;
 // Workgroup 0's thread 0: waits for request seq in host memory, copies it to
 // device memory and publishes seq in `go`; on a stop request or after
 // idle_ticks without one it publishes kServeExit.  Returns whether to leave.
+// The fields, `stop` among them, are loaded once the number has been seen, in
+// flight together.  Neither here nor in serve_wait_member is a cache written
+// back or invalidated: what changes between requests (the request, V, the
+// values of agent_store) is stored and loaded at device scope, and the rest
+// stays in the caches (32 served steps of K = 2048, T = 50, M = 64: 1376 ->
+// 1308 us; every workgroup used to invalidate its XCD's L2 as it started).
 __device__ __forceinline__ bool serve_wait_leader(const ServeArgs& sa, unsigned seq) {
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
     for (;;) {
-        // relaxed polls (no cache invalidation while other workgroups may
-        // still be finishing the last step), one acquire once it has come
         if (__hip_atomic_load(&sa.req_host->seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == seq) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
-            const ServeReq* r = sa.req_host;
-            if (__hip_atomic_load(&r->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u) break;
-            // three 16-byte reads across PCIe instead of one per field
-            // (after the acquire above, so they see the posted request)
-            ServeReq* d = sa.req_dev;
-            const uint4 a = *reinterpret_cast<const uint4*>(r);
-            const float4 b = *reinterpret_cast<const float4*>(&r->fx);
-            const float4 e = *reinterpret_cast<const float4*>(&r->theta0);
-            d->step_idx = a.z;
-            d->fx = b.x;
-            d->fy = b.y;
-            d->tox = b.z;
-            d->toy = b.w;
-            d->theta0 = e.x;
-            d->psi0 = e.y;
-            d->v0 = e.z;
-            __hip_atomic_store(sa.go, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // keeps the loads below after the poll
+            const uint64_t* r = reinterpret_cast<const uint64_t*>(sa.req_host);
+            uint64_t w[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+                w[i] = __hip_atomic_load(&r[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (w[0] >> 32) break;  // stop
+            uint64_t* d = reinterpret_cast<uint64_t*>(sa.req_dev);
+#pragma unroll
+            for (int i = 1; i < 6; ++i)
+                __hip_atomic_store(&d[i], w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            stores_done();
+            __hip_atomic_store(sa.go, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
         if (__builtin_amdgcn_s_memrealtime() - t0 > sa.idle_ticks) break;
         __builtin_amdgcn_s_sleep(1);
     }
-    __hip_atomic_store(sa.go, kServeExit, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(sa.go, kServeExit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
 }
 
@@ -1138,13 +1139,16 @@ __device__ __forceinline__ bool serve_wait_member(const ServeArgs& sa, unsigned 
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
     for (;;) {
         const unsigned g = __hip_atomic_load(sa.go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (g == seq) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            return false;
-        }
+        if (g == seq) return false;
         if (g == kServeExit || __builtin_amdgcn_s_memrealtime() - t0 > 2 * sa.idle_ticks) return true;
         __builtin_amdgcn_s_sleep(1);
     }
+}
+
+// A field of the request being served (the same in every lane), after the
+// barrier that follows serve_wait_leader and serve_wait_member.
+__device__ __forceinline__ float serve_field(const float* p) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(agent_load(p))));
 }
 
 // Workgroups of a rollout launch whose samples fall in chunk b: the nominal
@@ -1160,6 +1164,7 @@ __device__ __forceinline__ unsigned chunk_contributors(const StepConst& c, int b
 // chunk's update (its inputs S, CVaR and u are then all stored, written
 // through by agent_store); the workgroup that completes the last chunk merges
 // them.  No workgroup waits for another.
+template <bool kServe = false>
 __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs& f, int item, const float* S,
                                              const float* cvar, const float2* u, float* V, float* ush, float* red,
                                              int* flag_sh, int* fin_sh) {
@@ -1190,7 +1195,7 @@ __device__ __forceinline__ void fused_update(const StepConst& c, const FuseArgs&
     const int nf = fin_sh[7];
     if (nf == 0) return;
     for (int i = 0; i < nf; ++i) {
-        float* nb = update_chunk<kFuseBatch, true>(c, fin_sh[i], f.parts, S, cvar, u, f.S_tilde, f.part, ush, red,
+        float* nb = update_chunk<kFuseBatch, true, kServe>(c, fin_sh[i], f.parts, S, cvar, u, f.S_tilde, f.part, ush, red,
                                                    f.G == 1, V);
         if (f.G == 1)
             update_merge_single(c, nb, f.S_tilde, V, f.u0, c.u0_seq ? f.u0_host : nullptr, f.w_hat, ush, red);
