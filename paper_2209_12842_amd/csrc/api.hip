@@ -81,8 +81,10 @@ std::vector<int> obstacle_order(const float* o, int n) {
 }
 
 // Mapped pinned bytes per handle: the first command (2 floats), its
-// completion word, one spare word, then the serving request.
-constexpr size_t kPinnedBytes = 16 + sizeof(ramppi::ServeReq);
+// completion word, then in a line of its own the serving request.
+constexpr size_t kServeOffset = 64;
+constexpr size_t kPinnedBytes = kServeOffset + sizeof(ramppi::ServeReq);
+
 // A call that awaits a completion word asks the stream for an error every
 // kQueryMask + 1 polls, about two milliseconds: a stream query takes some 10
 // us of host time, and one that falls into the last microseconds of a step
@@ -207,7 +209,7 @@ Layout layout(const mppi_params* p) {
     l.work = o;    o += align_up(16 * (size_t)ramppi::kWorkSlots);
     l.chunk = o;   o += align_up(4 * (size_t)g.G);
     l.fuse = o;    o += align_up(sizeof(ramppi::FuseArgs));
-    l.serve = o;   o += align_up(sizeof(ramppi::ServeReq) + sizeof(unsigned));  // request copy, go word
+    l.serve = o;   o += align_up(sizeof(ramppi::ServeReq));  // request copy
     l.ranks = l.tail_idx = l.act_list = l.n_act = l.J = l.states = l.rows = l.rpart = l.gcounter = 0;
     l.R = l.stride = l.n_lane_blocks = 0;
     if (p->flags & MPPI_F_GRAD) {
@@ -494,7 +496,7 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->u0_pinned), kPinnedBytes,
                                  hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) std::memset(h->u0_pinned, 0, kPinnedBytes);
-    h->req = e == hipSuccess ? reinterpret_cast<ramppi::ServeReq*>(h->u0_pinned + 4) : nullptr;
+    h->req = e == hipSuccess ? reinterpret_cast<ramppi::ServeReq*>(h->u0_pinned + kServeOffset / 4) : nullptr;
     if (e != hipSuccess) {
         delete h;
         return hip_fail(e, "hipHostMalloc");
@@ -748,18 +750,16 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
     fill_static(&c, p, g, h->n_tail, h->n_warm);
     fill_dynamic(&c, p, x0, 0);
     ramppi::StepBuffers bufs = step_buffers(h, V_dev);
-    // workspace: request copy | go word
     char* sv = h->ws + h->l.serve;
     ramppi::ServeArgs sa;
-    sa.req_host = reinterpret_cast<const ramppi::ServeReq*>(h->u0_pinned_dev + 4);
+    sa.req_host = reinterpret_cast<const ramppi::ServeReq*>(h->u0_pinned_dev + kServeOffset / 4);
     sa.req_dev = reinterpret_cast<ramppi::ServeReq*>(sv);
-    sa.go = reinterpret_cast<unsigned*>(sv + sizeof(ramppi::ServeReq));
     sa.idle_ticks = 100000ull * idle_ms;  // s_memrealtime runs at 100 MHz
 
     // a new session: requests and completions count from 1 again
     std::memset(h->req, 0, sizeof(ramppi::ServeReq));
     __atomic_store_n(reinterpret_cast<uint32_t*>(h->u0_pinned + 2), 0u, __ATOMIC_RELEASE);
-    e = hipMemsetAsync(sa.go, 0, sizeof(unsigned), s);
+    e = hipMemsetAsync(sv, 0, sizeof(ramppi::ServeReq), s);
     if (e == hipSuccess)
         e = ramppi::launch_serve(c, bufs, g.block, lds,
                                  reinterpret_cast<const ramppi::FuseArgs*>(h->ws + h->l.fuse), sa, s);
@@ -772,21 +772,20 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
 
 namespace {
 
-// Posts the next request: the per-step fields first, its number last.
-void post_request(mppi_handle* h, const ramppi::StepConst* c, uint32_t stop) {
-    ramppi::ServeReq* r = h->req;
-    if (c) {
-        r->step_idx = c->step_idx;
-        r->fx = c->fx;
-        r->fy = c->fy;
-        r->tox = c->tox;
-        r->toy = c->toy;
-        r->theta0 = c->theta0;
-        r->psi0 = c->psi0;
-        r->v0 = c->v0;
+// Posts the next request, or without constants the end of the session.
+void post_request(mppi_handle* h, const ramppi::StepConst* c) {
+    ++h->serve_seq;
+    if (!c) {
+        __atomic_store_n(&h->req->w[0], ramppi::serve_word(ramppi::kServeExit, 0u), __ATOMIC_RELEASE);
+        return;
     }
-    r->stop = stop;
-    __atomic_store_n(&r->seq, ++h->serve_seq, __ATOMIC_RELEASE);
+    const float f[] = {c->fx, c->fy, c->tox, c->toy, c->theta0, c->psi0, c->v0};
+    __atomic_store_n(&h->req->w[ramppi::kServeIdx], ramppi::serve_word(h->serve_seq, c->step_idx), __ATOMIC_RELEASE);
+    for (int i = 0; i < 7; ++i) {
+        uint32_t bits;
+        std::memcpy(&bits, &f[i], 4);
+        __atomic_store_n(&h->req->w[ramppi::kServeFx + i], ramppi::serve_word(h->serve_seq, bits), __ATOMIC_RELEASE);
+    }
 }
 
 }  // namespace
@@ -799,7 +798,7 @@ mppi_status mppi_serve_step(mppi_handle* h, const float x0[4], uint32_t step_idx
         if (!finite(x0[i])) return fail(MPPI_EINVAL, "x0[%d] is not finite", i);
     ramppi::StepConst c;
     fill_dynamic(&c, h->p, x0, step_idx);
-    post_request(h, &c, 0u);
+    post_request(h, &c);
     const uint32_t* word = reinterpret_cast<const uint32_t*>(h->u0_pinned + 2);
     for (uint64_t spin = 1;; ++spin) {
         if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == h->serve_seq) break;
@@ -823,7 +822,7 @@ mppi_status mppi_serve_step(mppi_handle* h, const float x0[4], uint32_t step_idx
 mppi_status mppi_serve_stop(mppi_handle* h) {
     if (!h) return fail(MPPI_EINVAL, "handle is NULL");
     if (!h->serving) return MPPI_OK;
-    post_request(h, nullptr, 1u);
+    post_request(h, nullptr);
     const hipError_t e = hipStreamSynchronize(h->serve_stream);
     h->serving = false;
     // launched steps after the session use completion values above every served one

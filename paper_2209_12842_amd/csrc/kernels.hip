@@ -75,8 +75,8 @@ __global__ void __launch_bounds__(1024) k_rollout_fused(RolloutArgs a) {
 }
 
 // Persistent serving: the one-launch step in a loop, one iteration per
-// request (steps 1, 2, ... of the session).  Thread 0 of workgroup 0 takes
-// the requests from host memory; the others wait on its device-memory word.
+// request (steps 1, 2, ... of the session).  The first wave of workgroup 0
+// takes the requests from host memory; the others wait on its device copy.
 // Every wait is bounded, so every wave leaves even if no request comes.
 template <int kNoise>
 __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg) {
@@ -86,8 +86,12 @@ __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg)
     __shared__ int flag_sh;
     __shared__ int fin_sh[8];
     __shared__ int leave_sh;
+    __shared__ uint32_t words[kServeFields];
     for (unsigned seq = 1;; ++seq) {
-        if (threadIdx.x == 0) leave_sh = blockIdx.x == 0 ? serve_wait_leader(sa, seq) : serve_wait_member(sa, seq);
+        if (threadIdx.x < 64) {
+            const bool leave = serve_wait(sa, seq, blockIdx.x == 0, words);
+            if (threadIdx.x == 0) leave_sh = leave;
+        }
         __syncthreads();
         if (leave_sh) break;
         // The arguments are read again for every request (late_args): the
@@ -96,16 +100,14 @@ __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg)
         // which spilled it into VGPR lanes of the hot loop.
         const RolloutArgs* p = late_args();
         StepConst c = p->c;
-        const ServeReq* r = sa.req_dev;
-        c.fx = serve_field(&r->fx);
-        c.fy = serve_field(&r->fy);
-        c.tox = serve_field(&r->tox);
-        c.toy = serve_field(&r->toy);
-        c.theta0 = serve_field(&r->theta0);
-        c.psi0 = serve_field(&r->psi0);
-        c.v0 = serve_field(&r->v0);
-        c.step_idx = (uint32_t)__builtin_amdgcn_readfirstlane(
-            (int)__hip_atomic_load(&r->step_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        c.step_idx = serve_value(words, kServeIdx);
+        c.fx = __uint_as_float(serve_value(words, kServeFx));
+        c.fy = __uint_as_float(serve_value(words, kServeFy));
+        c.tox = __uint_as_float(serve_value(words, kServeTox));
+        c.toy = __uint_as_float(serve_value(words, kServeToy));
+        c.theta0 = __uint_as_float(serve_value(words, kServeTheta));
+        c.psi0 = __uint_as_float(serve_value(words, kServePsi));
+        c.v0 = __uint_as_float(serve_value(words, kServeV));
         rollout_body<kNoise, true>(c, p->obs, p->V, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
         const RolloutArgs* e = late_args();
         StepConst ce = e->c;

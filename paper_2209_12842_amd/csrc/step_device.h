@@ -1068,23 +1068,26 @@ __device__ __forceinline__ FuseArgs global_view(const FuseArgs& f) {
 // ---- persistent serving: one resident launch runs step after step ----
 
 // One served step's request: the per-step constants the host derives from
-// the measured state (the same arithmetic as for a launched step), written
-// into mapped host memory with seq last; the leader workgroup copies it to
-// device memory for the others.
-struct ServeReq {
-    uint32_t seq;   // request number, 1, 2, ... within a session
-    uint32_t stop;  // non-zero: leave the loop
-    uint32_t step_idx;
-    uint32_t pad0;
-    float fx, fy, tox, toy, theta0, psi0, v0, pad1;
+// the measured state (the same arithmetic as for a launched step), each in
+// the upper half of an eight-byte word whose lower half is the request's
+// number (1, 2, ... within a session), in one line of mapped host memory and
+// again of device memory.  A word is stored and loaded whole, so whoever sees
+// the number in all eight has the request, whatever order they came in.
+enum ServeField {
+    kServeIdx, kServeFx, kServeFy, kServeTox, kServeToy, kServeTheta, kServePsi, kServeV,
+    kServeFields
 };
-static_assert(sizeof(ServeReq) == 48 && offsetof(ServeReq, stop) == 4,
-              "ServeReq is read as six 8-byte words, stop in the first's upper half");
+struct ServeReq {
+    uint64_t w[kServeFields];
+};
+
+__host__ __device__ __forceinline__ uint64_t serve_word(uint32_t seq, uint32_t value) {
+    return (uint64_t)value << 32 | seq;
+}
 
 struct ServeArgs {
     const ServeReq* req_host;  // mapped host memory (device address)
-    ServeReq* req_dev;         // device copy read by every workgroup
-    unsigned* go;              // request number being served, or kServeExit
+    ServeReq* req_dev;         // device copy read by the other workgroups
     uint64_t idle_ticks;       // longest wait for a request (s_memrealtime ticks, 100 MHz)
 };
 
@@ -1092,63 +1095,51 @@ __device__ __forceinline__ ServeArgs global_view(const ServeArgs& a) {
     ServeArgs g = a;
     g.req_host = as_global(a.req_host);
     g.req_dev = as_global(a.req_dev);
-    g.go = as_global(a.go);
     return g;
 }
 
-constexpr unsigned kServeExit = 0xFFFFFFFFu;
+constexpr unsigned kServeExit = 0xFFFFFFFFu;  // a request number: leave
 
-// Workgroup 0's thread 0: waits for request seq in host memory, copies it to
-// device memory and publishes seq in `go`; on a stop request or after
-// idle_ticks without one it publishes kServeExit.  Returns whether to leave.
-// The fields, `stop` among them, are loaded once the number has been seen, in
-// flight together.  Neither here nor in serve_wait_member is a cache written
-// back or invalidated: what changes between requests (the request, V, the
-// values of agent_store) is stored and loaded at device scope, and the rest
-// stays in the caches (32 served steps of K = 2048, T = 50, M = 64: 1376 ->
-// 1308 us; every workgroup used to invalidate its XCD's L2 as it started).
-__device__ __forceinline__ bool serve_wait_leader(const ServeArgs& sa, unsigned seq) {
+// The first wave of a workgroup: waits for request seq and leaves its values
+// in words (LDS, published by the caller's barrier).  Workgroup 0 waits on
+// host memory and copies the request to device memory, on which the others
+// wait.  Returns whether to leave: when kServeExit comes, or without a
+// request within idle_ticks (workgroup 0, which then passes kServeExit on) or
+// twice that.  Lane l takes word l mod 8, so a request is there as soon as
+// it is seen, one trip across PCIe and one through device memory after the
+// host has posted it.  No cache is written back or invalidated: what changes
+// between requests (the request, V, the values of agent_store) is stored and
+// loaded at device scope, and the rest stays in the caches.  (32 served steps
+// of K = 2048, T = 50, M = 64: 1376 us when every workgroup invalidated its
+// XCD's L2 as it started, 1308 without, 1197 with the numbers in the words
+// instead of in words of their own, stored after the others.)
+__device__ __forceinline__ bool serve_wait(const ServeArgs& sa, unsigned seq, bool leader, uint32_t* words) {
+    const int i = threadIdx.x & (kServeFields - 1);
+    const uint64_t limit = leader ? sa.idle_ticks : 2 * sa.idle_ticks;
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    uint64_t w;
+    bool leave = false;
     for (;;) {
-        if (__hip_atomic_load(&sa.req_host->seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == seq) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // keeps the loads below after the poll
-            const uint64_t* r = reinterpret_cast<const uint64_t*>(sa.req_host);
-            uint64_t w[6];
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-                w[i] = __hip_atomic_load(&r[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            if (w[0] >> 32) break;  // stop
-            uint64_t* d = reinterpret_cast<uint64_t*>(sa.req_dev);
-#pragma unroll
-            for (int i = 1; i < 6; ++i)
-                __hip_atomic_store(&d[i], w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            stores_done();
-            __hip_atomic_store(sa.go, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
-        }
-        if (__builtin_amdgcn_s_memrealtime() - t0 > sa.idle_ticks) break;
+        w = leader ? __hip_atomic_load(&sa.req_host->w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)
+                   : __hip_atomic_load(&sa.req_dev->w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        leave = __builtin_amdgcn_ballot_w64((uint32_t)w == kServeExit) != 0;
+        if (leave || __builtin_amdgcn_ballot_w64((uint32_t)w != seq) == 0) break;
+        leave = __builtin_amdgcn_s_memrealtime() - t0 > limit;
+        if (leave) break;
         __builtin_amdgcn_s_sleep(1);
     }
-    __hip_atomic_store(sa.go, kServeExit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-}
-
-// Thread 0 of every other workgroup: waits until `go` names request seq
-// (serve) or kServeExit (leave); leaves too after twice the leader's limit.
-__device__ __forceinline__ bool serve_wait_member(const ServeArgs& sa, unsigned seq) {
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    for (;;) {
-        const unsigned g = __hip_atomic_load(sa.go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (g == seq) return false;
-        if (g == kServeExit || __builtin_amdgcn_s_memrealtime() - t0 > 2 * sa.idle_ticks) return true;
-        __builtin_amdgcn_s_sleep(1);
+    if (threadIdx.x < kServeFields) {
+        if (leader)
+            __hip_atomic_store(&sa.req_dev->w[i], leave ? serve_word(kServeExit, 0u) : w, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        words[i] = (uint32_t)(w >> 32);
     }
+    return leave;
 }
 
-// A field of the request being served (the same in every lane), after the
-// barrier that follows serve_wait_leader and serve_wait_member.
-__device__ __forceinline__ float serve_field(const float* p) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(agent_load(p))));
+// A value of the request being served, after that barrier (the same in every lane).
+__device__ __forceinline__ uint32_t serve_value(const uint32_t* words, ServeField f) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)words[f]);
 }
 
 // Workgroups of a rollout launch whose samples fall in chunk b: the nominal
