@@ -122,8 +122,11 @@ __global__ void __launch_bounds__(256) k_batch_update(const BatchCtl* __restrict
 // Items of one rollout launch: a grid holds fewer than 2^32 threads.
 constexpr int kMaxItemsPerLaunch = 1 << 23;
 
+// (As in a single step, no launch follows one that failed.)
 hipError_t launch_batch(const BatchLaunch& L, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_mid) {
     hipLaunchKernelGGL(k_batch_prep, dim3((L.n_ctl + 63) / 64), dim3(64), 0, stream, L.ctls, L.inputs, L.n_ctl);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     if (ev_start) (void)hipEventRecord(ev_start, stream);
     for (int i0 = 0; i0 < L.n_items; i0 += kMaxItemsPerLaunch) {  // one launch unless the batch is enormous
         const dim3 grid(std::min(L.n_items - i0, kMaxItemsPerLaunch));
@@ -136,10 +139,15 @@ hipError_t launch_batch(const BatchLaunch& L, hipStream_t stream, hipEvent_t ev_
             hipLaunchKernelGGL(k_batch_rollout_one<2>, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
         else
             hipLaunchKernelGGL(k_batch_rollout, grid, dim3(256), L.lds_rollout, stream, L.ctls, items, L.work);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    for (int i0 = 0; i0 < L.n_citems; i0 += kMaxItemsPerLaunch)
+    for (int i0 = 0; i0 < L.n_citems; i0 += kMaxItemsPerLaunch) {
         hipLaunchKernelGGL(k_batch_cvar, dim3(std::min(L.n_citems - i0, kMaxItemsPerLaunch)), dim3(256), L.lds_cvar,
                            stream, L.ctls, L.citems + i0);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     if (ev_mid) (void)hipEventRecord(ev_mid, stream);
     hipLaunchKernelGGL(k_batch_update, dim3(L.n_uitems), dim3(256), L.lds_update, stream, L.ctls, L.uitems);
     return hipGetLastError();

@@ -476,9 +476,12 @@ __global__ void __launch_bounds__(256) k_update_grad(StepConst c, int G, int par
 hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs& a, const GradOut& go, int block,
                        size_t lds_rollout, int G, size_t lds_update, int n_lane_blocks, hipStream_t stream) {
     const int n_dist_wg = (c.K + c.spb - 1) / c.spb;
-    (void)launch_rollout(c, b, block, lds_rollout, n_dist_wg, stream, a.ranks_w, a.tail_w);
+    hipError_t e = launch_rollout(c, b, block, lds_rollout, n_dist_wg, stream, a.ranks_w, a.tail_w);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_update_grad, dim3(G), dim3(256), lds_update, stream, c, G, update_parts(c.T), b.S, b.cvar,
                        b.u, b.S_tilde, b.part, b.counter, b.w_hat, go);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     const int n_time = (int)std::min<int64_t>(kTimeGrid, ((int64_t)c.K * a.R + kTimeRows - 1) / kTimeRows);
     const dim3 grid(std::max(n_lane_blocks, n_time));
     if (c.noise_kind == 1)
@@ -487,6 +490,8 @@ hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs&
         hipLaunchKernelGGL(k_grad_rollouts<2>, grid, dim3(256), 0, stream, c, a);
     else
         hipLaunchKernelGGL(k_grad_rollouts<0>, grid, dim3(256), 0, stream, c, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     const int split = std::min(16, (n_lane_blocks + kReduceBlocks - 1) / kReduceBlocks);
     hipLaunchKernelGGL(k_grad_reduce, dim3(2 * c.T, split), dim3(256), 0, stream, a);
     return hipGetLastError();

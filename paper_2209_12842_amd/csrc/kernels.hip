@@ -231,9 +231,11 @@ static RolloutArgs rollout_args(const StepConst& c, const StepBuffers& b, int* r
     return RolloutArgs{c, b.obs, b.V, b.u, b.S, b.cvar, b.L, ranks, tail_idx, b.work, fa, b.clear};
 }
 
+// (Every launch is checked before the next is made: a launch works on what the
+// one before it has written, so none may follow a failure.)
 template <bool kFuse>
-static void launch_rollout_t(const StepConst& c, const StepBuffers& b, dim3 grid, int block, size_t lds,
-                             hipStream_t stream, int* ranks, int* tail_idx, const FuseArgs* fa) {
+static hipError_t launch_rollout_t(const StepConst& c, const StepBuffers& b, dim3 grid, int block, size_t lds,
+                                   hipStream_t stream, int* ranks, int* tail_idx, const FuseArgs* fa) {
     const RolloutArgs a = rollout_args(c, b, ranks, tail_idx, fa);
     if constexpr (kFuse) {
         if (c.noise_kind == 1)
@@ -250,13 +252,13 @@ static void launch_rollout_t(const StepConst& c, const StepBuffers& b, dim3 grid
         else
             hipLaunchKernelGGL(k_rollout<0>, grid, dim3(block), lds, stream, a);
     }
+    return hipGetLastError();
 }
 
 hipError_t launch_rollout(const StepConst& c, const StepBuffers& b, int block, size_t lds_rollout, int n_dist_wg,
                           hipStream_t stream, int* ranks, int* tail_idx) {
-    launch_rollout_t<false>(c, b, dim3(c.n_nom_wg + n_dist_wg), block, lds_rollout, stream, ranks, tail_idx,
-                            nullptr);
-    return hipGetLastError();
+    return launch_rollout_t<false>(c, b, dim3(c.n_nom_wg + n_dist_wg), block, lds_rollout, stream, ranks, tail_idx,
+                                   nullptr);
 }
 
 hipError_t fused_rollout_capacity(int noise_kind, int block, size_t lds, int* blocks_per_cu) {
@@ -310,23 +312,26 @@ hipError_t launch_step(const StepConst& c, const StepBuffers& b, int block, size
     const dim3 grid((unsigned)(c.n_nom_wg + n_dist));
     if (ev_start) (void)hipEventRecord(ev_start, stream);
     if (fa) {  // one launch: the update runs in the workgroups that finish each chunk
-        launch_rollout_t<true>(c, b, grid, block, lds_rollout > lds_update ? lds_rollout : lds_update, stream,
-                               nullptr, nullptr, fa);
+        const hipError_t e = launch_rollout_t<true>(c, b, grid, block, lds_rollout > lds_update ? lds_rollout : lds_update,
+                                                    stream, nullptr, nullptr, fa);
         if (ev_mid) (void)hipEventRecord(ev_mid, stream);
-    } else {
-        launch_rollout_t<false>(c, b, grid, block, lds_rollout, stream, nullptr, nullptr, nullptr);
-        if (c.flat && c.n_tail <= kWaveTail) {  // each sample's CVaR from the stored risk costs
-            (void)launch_cvar_wave(b.L, c.K, c.M, c.n_tail, c.scale_risk, c.B, b.cvar, stream);
-        } else if (c.flat) {
-            int P = 64;
-            while (P < c.M) P <<= 1;
-            hipLaunchKernelGGL(k_cvar_sorted, dim3(c.K), dim3(P), 2 * sizeof(float) * (size_t)P, stream, b.L, c.M,
-                               c.n_tail, c.scale_risk, c.B, b.cvar);
-        }
-        if (ev_mid) (void)hipEventRecord(ev_mid, stream);
-        hipLaunchKernelGGL(k_update, dim3(G), dim3(256), lds_update, stream, c, G, update_parts(c.T), b.S, b.cvar,
-                           b.u, b.S_tilde, b.part, b.counter, b.Vout, b.u0, b.u0_host, b.w_hat);
+        return e;
     }
+    hipError_t e = launch_rollout_t<false>(c, b, grid, block, lds_rollout, stream, nullptr, nullptr, nullptr);
+    if (e != hipSuccess) return e;
+    if (c.flat && c.n_tail <= kWaveTail) {  // each sample's CVaR from the stored risk costs
+        e = launch_cvar_wave(b.L, c.K, c.M, c.n_tail, c.scale_risk, c.B, b.cvar, stream);
+    } else if (c.flat) {
+        int P = 64;
+        while (P < c.M) P <<= 1;
+        hipLaunchKernelGGL(k_cvar_sorted, dim3(c.K), dim3(P), 2 * sizeof(float) * (size_t)P, stream, b.L, c.M,
+                           c.n_tail, c.scale_risk, c.B, b.cvar);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
+    if (ev_mid) (void)hipEventRecord(ev_mid, stream);
+    hipLaunchKernelGGL(k_update, dim3(G), dim3(256), lds_update, stream, c, G, update_parts(c.T), b.S, b.cvar, b.u,
+                       b.S_tilde, b.part, b.counter, b.Vout, b.u0, b.u0_host, b.w_hat);
     return hipGetLastError();
 }
 
