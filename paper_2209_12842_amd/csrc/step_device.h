@@ -875,7 +875,16 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
         if (shift) src = min(j + 2, 2 * T - 2 + (j & 1));
         agent_store(&V[j], vp[src]);
     }
-    if (tid < 2) u0[tid] = vp[tid];
+    // The workgroup that merges differs from step to step, and where one launch
+    // serves many, an XCD's L2 could still hold an earlier step's command or
+    // weights and write them back over later ones: both are written through.
+    if (tid < 2) agent_store(&u0[tid], vp[tid]);
+    if (c.debug) {
+        // (before the completion word, after which the next served step may
+        // rewrite S~)
+        for (int k = tid; k < K; k += nt)
+            agent_store(&w_hat[k], expf(-(agent_load(&S_tilde[k]) - beta) / c.lambda) * invZ);
+    }
     if (u0_host) {
         // mapped pinned host memory: the command first, then the completion
         // word, each at system scope.  The word may release the next served
@@ -889,9 +898,6 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
         if (tid == 0 && c.u0_seq)
             __hip_atomic_store(reinterpret_cast<unsigned*>(u0_host + 2), c.u0_seq, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-    if (c.debug) {
-        for (int k = tid; k < K; k += nt) w_hat[k] = expf(-(agent_load(&S_tilde[k]) - beta) / c.lambda) * invZ;
     }
 }
 
