@@ -146,10 +146,10 @@ double idle_lane_us(const Geometry& g, const mppi_params* p) {
 // (its tail ranks come from the rollout's own CVaR pass).
 bool flat_pays(const Geometry& g, const mppi_params* p) {
     if (p->flags & MPPI_F_GRAD) return false;
-    if (p->M > 256) return true;
     Geometry f = g;
     set_flat(&f, p);
-    return idle_lane_us(g, p) > 8.0 && f.lds_rollout <= kMaxLdsBytes;
+    if (f.lds_rollout > kMaxLdsBytes) return false;  // it holds the controls of more samples
+    return p->M > 256 || idle_lane_us(g, p) > 8.0;
 }
 
 // Workgroups of the one-launch step.
