@@ -46,11 +46,12 @@ bool finite(float v) { return std::isfinite(v); }
 
 // Dynamic LDS of the rollout kernel: controls, risk costs, tail slots and
 // means of the workgroup's samples, then the obstacle table in groups of 64.
-size_t rollout_lds_bytes(int spb, const mppi_params* p) {
+size_t rollout_lds_bytes(int spb, const mppi_params* p, int nom_groups) {
     if ((int64_t)spb * p->T > (1 << 24)) return SIZE_MAX;  // far beyond any LDS
     // the table (64 entries per group), then 64 group boxes
     const size_t n_grp = (size_t)ramppi::rollout_n_grp(p->n_obs);
-    return 4 * (size_t)ramppi::rollout_otab_offset(spb, p->T, p->M) + 16 * 64 * n_grp + (n_grp > 1 ? 16 * 64 : 0);
+    return 4 * (size_t)ramppi::rollout_otab_offset(spb, p->T, p->M, nom_groups) + 16 * 64 * n_grp +
+           (n_grp > 1 ? 16 * 64 : 0);
 }
 
 // The order in which the obstacles are staged: by angle around their
@@ -102,20 +103,20 @@ struct Geometry {
     size_t lds_rollout, lds_update;
 };
 
-// Nominal workgroups of `groups` times 64 samples each.
-void set_nominal(Geometry* g, int K, int groups) {
+// Nominal workgroups of `groups` times 64 samples each (nominal_rollouts).
+void set_nominal(Geometry* g, const mppi_params* p, int groups) {
     g->nom_groups = groups;
-    g->n_nom_wg = (K + 64 * groups - 1) / (64 * groups);
+    g->n_nom_wg = (p->K + 64 * groups - 1) / (64 * groups);
+    g->lds_rollout = rollout_lds_bytes(g->spb, p, groups);
 }
 
 Geometry geometry(const mppi_params* p) {
     Geometry g;
     g.spb = p->M >= 256 ? 1 : 256 / p->M;
     g.block = (g.spb * p->M + 63) / 64 * 64;
-    set_nominal(&g, p->K, 1);
+    set_nominal(&g, p, 1);
     g.flat = false;
     g.G = (p->K + kPartBlock - 1) / kPartBlock;
-    g.lds_rollout = rollout_lds_bytes(g.spb, p);
     g.lds_update = ramppi::update_lds_bytes(p->T, g.G);
     return g;
 }
@@ -127,7 +128,7 @@ void set_flat(Geometry* g, const mppi_params* p) {
     g->flat = true;
     g->block = 256;
     g->spb = (256 + p->M - 2) / p->M + 1;  // samples that 256 pairs can touch
-    g->lds_rollout = rollout_lds_bytes(g->spb, p);
+    g->lds_rollout = rollout_lds_bytes(g->spb, p, g->nom_groups);
 }
 
 // Microseconds of a full device that the lanes without a draw of the
@@ -155,18 +156,13 @@ bool flat_pays(const Geometry& g, const mppi_params* p) {
 // Workgroups of the one-launch step.
 int64_t one_launch_grid(const Geometry& g, int K) { return g.n_nom_wg + ((int64_t)K + g.spb - 1) / g.spb; }
 
-// Picks the nominal workgroups of a one-launch step on a device that holds
-// `resident` workgroups at once: 64 samples each (the shortest), or where
-// that grid does not fit, as many samples as the workgroup has threads (the
-// fewest workgroups).  Returns whether the grid fits.
-bool fit_nominal(Geometry* g, int K, int64_t resident) {
-    set_nominal(g, K, 1);
-    if (one_launch_grid(*g, K) <= resident) return true;
-    Geometry wide = *g;
-    set_nominal(&wide, K, g->block / 64);
-    if (one_launch_grid(wide, K) > resident) return false;
-    *g = wide;
-    return true;
+// A served step's nominal workgroups where those of 64 samples are too many to
+// be resident at once: a wave for each 64 samples, as many as the workgroup has
+// (eight at most, for the LDS of their controls).
+void set_nominal_packed(Geometry* g, const mppi_params* p) {
+    Geometry packed = *g;
+    set_nominal(&packed, p, std::min(g->block / 64, 8));
+    if (packed.lds_rollout <= kMaxLdsBytes) *g = packed;
 }
 
 // Integer tail size and warm count, computed in double precision.
@@ -522,7 +518,9 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
     if (e == hipSuccess && (p->flags & MPPI_F_GRAD))
         e = hipMemsetAsync(h->ws + l.gcounter, 0, 4 * 2 * (size_t)p->T, s);
     // one launch per step when every workgroup of the step can be resident at
-    // once (the update then runs in the workgroups that finish each chunk)
+    // once (the update then runs in the workgroups that finish each chunk);
+    // grids just above that are two launches (K = 3900, T = 50, M = 64: 58 us;
+    // packed into one launch of fewer, longer nominal workgroups 72)
     h->fuse = false;
     ramppi::FuseArgs fa;
     std::memset(&fa, 0, sizeof fa);
@@ -531,7 +529,7 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
         e = ramppi::fused_rollout_capacity((int)p->noise_kind, h->g.block,
                                            std::max(h->g.lds_rollout, h->g.lds_update), &per_cu);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-        h->fuse = e == hipSuccess && fit_nominal(&h->g, p->K, (int64_t)per_cu * n_cu);
+        h->fuse = e == hipSuccess && one_launch_grid(h->g, p->K) <= (int64_t)per_cu * n_cu;
         fa.chunk_ctr = reinterpret_cast<unsigned*>(h->ws + l.chunk);
         fa.counter = reinterpret_cast<unsigned*>(h->ws + l.counter);
         fa.S_tilde = reinterpret_cast<float*>(h->ws + l.S_tilde);
@@ -732,17 +730,24 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
     if (h->serving) return fail(MPPI_EINVAL, "the handle is already serving");
     if (idle_ms < 1 || idle_ms > kMaxServeIdleMs)
         return fail(MPPI_EINVAL, "idle_ms = %u outside [1, %u]", idle_ms, kMaxServeIdleMs);
-    if (!h->fuse) return fail(MPPI_EUNSUPPORTED, "the step does not run as one launch, so it cannot be served");
     const mppi_params& p = h->p;
-    Geometry g = h->g;
+    if (p.flags & MPPI_F_SPLIT_UPDATE)
+        return fail(MPPI_EUNSUPPORTED, "the step does not run as one launch, so it cannot be served");
+    // the nominal form of the one-launch step, or where that grid cannot be
+    // resident at once, the one of fewer workgroups
+    Geometry g = geometry(&p);
+    for (int form = 0;; ++form) {
+        if (form == 1) set_nominal_packed(&g, &p);
+        int per_cu = 0, n_cu = 0;
+        hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, std::max(g.lds_rollout, g.lds_update), &per_cu);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device);
+        if (e != hipSuccess) return hip_fail(e, "serving occupancy");
+        if (one_launch_grid(g, p.K) <= (int64_t)per_cu * n_cu) break;
+        if (form == 1)
+            return fail(MPPI_EUNSUPPORTED, "the serving grid (%lld workgroups) cannot be resident at once",
+                        (long long)one_launch_grid(g, p.K));
+    }
     const size_t lds = std::max(g.lds_rollout, g.lds_update);
-    int per_cu = 0, n_cu = 0;
-    hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, lds, &per_cu);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device);
-    if (e != hipSuccess) return hip_fail(e, "serving occupancy");
-    if (!fit_nominal(&g, p.K, (int64_t)per_cu * n_cu))
-        return fail(MPPI_EUNSUPPORTED, "the serving grid (%lld workgroups) cannot be resident at once",
-                    (long long)one_launch_grid(g, p.K));
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     ramppi::StepConst c;
@@ -759,7 +764,7 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
     // a new session: requests and completions count from 1 again
     std::memset(h->req, 0, sizeof(ramppi::ServeReq));
     __atomic_store_n(reinterpret_cast<uint32_t*>(h->u0_pinned + 2), 0u, __ATOMIC_RELEASE);
-    e = hipMemsetAsync(sv, 0, sizeof(ramppi::ServeReq), s);
+    hipError_t e = hipMemsetAsync(sv, 0, sizeof(ramppi::ServeReq), s);
     if (e == hipSuccess)
         e = ramppi::launch_serve(c, bufs, g.block, lds,
                                  reinterpret_cast<const ramppi::FuseArgs*>(h->ws + h->l.fuse), sa, s);
@@ -1013,7 +1018,7 @@ Geometry batch_geometry(const mppi_params* p, bool flat) {
     Geometry g = geometry(p);
     g.spb = p->M >= kBatchBlock ? 1 : kBatchBlock / p->M;
     g.block = kBatchBlock;
-    g.lds_rollout = rollout_lds_bytes(g.spb, p);
+    set_nominal(&g, p, 1);
     int n_tail, n_warm;
     derived_counts(p, &n_tail, &n_warm);
     if (flat && g.spb * p->M < 249 && n_tail <= ramppi::kWaveTail) {

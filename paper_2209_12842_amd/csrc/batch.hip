@@ -77,16 +77,15 @@ __device__ __forceinline__ void batch_rollout_item(const BatchCtl* __restrict__ 
     }
 }
 
-// Controllers of several disturbance forms.
-__global__ void __launch_bounds__(256) k_batch_rollout(const BatchCtl* __restrict__ ctls,
-                                                       const int2* __restrict__ items,
-                                                       unsigned long long* __restrict__ work) {
+// Controllers of several disturbance forms.  Like the two-launch rollout kernel
+// compiled for five waves per SIMD.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
+    k_batch_rollout(const BatchCtl* __restrict__ ctls, const int2* __restrict__ items,
+                    unsigned long long* __restrict__ work) {
     batch_rollout_item<-1>(ctls, items, work);
 }
 
-// One disturbance form for the whole batch: compiled, like the two-launch
-// rollout kernel, for five waves per SIMD (the kernel for several forms
-// needs the registers of the largest and holds four).
+// One disturbance form for the whole batch: a third of the code.
 template <int kNoise>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
     k_batch_rollout_one(const BatchCtl* __restrict__ ctls, const int2* __restrict__ items,

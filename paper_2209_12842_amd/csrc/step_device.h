@@ -88,9 +88,10 @@ __device__ __forceinline__ void cvar_pass(const float* __restrict__ L, int K, in
     if (k < K && (lane & (P - 1)) == 0) cvar_out[k] = cv;
 }
 
-// LDS floats of a nominal workgroup before the obstacle table (aligned to 16
-// bytes): two buffers of one run of sampled controls for 64 samples, (dt a,
-// tan(delta) / wheelbase) and the control-cost term of each.
+// LDS floats of one run of sampled controls for 64 samples: (dt a, tan(delta)
+// / wheelbase) and the control-cost term of each.  A nominal workgroup has a
+// buffer for each of its groups of samples, or two for a single one
+// (nominal_rollouts), before the obstacle table (aligned to 16 bytes).
 constexpr int kNomBuf = 3 * 64 * kCullSteps;
 
 // Arguments of a rollout kernel: one struct, the kernel's first parameter, so
@@ -154,13 +155,14 @@ __device__ __forceinline__ RolloutLate late_view(const RolloutArgs* a) {
 //   float4 otab[64 n_grp] the obstacle table, padded to groups of 64 entries
 //                         (16-byte aligned; n_grp = ceil(n_obs / 64))
 //   float4 gbox[64]       the groups' boxes for the group skip (group_bounds)
-// Nominal workgroups keep their runs of sampled controls (2 kNomBuf floats)
+// Nominal workgroups keep their runs of sampled controls (kNomBuf floats each)
 // before otab instead.  rollout_otab_offset gives the offset of otab in
 // floats.  Every workgroup writes otab and gbox from the raw obstacles before
 // its rollouts.
-__host__ __device__ __forceinline__ int rollout_otab_offset(int spb, int T, int M) {
+__host__ __device__ __forceinline__ int rollout_otab_offset(int spb, int T, int M, int nom_groups) {
     const int dist = (2 * spb * T + 2 * spb * M + spb + 3) & ~3;
-    return dist > 2 * kNomBuf ? dist : 2 * kNomBuf;
+    const int nom = (nom_groups > 1 ? nom_groups : 2) * kNomBuf;
+    return dist > nom ? dist : nom;
 }
 
 __host__ __device__ __forceinline__ int rollout_n_grp(int n_obs) { return (n_obs + 63) >> 6; }
@@ -278,19 +280,23 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
     }
 }
 
-// The nominal rollouts of a workgroup: c.nom_groups groups of 64 samples, one
-// after the other; in each, the first wave rolls the 64 samples out (one per
-// lane; lanes past K repeat the last sample, since the obstacle test works on
-// whole waves, and write nothing) while the other waves sample the controls
-// of the next run of kCullSteps steps into LDS, one barrier per run.  The
-// rollouts are a chain of T steps bound by latency and by the issue slots
-// that the disturbed waves leave, and drawing the controls (Philox,
-// Box-Muller, the steering tangent) is 60 % of a nominal step's
-// instructions: moved off the chain, the nominal rollouts of K = 2048, T = 50,
-// M = 64 end at 27 us of the launch instead of 35 us and no longer finish
-// last (step 37.2 -> 33.4 us with RolloutLate).  On grids of many rounds the
-// three waves that wait cost about 1 % of the step (K = 16384, T = 100,
-// M = 128: 614 -> 621 us).
+// The nominal rollouts of a workgroup, one sample per lane, in runs of
+// kCullSteps steps whose sampled controls pass through LDS (lanes past K repeat
+// the last sample, since the obstacle test works on whole waves, and write
+// nothing).  Two forms:
+//  - one group of 64 samples: the first wave rolls them out while the other
+//    waves draw the controls of the next run, one barrier per run.  The
+//    rollouts are a chain of T steps bound by latency and by the issue slots
+//    that the disturbed waves leave, and drawing the controls (Philox,
+//    Box-Muller, the steering tangent) is 60 % of a nominal step's
+//    instructions: moved off the chain, the nominal rollouts of K = 2048,
+//    T = 50, M = 64 end at 27 us of the launch instead of 35 us and no longer
+//    finish last (step 37.2 -> 33.4 us with RolloutLate).
+//  - served steps whose grid would not be resident at once with that many
+//    workgroups (nom_groups > 1): each of the first nom_groups waves draws the
+//    controls of 64 samples of its own and rolls them out (K = 3900, T = 50,
+//    M = 64: served step 64.1 us; the groups one after the other in the first
+//    form 68.2).
 template <bool kServe, class Late>
 __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float* __restrict__ V,
                                                  float2* __restrict__ u_out, int item, float2* smem,
@@ -302,43 +308,42 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n_waves = (int)blockDim.x >> 6;  // at least 3 (spb M > 128)
     const int n_runs = (T + kCullSteps - 1) / kCullSteps;
-    for (int g = 0; g < c.nom_groups; ++g) {
-        const int k0 = (item * c.nom_groups + g) * 64;
-        if (k0 >= c.K) break;  // uniform
-        const int k = k0 + lane;
-        const bool act = k < c.K;
-        const int kc = act ? k : c.K - 1;
-        // the controls of run r, its steps shared out over `count` waves
-        const auto produce = [&](int r, int first, int count) {
-            float* b = buf + (r & 1) * kNomBuf;
-            for (int i = first; i < kCullSteps; i += count) {
-                const int t = r * kCullSteps + i;
-                if (t >= T) break;  // uniform
-                const float2 u = sample_control<kServe>(c, V, kc, t);
-                if (c.store_u && act) u_out[(size_t)t * c.K + k] = u;
-                reinterpret_cast<float2*>(b)[i * 64 + lane] = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
-                b[2 * 64 * kCullSteps + i * 64 + lane] =
-                    __fmaf_rn(mean_load<kServe>(&V[2 * t]) * c.inv_var0, u.x,
-                              mean_load<kServe>(&V[2 * t + 1]) * c.inv_var1 * u.y);
-            }
-        };
-        produce(0, wave, n_waves);
-        __syncthreads();  // the first run's controls, and the table, staged
-        if (wave != 0) {
-            for (int r = 1; r <= n_runs; ++r) {
-                if (r < n_runs) produce(r, wave - 1, n_waves - 1);
-                __syncthreads();
-            }
-            continue;
+    const bool own = kServe && c.nom_groups > 1;
+    const int k0 = (item * c.nom_groups + (own ? wave : 0)) * 64;
+    const bool rolls = own ? wave < c.nom_groups && k0 < c.K : wave == 0;
+    const int k = k0 + lane;
+    const bool act = k < c.K;
+    const int kc = act ? k : c.K - 1;
+    if (own) buf += wave * kNomBuf;
+    // the controls of run r, its steps shared out over `count` waves
+    const auto produce = [&](int r, int first, int count) {
+        float* b = buf + (own ? 0 : (r & 1) * kNomBuf);
+        for (int i = first; i < kCullSteps; i += count) {
+            const int t = r * kCullSteps + i;
+            if (t >= T) break;  // uniform
+            const float2 u = sample_control<kServe>(c, V, kc, t);
+            if (c.store_u && act) u_out[(size_t)t * c.K + k] = u;
+            reinterpret_cast<float2*>(b)[i * 64 + lane] = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
+            b[2 * 64 * kCullSteps + i * 64 + lane] =
+                __fmaf_rn(mean_load<kServe>(&V[2 * t]) * c.inv_var0, u.x,
+                          mean_load<kServe>(&V[2 * t + 1]) * c.inv_var1 * u.y);
         }
-        const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        State s{0.0f, 0.0f, c.psi0, c.v0};
-        float acc = 0.0f, ctrl = 0.0f;
-        int cnt = 0;
-        const StepConst cn = with_vector_constants(c);
-        const float gamma = in_vgpr(c.gamma);
-        for (int r = 0; r < n_runs; ++r) {
-            const float* b = buf + (r & 1) * kNomBuf;
+    };
+    if (!own) produce(0, wave, n_waves);
+    __syncthreads();  // the first run's controls, and the table, staged
+    const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    State s{0.0f, 0.0f, c.psi0, c.v0};
+    float acc = 0.0f, ctrl = 0.0f;
+    int cnt = 0;
+    const StepConst cn = with_vector_constants(c);
+    const float gamma = in_vgpr(c.gamma);
+    for (int r = 0; r < n_runs; ++r) {
+        if (own ? rolls : wave != 0 && r + 1 < n_runs) {
+            produce(own ? r : r + 1, own ? 0 : wave - 1, own ? 1 : n_waves - 1);
+            if (own) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // every lane reads what it wrote itself
+        }
+        if (rolls) {
+            const float* b = buf + (own ? 0 : (r & 1) * kNomBuf);
             // one nominal state step: running and control costs at x_t (the
             // control cost is summed in every case and used when asked, so
             // that the step holds no branch), then x_{t+1}
@@ -377,14 +382,15 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float
                 }
                 if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
             }
-            __syncthreads();  // the next run's controls are in, this run's are read
         }
-        const RolloutLate e = late();
-        float S = __fmaf_rn(e.c->c_obs, (float)cnt, acc);
-        if (e.c->use_ctrl) S += ctrl;
-        if (e.c->use_term) S += terminal_cost(c, s);
-        if (act) agent_store(&e.S[k], S);
+        if (!own) __syncthreads();  // the next run's controls are in, this run's are read
     }
+    if (!rolls) return;
+    const RolloutLate e = late();
+    float S = __fmaf_rn(e.c->c_obs, (float)cnt, acc);
+    if (e.c->use_ctrl) S += ctrl;
+    if (e.c->use_term) S += terminal_cost(c, s);
+    if (act) agent_store(&e.S[k], S);
 }
 
 // Adds a wave's broad-phase work to its slot of the counters (timing mode).
@@ -408,7 +414,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     const int tid = threadIdx.x;
     const int spb = c.spb, M = c.M, T = c.T;
     const int n_grp = rollout_n_grp(c.n_obs);
-    float4* otab = reinterpret_cast<float4*>(reinterpret_cast<float*>(smem) + rollout_otab_offset(spb, T, M));
+    float4* otab = reinterpret_cast<float4*>(reinterpret_cast<float*>(smem) + rollout_otab_offset(spb, T, M, c.nom_groups));
     float4* gbox = otab + 64 * n_grp;
     for (int i = tid; i < n_grp * 64; i += blockDim.x) otab[i] = obstacle_entry(obs, c.n_obs, i, c.fx, c.fy);
     if (n_grp > 1 && tid < 64) group_bounds(obs, c.n_obs, n_grp, c.fx, c.fy, gbox);

@@ -1,0 +1,46 @@
+"""Where a step is one launch and how a served step's nominal workgroups are
+laid out, on a device that holds 1024 workgroups at once: a step whose grid of
+64-sample nominal workgroups does not fit takes two launches, and a served
+one, which has no such choice, packs them (CPU only)."""
+import ctypes
+
+import pytest
+
+import fake_hip
+
+TWO, FLAT = ["k_rollout", "k_update"], ["k_rollout", "k_cvar_wave", "k_update"]
+CASES = {  # (K, M, resident workgroups per unit): the step's kernels, the served grid or None where it is refused
+    (3852, 64, 4): (["k_rollout_fused"], 963 + 61),
+    (3855, 64, 4): (TWO, 964 + 16),                   # 964 + 61 is one too many
+    (4032, 64, 4): (TWO, 1008 + 16),
+    (4033, 64, 4): (TWO, None),
+    (14000, 16, 4): (TWO, 875 + 55),
+    (511, 512, 2): (FLAT, 511 + 1),
+    (254, 1024, 1): (["k_rollout", "k_cvar_sorted", "k_update"], 254 + 1),
+}
+
+
+def launches(K, M, per_cu):
+    import paper_2209_12842_amd as R
+    L, mem = R.lib(), fake_hip.memory
+    fake_hip.fake.fake_resident(per_cu)
+    p, obs, x0 = fake_hip.world(K=K, M=M, T=20)
+    h = fake_hip.handle(p, obs)
+    V = mem(8 * p.T)
+    fake_hip.fake.fake_reset(-1)
+    R.check(L.mppi_step(h, x0, V, 0, None, None))
+    step = [k for k, *_ in fake_hip.launches()]
+    fake_hip.fake.fake_reset(-1)
+    status = L.mppi_serve_start(h, V, 100, None)
+    serve = fake_hip.launches()
+    assert (status == 0) == (len(serve) == 1) and (status in (0, -4))
+    L.mppi_destroy(h)
+    return [step, serve[0][1] if serve else None, serve[0][3] if serve else 0]
+
+
+@pytest.mark.parametrize("K,M,per_cu", list(CASES))
+def test_forms(K, M, per_cu):
+    step, grid, lds = fake_hip.run("test_nominal_forms_cpu", "launches(%d, %d, %d)" % (K, M, per_cu))
+    assert step == CASES[(K, M, per_cu)][0]
+    assert grid == CASES[(K, M, per_cu)][1]
+    assert lds <= 64 * 1024

@@ -1,0 +1,39 @@
+"""Served steps whose nominal workgroups are packed, a wave for each 64 samples
+(grids that would not be resident with one workgroup for each), bit for bit
+against launched steps, which take two launches at these sizes."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("world,kw", [("c2", dict(K=3900, T=13, M=64)), ("c2", dict(K=14001, T=6, M=16, noise_kind=1)),
+                                      ("c2", dict(K=45000, T=7, M=4)), ("p0", dict(K=4030, T=5, M=60)),
+                                      ("c2", dict(K=3999, T=1, M=64, n_obs=0)), ("c2", dict(K=511, T=12, M=512)),
+                                      ("c2", dict(K=3900, T=20, M=64, n_obs=130, debug=True))])
+def test_packed_sessions_follow_launched_steps(world, kw):
+    import paper_2209_12842_amd as ra
+    from paper_2209_12842_amd import workloads as W
+    torch.cuda.set_device(0)
+    kw = dict(kw)
+    debug = kw.pop("debug", False)
+    w = W.make_world(world, lam=50.0, shift=True, **kw)
+    V0 = W.random_V(int(w["params"]["T"]), 3)
+    xs = [np.asarray(w["x0"], dtype=np.float32) + np.float32(0.01 * i) for i in range(12)]
+    out = []
+    for served in (False, True):
+        c = ra.Controller(w["params"], w["obstacles"], debug=debug)
+        V = c.new_V(V0)
+        if served:
+            c.serve_start(V)
+        u = [np.array(c.serve_step(x, i) if served else c.step(x, V, i)) for i, x in enumerate(xs)]
+        if served:
+            c.serve_stop()
+        torch.cuda.synchronize()
+        keys = ("S", "cvar", "S_tilde") + (("u", "L", "w_hat") if debug else ())
+        out.append(dict({k: v.cpu().numpy().copy() for k, v in c.debug().items() if k in keys},
+                        V=V.cpu().numpy().copy(), cmd=np.stack(u)))
+        c.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
