@@ -177,6 +177,21 @@ void derived_counts(const mppi_params* p, int* n_tail, int* n_warm) {
     *n_warm = nw;
 }
 
+// Whether the per-sample layout sorts its tails inside single waves
+// (cvar_waves) or over the whole workgroup (cvar_epilogue): where the waves
+// hold the workgroup's samples at once.  A second pass over them, as for most M
+// below 52 that are no power of two, costs more than the M comparisons per lane
+// it saves (K = 1666, T = 10, M = 36: 19.3 us by waves, 17.9 otherwise; K =
+// 25000, T = 20, M = 40: 77.8 and 75.2; with one pass K = 16666, M = 60: 74.0
+// and 76.9), and from M = 512 the exchanges of a workgroup of M threads are
+// the shorter chain for powers of two (K = 200, T = 20, M = 512: 26.1 and
+// 23.8; M = 448 25.1 and 30.3).
+bool wave_tails_pay(const mppi_params& p, const Geometry& g, int n_tail) {
+    if (n_tail > ramppi::kWaveTail) return false;
+    if (p.M >= 512 && (p.M & (p.M - 1)) == 0) return false;
+    return g.spb <= g.block / 64 * (64 / ramppi::tail_lanes(p.M));
+}
+
 // Workspace layout (byte offsets), each buffer 256-byte aligned.
 struct Layout {
     size_t obs, u, S, cvar, S_tilde, w_hat, L, part, u0, counter, work, chunk, fuse, serve;
@@ -250,6 +265,7 @@ void fill_static(ramppi::StepConst* cp, const mppi_params& p, const Geometry& g,
     c.nom_groups = g.nom_groups;
     c.n_warm = n_warm;
     c.n_tail = n_tail;
+    c.wave_tails = wave_tails_pay(p, g, n_tail);
     c.dt = p.dt;
     c.inv_wheelbase = (float)(1.0 / (double)p.wheelbase);
     c.u_lo0 = p.u_lo[0];

@@ -229,6 +229,7 @@ struct StepConst {
     int32_t nom_groups;  // groups of 64 samples per nominal workgroup
     int32_t n_warm;      // samples k < n_warm keep the mean sequence
     int32_t n_tail;      // M - ceil(alpha M) + 1
+    int32_t wave_tails;  // the per-sample layout's CVaR by single waves (cvar_waves)
     float dt, inv_wheelbase;
     float u_lo0, u_lo1, u_hi0, u_hi1;
     float se0, se1;      // control-noise standard deviations

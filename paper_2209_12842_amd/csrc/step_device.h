@@ -252,8 +252,8 @@ __device__ __forceinline__ float cvar_epilogue(float* vals, float* tail, float* 
 // needed.  store(sl, cvar) is called by one lane per sample.  Bound by the
 // chain of exchanges: at K = 2048, M = 64 the epilogue takes 1.9 us instead
 // of the 3.5 us of the sort with draw indices, and for M not a power of two
-// it replaces M comparisons per lane (K = 4000, T = 60, M = 100: step 96.7
-// -> 92.5 us).
+// it replaces M comparisons per lane (K = 8333, T = 20, M = 120: step 82.0 ->
+// 73.1 us).  Taken where the waves hold all samples at once (wave_tails_pay).
 template <class Store>
 __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, int n_tail, int scale_risk, float B,
                                            int tid, Store store) {
@@ -557,7 +557,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     float* vals = reinterpret_cast<float*>(smem + (size_t)spb_e * ce.T);
     float* tail = vals + spb_e * M_e;
     float* means = tail + spb_e * M_e;
-    if (!ce.grad && ce.n_tail <= kWaveTail) {
+    if (!ce.grad && ce.wave_tails) {
         if (sl_e < spb_e) vals[tid_e] = active_e ? L : 0.0f;
         cvar_waves(vals, spb_e, M_e, ce.n_tail, ce.scale_risk, ce.B, tid_e, [&](int q, float cv) {
             const int ks = wg * spb_e + q;
