@@ -156,13 +156,20 @@ bool flat_pays(const Geometry& g, const mppi_params* p) {
 // Workgroups of the one-launch step.
 int64_t one_launch_grid(const Geometry& g, int K) { return g.n_nom_wg + ((int64_t)K + g.spb - 1) / g.spb; }
 
-// A served step's nominal workgroups where those of 64 samples are too many to
-// be resident at once: a wave for each 64 samples, as many as the workgroup has
-// (eight at most, for the LDS of their controls).
+// Nominal workgroups of a wave for each 64 samples, as many as the workgroup
+// has (eight at most, for the LDS of their controls).
 void set_nominal_packed(Geometry* g, const mppi_params* p) {
     Geometry packed = *g;
     set_nominal(&packed, p, std::min(g->block / 64, 8));
     if (packed.lds_rollout <= kMaxLdsBytes) *g = packed;
+}
+
+// The layout of a two-launch step: flattened or not; packed nominal workgroups
+// for one or two draws (K = 73773, T = 56, M = 2, boundary cost: 95.4 -> 92.1
+// us), not for three (K = 100000, T = 40, M = 3: 77.7, packed 83.3).
+void set_two_launch(Geometry* g, const mppi_params* p) {
+    if (flat_pays(*g, p)) set_flat(g, p);
+    if (p->M < 3) set_nominal_packed(g, p);
 }
 
 // Integer tail size and warm count, computed in double precision.
@@ -557,7 +564,7 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
         fa.parts = ramppi::update_parts(p->T);
         if (e == hipSuccess) e = hipMemcpyAsync(h->ws + l.fuse, &fa, sizeof fa, hipMemcpyHostToDevice, s);
     }
-    if (!h->fuse && flat_pays(h->g, p)) set_flat(&h->g, p);
+    if (!h->fuse) set_two_launch(&h->g, p);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipHostFree(h->u0_pinned);
@@ -704,7 +711,7 @@ mppi_status mppi_step_noalloc(const mppi_params* p, const float* obstacles_dev, 
     if (st != MPPI_OK) return st;
 
     Geometry g = geometry(p);
-    if (flat_pays(g, p)) set_flat(&g, p);
+    set_two_launch(&g, p);
     int n_tail = 0, n_warm = 0;
     derived_counts(p, &n_tail, &n_warm);
     ramppi::StepConst c;

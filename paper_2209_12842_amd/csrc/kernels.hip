@@ -42,7 +42,7 @@ __device__ __forceinline__ void rollout_launch_body(const RolloutArgs& a) {
     extern __shared__ float2 smem[];
     const int item = kFuse ? (int)blockIdx.x : rollout_item(a.c);
     if (!kFuse && a.clear && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0u;  // the update launch follows
-    rollout_body<kNoise>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
+    rollout_body<kNoise, false, !kFuse>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
     if constexpr (kFuse) {
         __shared__ float red[16];
         __shared__ int flag_sh;

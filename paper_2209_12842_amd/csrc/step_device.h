@@ -292,12 +292,14 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
 //    instructions: moved off the chain, the nominal rollouts of K = 2048,
 //    T = 50, M = 64 end at 27 us of the launch instead of 35 us and no longer
 //    finish last (step 37.2 -> 33.4 us with RolloutLate).
-//  - served steps whose grid would not be resident at once with that many
-//    workgroups (nom_groups > 1): each of the first nom_groups waves draws the
-//    controls of 64 samples of its own and rolls them out (K = 3900, T = 50,
+//  - nom_groups > 1 (kOwn): each of the first nom_groups waves draws the
+//    controls of 64 samples of its own and rolls them out.  For served steps
+//    whose grid would not be resident at once otherwise (K = 3900, T = 50,
 //    M = 64: served step 64.1 us; the groups one after the other in the first
-//    form 68.2).
-template <bool kServe, class Late>
+//    form 68.2), and for two-launch steps of one or two draws, where the
+//    nominal rollouts are as much work as the others and three waves out of
+//    four would wait (K = 200000, T = 20, M = 1: 82.4 -> 77.0 us).
+template <bool kServe, bool kOwn, class Late>
 __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float* __restrict__ V,
                                                  float2* __restrict__ u_out, int item, float2* smem,
                                                  const float4* otab, const float4* gbox, int n_grp, int& n_cand,
@@ -308,7 +310,7 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n_waves = (int)blockDim.x >> 6;  // at least 3 (spb M > 128)
     const int n_runs = (T + kCullSteps - 1) / kCullSteps;
-    const bool own = kServe && c.nom_groups > 1;
+    const bool own = kOwn && c.nom_groups > 1;
     const int k0 = (item * c.nom_groups + (own ? wave : 0)) * 64;
     const bool rolls = own ? wave < c.nom_groups && k0 < c.K : wave == 0;
     const int k = k0 + lane;
@@ -406,7 +408,7 @@ __device__ __forceinline__ void count_work(unsigned long long* work, int item, i
 // nominal workgroup (one lane per sample), otherwise a disturbed workgroup
 // (spb samples of M lanes).  Ends with every lane past its last LDS access
 // (the caller may reuse the LDS after a barrier).
-template <int kNoise, bool kServe = false, class Late>
+template <int kNoise, bool kServe = false, bool kOwn = kServe, class Late>
 __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __restrict__ obs,
                                              const float* __restrict__ V, float2* __restrict__ u_out, int item,
                                              float2* smem, Late late) {
@@ -422,7 +424,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     int n_gtest = 0;  // broad-phase group tests of this wave (wave-uniform)
 
     if (item < c.n_nom_wg) {
-        nominal_rollouts<kServe>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
+        nominal_rollouts<kServe, kOwn>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
         count_work(late().work, item, n_cand, n_gtest);
         return;
     }

@@ -29,18 +29,25 @@ def launches(K, M, per_cu):
     V = mem(8 * p.T)
     fake_hip.fake.fake_reset(-1)
     R.check(L.mppi_step(h, x0, V, 0, None, None))
-    step = [k for k, *_ in fake_hip.launches()]
+    ran = fake_hip.launches()
+    step = [k for k, *_ in ran]
     fake_hip.fake.fake_reset(-1)
     status = L.mppi_serve_start(h, V, 100, None)
     serve = fake_hip.launches()
     assert (status == 0) == (len(serve) == 1) and (status in (0, -4))
     L.mppi_destroy(h)
-    return [step, serve[0][1] if serve else None, serve[0][3] if serve else 0]
+    return [step, serve[0][1] if serve else None, serve[0][3] if serve else 0, ran[0][1]]
 
 
 @pytest.mark.parametrize("K,M,per_cu", list(CASES))
 def test_forms(K, M, per_cu):
-    step, grid, lds = fake_hip.run("test_nominal_forms_cpu", "launches(%d, %d, %d)" % (K, M, per_cu))
+    step, grid, lds, _ = fake_hip.run("test_nominal_forms_cpu", "launches(%d, %d, %d)" % (K, M, per_cu))
     assert step == CASES[(K, M, per_cu)][0]
     assert grid == CASES[(K, M, per_cu)][1]
     assert lds <= 64 * 1024
+
+
+@pytest.mark.parametrize("K,M,grid", [(200000, 1, 782 + 782), (80001, 2, 626 + 313), (100000, 3, 1177 + 1563)])
+def test_few_draws_pack_their_nominal_workgroups(K, M, grid):
+    step, _, _, got = fake_hip.run("test_nominal_forms_cpu", "launches(%d, %d, 4)" % (K, M))
+    assert step == TWO and got == grid

@@ -1,6 +1,7 @@
-"""Served steps whose nominal workgroups are packed, a wave for each 64 samples
-(grids that would not be resident with one workgroup for each), bit for bit
-against launched steps, which take two launches at these sizes."""
+"""Packed nominal workgroups, a wave for each 64 samples: served steps whose
+grid would not be resident with one workgroup for each, bit for bit against
+launched steps, which take two launches at these sizes; and two-launch steps of
+one or two draws against the one-launch form."""
 import numpy as np
 import pytest
 
@@ -34,6 +35,26 @@ def test_packed_sessions_follow_launched_steps(world, kw):
         keys = ("S", "cvar", "S_tilde") + (("u", "L", "w_hat") if debug else ())
         out.append(dict({k: v.cpu().numpy().copy() for k, v in c.debug().items() if k in keys},
                         V=V.cpu().numpy().copy(), cmd=np.stack(u)))
+        c.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("world,kw", [("c2", dict(K=1, T=1, M=1)), ("c2", dict(K=65, T=5, M=2)), ("p0", dict(K=256, T=6, M=1)),
+                                      ("c2", dict(K=257, T=13, M=2, n_obs=70)), ("p0", dict(K=3000, T=18, M=2, noise_kind=1))])
+def test_packed_two_launch_steps(world, kw):
+    import paper_2209_12842_amd as ra
+    from paper_2209_12842_amd import workloads as W
+    w = W.make_world(world, lam=50.0, **kw)
+    V0 = W.random_V(int(w["params"]["T"]), 3)
+    out = []
+    for split in (False, True):
+        c = ra.Controller(w["params"], w["obstacles"], debug=True, split_update=split)
+        V = c.new_V(V0)
+        u0 = c.step(w["x0"], V, 5)
+        torch.cuda.synchronize()
+        out.append(dict({k: v.cpu().numpy().copy() for k, v in c.debug().items()}, V=V.cpu().numpy().copy(), cmd=u0.copy()))
         c.close()
     for k in out[0]:
         assert np.array_equal(out[0][k], out[1][k]), k
