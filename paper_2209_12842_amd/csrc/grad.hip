@@ -95,11 +95,14 @@ enum {
     kFc4 = kFda, kFc3 = kFkap, kFgx = kFp2, kFgy = kFp3, kFc5 = kFp0, kFgw = kFq0, kFgd = kFp1, kFc1 = kFpsi,
     kFc2 = kFv, kFlw = kFq1, kFlz = kFq2
 };
-// Largest grid of the row-by-time form, eight workgroups per compute unit;
-// more rows than that fill the device with one lane each (T = 50, whole
-// gradient: 8.8 thousand rows 74 us here, 85 us by lanes; 17 thousand 107 us
-// either way; 33 thousand 131 us here, 112 us by lanes).
-constexpr int kTimeGrid = 2048;
+// Largest grid of the row-by-time form for horizons of T steps; more rows than
+// that fill the device with one lane each.  What a workgroup does besides its
+// chains costs as much as a chain of some eight steps per row (whole gradient
+// by time and by lanes: T = 5 26.2 and 24.3 us at 500 rows; T = 10 27.1 and
+// 28.0, 35.5 and 36.4 at 8 thousand, 47.6 and 42.5 at 16; T = 20 30.1 and
+// 35.8, 40.7 and 46.6, 54.6 and 53.0; T = 50 40.5 and 61.9, 55.1 and 74.2,
+// 75.5 and 82.2, at 24 thousand 88.7 and 84.5).
+__host__ __device__ constexpr int time_grid(int T) { return T < 8 ? 0 : T < 25 ? 1024 : 2048; }
 
 template <int kNoise>
 __device__ __forceinline__ void grad_rows_by_time(const StepConst& c, const GradArgs& a, int n_rows) {
@@ -287,12 +290,7 @@ __device__ __forceinline__ void grad_rows_by_time(const StepConst& c, const Grad
 constexpr int kGradAhead = 4;
 
 template <int kNoise>
-__global__ void __launch_bounds__(256) k_grad_rollouts(StepConst c, GradArgs a) {
-    const int n_rows = *a.n_act * a.R;
-    if (n_rows <= kTimeRows * kTimeGrid) {
-        grad_rows_by_time<kNoise>(c, a, n_rows);
-        return;
-    }
+__device__ __forceinline__ void grad_rows_by_lane(const StepConst& c, const GradArgs& a, int n_rows) {
     const int l = blockIdx.x * 256 + threadIdx.x;
     if (l >= n_rows) return;  // no barrier below
     const int T = c.T, K = c.K;
@@ -396,6 +394,49 @@ __global__ void __launch_bounds__(256) k_grad_rollouts(StepConst c, GradArgs a) 
     }
 }
 
+// The form of the rows.  Where the horizon or the largest number of rows leaves
+// one only, its kernel holds no code of the other (T = 5, 18 thousand rows by
+// lanes: 8.5 us from a kernel of both, 7.6 alone).
+enum { kRowsByTime, kRowsByLane, kRowsEither };
+
+struct GradLaunch {
+    StepConst c;
+    GradArgs a;
+};
+
+__device__ __forceinline__ GradArgs global_view(const GradArgs& a) {
+    GradArgs g = a;
+    g.V = as_global(a.V);
+    g.u = as_global(a.u);
+    g.cvar = as_global(a.cvar);
+    g.w_hat = as_global(a.w_hat);
+    g.act_list = as_global(a.act_list);
+    g.n_act = as_global(a.n_act);
+    g.tail_idx = as_global(a.tail_idx);
+    g.ranks = as_global(a.ranks);
+    g.states = as_global(a.states);
+    g.rows = as_global(a.rows);
+    return g;
+}
+
+template <int kNoise, int kForm>
+__global__ void __launch_bounds__(256) k_grad_rollouts(GradLaunch g) {
+    const int n_rows = *g.a.n_act * g.a.R;
+    if constexpr (kForm == kRowsByTime) {
+        grad_rows_by_time<kNoise>(g.c, g.a, n_rows);
+    } else if constexpr (kForm == kRowsByLane) {
+        grad_rows_by_lane<kNoise>(g.c, g.a, n_rows);
+    } else {
+        // each form reads the arguments again, as in RolloutLate: read once
+        // for both they filled the scalar registers and spilled
+        const GradLaunch* e = late_ptr<GradLaunch>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+        if (n_rows <= kTimeRows * time_grid(e->c.T))
+            grad_rows_by_time<kNoise>(e->c, global_view(e->a), n_rows);
+        else
+            grad_rows_by_lane<kNoise>(e->c, global_view(e->a), n_rows);
+    }
+}
+
 // Sum of the gradient rows: output q in workgroups (q, 0), (q, 1), ...  The
 // rows are added in blocks of 256 (lane i of a wave adds rows i, i + 64,
 // i + 128, i + 192 of a block, then the wave adds its lanes), each wave taking
@@ -473,6 +514,18 @@ __global__ void __launch_bounds__(256) k_update_grad(StepConst c, int G, int par
                 red, &is_last, &go);
 }
 
+template <int kForm>
+static hipError_t launch_grad_rollouts(const StepConst& c, const GradArgs& a, int grid, hipStream_t stream) {
+    const GradLaunch g{c, a};
+    if (c.noise_kind == 1)
+        hipLaunchKernelGGL((k_grad_rollouts<1, kForm>), dim3(grid), dim3(256), 0, stream, g);
+    else if (c.noise_kind == 2)
+        hipLaunchKernelGGL((k_grad_rollouts<2, kForm>), dim3(grid), dim3(256), 0, stream, g);
+    else
+        hipLaunchKernelGGL((k_grad_rollouts<0, kForm>), dim3(grid), dim3(256), 0, stream, g);
+    return hipGetLastError();
+}
+
 hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs& a, const GradOut& go, int block,
                        size_t lds_rollout, int G, size_t lds_update, int n_lane_blocks, hipStream_t stream) {
     const int n_dist_wg = (c.K + c.spb - 1) / c.spb;
@@ -482,15 +535,12 @@ hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs&
                        b.u, b.S_tilde, b.part, b.counter, b.w_hat, go);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int n_time = (int)std::min<int64_t>(kTimeGrid, ((int64_t)c.K * a.R + kTimeRows - 1) / kTimeRows);
-    const dim3 grid(std::max(n_lane_blocks, n_time));
-    if (c.noise_kind == 1)
-        hipLaunchKernelGGL(k_grad_rollouts<1>, grid, dim3(256), 0, stream, c, a);
-    else if (c.noise_kind == 2)
-        hipLaunchKernelGGL(k_grad_rollouts<2>, grid, dim3(256), 0, stream, c, a);
-    else
-        hipLaunchKernelGGL(k_grad_rollouts<0>, grid, dim3(256), 0, stream, c, a);
-    e = hipGetLastError();
+    const int64_t max_rows = (int64_t)c.K * a.R;
+    const int n_time = (int)std::min<int64_t>(time_grid(c.T), (max_rows + kTimeRows - 1) / kTimeRows);
+    e = n_time == 0 ? launch_grad_rollouts<kRowsByLane>(c, a, n_lane_blocks, stream)
+        : max_rows <= (int64_t)kTimeRows * n_time
+            ? launch_grad_rollouts<kRowsByTime>(c, a, n_time, stream)
+            : launch_grad_rollouts<kRowsEither>(c, a, std::max(n_lane_blocks, n_time), stream);
     if (e != hipSuccess) return e;
     const int split = std::min(16, (n_lane_blocks + kReduceBlocks - 1) / kReduceBlocks);
     hipLaunchKernelGGL(k_grad_reduce, dim3(2 * c.T, split), dim3(256), 0, stream, a);
