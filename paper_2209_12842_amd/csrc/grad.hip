@@ -440,49 +440,60 @@ __global__ void __launch_bounds__(256) k_grad_rollouts(GradLaunch g) {
 // Sum of the gradient rows: output q in workgroups (q, 0), (q, 1), ...  The
 // rows are added in blocks of 256 (lane i of a wave adds rows i, i + 64,
 // i + 128, i + 192 of a block, then the wave adds its lanes), each wave taking
-// every fourth block of its workgroup's, and one thread adds the block sums
+// every n-th block of its workgroup's n waves, and one wave adds the block sums
 // in block order.  Up to kReduceBlocks blocks one workgroup does it all, its
 // block sums in LDS; more blocks are split over the workgroups of the output,
-// which hand their sums over in memory to the last of them.  (A workgroup per
-// block of rows, its waves going through the outputs one by one, waited on
-// memory once per output: 8.5 us for a few rows and 17 us for 17 thousand at
-// T = 50, now 4.6 and 5.)
+// which hand their sums over in memory to the last of them.  Bound by the trips
+// to memory, for rows that other XCDs wrote: with as many waves as a workgroup
+// can have its loads are one trip, and so are the sums of up to 1024 blocks (134
+// thousand rows at T = 5 8.0 us, 16 thousand at T = 9 4.4; with four waves, 64
+// sums a trip, each added from the lane that held it, 34 and 13).
 constexpr int kReduceAhead = 4;   // blocks whose loads a wave has in flight
 constexpr int kReduceBlocks = 64;  // block sums of one workgroup
 
-__global__ void __launch_bounds__(256) k_grad_reduce(GradArgs a) {
-    __shared__ float sums[kReduceBlocks];
+__global__ void __launch_bounds__(1024) k_grad_reduce(GradArgs a) {
+    __shared__ float sums[1024];
     __shared__ int flag_sh;
     const int n_rows = *a.n_act * a.R;
     const int nb = max(1, (n_rows + 255) / 256);
     const int q = blockIdx.x, tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
+    const int lane = tid & 63, wv = tid >> 6, n_waves = (int)blockDim.x >> 6;
     const float* rq = a.rows + (size_t)q * a.stride;
+    if (nb == 1) {
+        if (wv != 0 || blockIdx.y != 0) return;
+        float acc = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc += lane + 64 * j < n_rows ? rq[lane + 64 * j] : 0.0f;
+        acc = wave_sum(acc);
+        if (lane == 0) a.grad_out[q] = acc;
+        return;
+    }
     const bool alone = nb <= kReduceBlocks;
     const int per = alone ? nb : (nb + (int)gridDim.y - 1) / (int)gridDim.y;
     const int b0 = (int)blockIdx.y * per, b1 = min(nb, b0 + per);
     if (b0 >= b1) return;  // uniform
     float* part = a.rpart + (size_t)q * a.n_blocks;
-    for (int b = b0 + wv; b < b1; b += 4 * kReduceAhead) {
+    for (int b = b0 + wv; b < b1; b += n_waves * kReduceAhead) {
         float r[kReduceAhead][4];
 #pragma unroll
         for (int i = 0; i < kReduceAhead; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int l = (b + 4 * i) * 256 + lane + 64 * j;
-                r[i][j] = (b + 4 * i < b1 && l < n_rows) ? rq[l] : 0.0f;
+                const int bi = b + n_waves * i, l = bi * 256 + lane + 64 * j;
+                r[i][j] = (bi < b1 && l < n_rows) ? rq[l] : 0.0f;
             }
 #pragma unroll
         for (int i = 0; i < kReduceAhead; ++i) {
+            const int bi = b + n_waves * i;
             float acc = 0.0f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc += r[i][j];
             acc = wave_sum(acc);
-            if (lane == 0 && b + 4 * i < b1) {
+            if (lane == 0 && bi < b1) {
                 if (alone)
-                    sums[b + 4 * i] = acc;
+                    sums[bi] = acc;
                 else
-                    agent_store(&part[b + 4 * i], acc);
+                    agent_store(&part[bi], acc);
             }
         }
     }
@@ -492,15 +503,27 @@ __global__ void __launch_bounds__(256) k_grad_reduce(GradArgs a) {
         // the workgroups of this output that hold blocks
         if (!arrive_last(&a.counter[q], (unsigned)((nb + per - 1) / per), &flag_sh)) return;
     }
-    // one wave adds the block sums in order, 64 of them at a time from its lanes
-    if (wv != 0) return;
+    // one wave adds the block sums in order, eight loads in flight
     float total = 0.0f;
-    for (int s0 = 0; s0 < nb; s0 += 64) {
-        const float x = s0 + lane < nb ? (alone ? sums[lane] : agent_load(&part[s0 + lane])) : 0.0f;
-        const int n = min(64, nb - s0);
-        for (int i = 0; i < n; ++i) total += lane_f32(x, i);
+    for (int c0 = 0; c0 < nb; c0 += (int)blockDim.x) {
+        const int nc = min((int)blockDim.x, nb - c0);
+        if (!alone) {
+            __syncthreads();  // the last part's sums are read
+            if (tid < nc) sums[tid] = agent_load(&part[c0 + tid]);
+            __syncthreads();
+        }
+        if (wv != 0) continue;
+        int i = 0;
+        for (; i + 8 <= nc; i += 8) {
+            float t[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) t[j] = sums[i + j];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) total += t[j];
+        }
+        for (; i < nc; ++i) total += sums[i];
     }
-    if (lane == 0) a.grad_out[q] = nb == 1 ? sums[0] : total;
+    if (tid == 0) a.grad_out[q] = total;
 }
 
 __global__ void __launch_bounds__(256) k_update_grad(StepConst c, int G, int parts, const float* __restrict__ S,
@@ -543,7 +566,10 @@ hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs&
             : launch_grad_rollouts<kRowsEither>(c, a, std::max(n_lane_blocks, n_time), stream);
     if (e != hipSuccess) return e;
     const int split = std::min(16, (n_lane_blocks + kReduceBlocks - 1) / kReduceBlocks);
-    hipLaunchKernelGGL(k_grad_reduce, dim3(2 * c.T, split), dim3(256), 0, stream, a);
+    // enough waves for a workgroup's share of the most rows there can be
+    const int share = (n_lane_blocks + split - 1) / split;
+    const int waves = std::max(4, std::min(16, (share + kReduceAhead - 1) / kReduceAhead));
+    hipLaunchKernelGGL(k_grad_reduce, dim3(2 * c.T, split), dim3(64 * waves), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""The gradient around the horizons (7, 8, 24, 25 steps) and row counts at which
-its form changes, against the FP64 oracle (worlds without jumps and tolerances
+"""The gradient around the horizons (7, 8, 24, 25 steps), row counts and sample
+counts at which its form changes, against the FP64 oracle (worlds without jumps and tolerances
 as in test_grad_forms_gpu)."""
 import numpy as np
 import pytest
@@ -12,7 +12,9 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("K,M,T", [(30, 8, 7), (30, 8, 8), (910, 8, 8), (911, 8, 8), (910, 8, 24), (911, 8, 24), (911, 8, 25),
-                                   (1820, 8, 25), (1821, 8, 25)])
+                                   (1820, 8, 25), (1821, 8, 25),
+                                   # one block of 256 rows, two, 64, 65, and more than 1024
+                                   (28, 8, 9), (29, 8, 9), (1820, 8, 3), (1821, 8, 3), (32768, 8, 3)])
 def test_gradient_around_its_lines(K, M, T):
     import paper_2209_12842_amd as R
     w = W.make_world("c2", K=K, M=M, T=T, n_obs=0, lam=500.0, alpha=0.001, B=2.0, C_u=-1.0e9)
