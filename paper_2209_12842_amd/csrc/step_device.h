@@ -816,7 +816,7 @@ __device__ __forceinline__ float* update_chunk(const StepConst& c, int b, int pa
 __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, float Z, float invZ, const float* vp,
                                              const float* S_tilde, float* __restrict__ V, float* __restrict__ u0,
                                              float* __restrict__ u0_host, float* __restrict__ w_hat,
-                                             float* ush_free, const GradOut* go) {
+                                             float* ush, const float* w_only, const GradOut* go) {
     const int T = c.T, K = c.K;
     const int tid = threadIdx.x, nt = blockDim.x;
     __syncthreads();
@@ -831,23 +831,29 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
         // up in sample order, and every non-zero sample goes to its place.
         // (A contiguous run of samples per thread waits on memory for each
         // of them, twice: K = 4096, the whole update 15.2 us, now 11.0.)
+        // The only chunk's weights are still in LDS (w_only): they are those
+        // of the merge, its minimum being beta.
         constexpr int kTile = 16;
-        int* cnt_sh = reinterpret_cast<int*>(ush_free);  // 4 kTile counts, then their exclusive sums
+        int* cnt_sh = reinterpret_cast<int*>(ush + 256);  // 4 kTile counts, then their exclusive sums
         const int lane = tid & 63, wv = tid >> 6;
         int total = 0;
         for (int base = 0; base < K; base += 256 * kTile) {
+            const int nj = min(kTile, (K - base + 255) >> 8);  // rows of the tile that hold samples
             float st[kTile];
+            if (!w_only) {
 #pragma unroll
-            for (int j = 0; j < kTile; ++j) {
-                const int k = base + 256 * j + tid;
-                st[j] = k < K ? agent_load(&S_tilde[k]) : __builtin_inff();  // no weight past the end
+                for (int j = 0; j < kTile; ++j) {
+                    const int k = base + 256 * j + tid;
+                    st[j] = k < K ? agent_load(&S_tilde[k]) : __builtin_inff();  // no weight past the end
+                }
             }
             uint32_t nz = 0;
             int before[kTile];
 #pragma unroll
             for (int j = 0; j < kTile; ++j) {
+                if (j >= nj) break;  // uniform
                 const int k = base + 256 * j + tid;
-                const float wk = expf(-(st[j] - beta) / c.lambda) * invZ;
+                const float wk = (w_only ? w_only[tid] : expf(-(st[j] - beta) / c.lambda)) * invZ;
                 const bool on = k < K && wk > 0.0f;
                 if (k < K) w_hat[k] = wk;
                 const uint64_t bal = __builtin_amdgcn_ballot_w64(on);
@@ -857,8 +863,8 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
                 if (lane == 0) cnt_sh[4 * j + wv] = __builtin_popcountll(bal);
             }
             __syncthreads();
-            if (tid < 64) {  // 4 kTile = 64 counts in sample order
-                const int own = cnt_sh[lane];
+            if (tid < 64) {  // up to 4 kTile = 64 counts in sample order
+                const int own = lane < 4 * nj ? cnt_sh[lane] : 0;
                 int incl = own;
                 for (int d = 1; d < 64; d <<= 1) {
                     const int o = __shfl_up(incl, d);
@@ -869,8 +875,10 @@ __device__ __forceinline__ void merge_finish(const StepConst& c, float beta, flo
             }
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < kTile; ++j)
+            for (int j = 0; j < kTile; ++j) {
+                if (j >= nj) break;
                 if (nz & (1u << j)) go->act_list[total + cnt_sh[4 * j + wv] + before[j]] = base + 256 * j + tid;
+            }
             total += cnt_sh[64];
             __syncthreads();  // cnt_sh is refilled
         }
@@ -1011,7 +1019,7 @@ __device__ __forceinline__ void update_merge(const StepConst& c, int G, const fl
         }
         vp[j] = acc * invZ;
     }
-    merge_finish(c, beta, Z, invZ, vp, S_tilde, V, u0, u0_host, w_hat, ush, go);
+    merge_finish(c, beta, Z, invZ, vp, S_tilde, V, u0, u0_host, w_hat, ush, nullptr, go);
 }
 
 // The merge when there is one chunk (K <= 256), run by the workgroup that
@@ -1027,8 +1035,8 @@ __device__ __forceinline__ void update_merge_single(const StepConst& c, float* n
     const float Z = red[1];
     const float invZ = 1.0f / Z;
     for (int j = threadIdx.x; j < 2 * c.T; j += blockDim.x) nb[j] *= invZ;
-    if (c.debug || go) stores_done();  // S~, read back below by other waves of this workgroup
-    merge_finish(c, beta, Z, invZ, nb, S_tilde, V, u0, u0_host, w_hat, ush, go);
+    if (c.debug) stores_done();  // S~, read back below by other waves of this workgroup
+    merge_finish(c, beta, Z, invZ, nb, S_tilde, V, u0, u0_host, w_hat, ush, ush, go);
 }
 
 // Counts the workgroup in at a device-scope counter, after every wave's

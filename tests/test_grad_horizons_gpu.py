@@ -14,7 +14,9 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("K,M,T", [(30, 8, 7), (30, 8, 8), (910, 8, 8), (911, 8, 8), (910, 8, 24), (911, 8, 24), (911, 8, 25),
                                    (1820, 8, 25), (1821, 8, 25),
                                    # one block of 256 rows, two, 64, 65, and more than 1024
-                                   (28, 8, 9), (29, 8, 9), (1820, 8, 3), (1821, 8, 3), (32768, 8, 3)])
+                                   (28, 8, 9), (29, 8, 9), (1820, 8, 3), (1821, 8, 3), (32768, 8, 3),
+                                   # one chunk of samples, two, sixteen, seventeen
+                                   (256, 4, 8), (257, 4, 8), (4096, 4, 2), (4097, 4, 2)])
 def test_gradient_around_its_lines(K, M, T):
     import paper_2209_12842_amd as R
     w = W.make_world("c2", K=K, M=M, T=T, n_obs=0, lam=500.0, alpha=0.001, B=2.0, C_u=-1.0e9)
