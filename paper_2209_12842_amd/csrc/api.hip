@@ -757,26 +757,38 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
     if (p.flags & MPPI_F_SPLIT_UPDATE)
         return fail(MPPI_EUNSUPPORTED, "the step does not run as one launch, so it cannot be served");
     // the nominal form of the one-launch step, or where that grid cannot be
-    // resident at once, the one of fewer workgroups
+    // resident at once, the one of fewer workgroups; in either, the mean
+    // sequence in LDS if its room costs neither the limit nor the residence
+    // (read from memory for every control, a served step of K = 32000, T = 50,
+    // M = 4 took 71 us, now 55)
     Geometry g = geometry(&p);
+    size_t lds = 0;
+    int mean_off = 0;
     for (int form = 0;; ++form) {
-        if (form == 1) set_nominal_packed(&g, &p);
+        if (form == 2) set_nominal_packed(&g, &p);
+        const size_t step_lds = (std::max(g.lds_rollout, g.lds_update) + 15) / 16 * 16;
+        const size_t mean_lds = form % 2 == 0 ? 8 * (size_t)p.T : 0;
+        if (mean_lds && step_lds + mean_lds > kMaxLdsBytes) continue;
         int per_cu = 0, n_cu = 0;
-        hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, std::max(g.lds_rollout, g.lds_update), &per_cu);
+        hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, step_lds + mean_lds, &per_cu);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device);
         if (e != hipSuccess) return hip_fail(e, "serving occupancy");
-        if (one_launch_grid(g, p.K) <= (int64_t)per_cu * n_cu) break;
-        if (form == 1)
+        if (one_launch_grid(g, p.K) <= (int64_t)per_cu * n_cu) {
+            lds = step_lds + mean_lds;
+            mean_off = mean_lds ? (int)(step_lds / 4) : 0;
+            break;
+        }
+        if (form == 3)
             return fail(MPPI_EUNSUPPORTED, "the serving grid (%lld workgroups) cannot be resident at once",
                         (long long)one_launch_grid(g, p.K));
     }
-    const size_t lds = std::max(g.lds_rollout, g.lds_update);
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     ramppi::StepConst c;
     const float x0[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // the per-step fields come with each request
     fill_static(&c, p, g, h->n_tail, h->n_warm);
     fill_dynamic(&c, p, x0, 0);
+    c.mean_off = mean_off;
     ramppi::StepBuffers bufs = step_buffers(h, V_dev);
     char* sv = h->ws + h->l.serve;
     ramppi::ServeArgs sa;

@@ -66,14 +66,14 @@ __device__ __forceinline__ void batch_rollout_item(const BatchCtl* __restrict__ 
         return RolloutLate{&e->c, as_global(e->S), as_global(e->cvar), as_global(e->L), nullptr, nullptr, work};
     };
     if constexpr (kNoise >= 0) {
-        rollout_body<kNoise>(c, obs, V, u, w, bsmem, late);
+        rollout_body<kNoise, false>(c, obs, V, u, w, bsmem, late);
     } else {
         if (c.noise_kind == 1)
-            rollout_body<1>(c, obs, V, u, w, bsmem, late);
+            rollout_body<1, false>(c, obs, V, u, w, bsmem, late);
         else if (c.noise_kind == 2)
-            rollout_body<2>(c, obs, V, u, w, bsmem, late);
+            rollout_body<2, false>(c, obs, V, u, w, bsmem, late);
         else
-            rollout_body<0>(c, obs, V, u, w, bsmem, late);
+            rollout_body<0, false>(c, obs, V, u, w, bsmem, late);
     }
 }
 

@@ -103,6 +103,16 @@ __device__ __forceinline__ float mean_load(const float* p) {
     return *p;
 }
 
+// The mean sequence of a served step as its rollouts read it: from the copy in
+// LDS (`staged`), which each workgroup loads once per step, or where there is
+// no room for one from memory, past the caches, for every control.
+struct ServedMean {
+    const float* V;
+    const float* sh;
+    bool staged;
+    __device__ __forceinline__ float operator[](int i) const { return staged ? sh[i] : agent_load(&V[i]); }
+};
+
 // Waits until this wave's stores have reached the scope they were made at.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -229,6 +239,7 @@ struct StepConst {
     int32_t nom_groups;  // groups of 64 samples per nominal workgroup
     int32_t n_warm;      // samples k < n_warm keep the mean sequence
     int32_t n_tail;      // M - ceil(alpha M) + 1
+    int32_t mean_off;    // served steps: the LDS copy of the mean sequence (floats into the LDS), or 0
     int32_t wave_tails;  // the per-sample layout's CVaR by single waves (cvar_waves)
     float dt, inv_wheelbase;
     float u_lo0, u_lo1, u_hi0, u_hi1;
@@ -599,15 +610,15 @@ __device__ __forceinline__ int obstacle_hits_culled(const float4* __restrict__ o
 
 // Sampled control (Eq. 2b-2c with the warm / zero-mean rule of Algorithm 1):
 // u = clamp(base + sqrt(Sigma_eps) z, u_lo, u_hi), base = v_t for k < n_warm.
-template <bool kServe>
-__device__ __forceinline__ float2 sample_control_from(const StepConst& c, const float* __restrict__ V, int k, int t,
+template <class Mean>
+__device__ __forceinline__ float2 sample_control_from(const StepConst& c, const Mean& V, int k, int t,
                                                      uint4 r, uint32_t exp_word) {
     float z0, z1;
     box_muller(uniform01(r.x, exp_word), uniform01(r.y, exp_word), z0, z1);
     // every lane reads v_t (t < T, in bounds) and warm samples keep it: a
     // select, not a branch
     const bool warm = k < c.n_warm;
-    const float v0 = mean_load<kServe>(&V[2 * t]), v1 = mean_load<kServe>(&V[2 * t + 1]);
+    const float v0 = V[2 * t], v1 = V[2 * t + 1];
     const float b0 = warm ? v0 : 0.0f;
     const float b1 = warm ? v1 : 0.0f;
     float a = __fmaf_rn(c.se0, z0, b0);
@@ -617,10 +628,10 @@ __device__ __forceinline__ float2 sample_control_from(const StepConst& c, const 
     return make_float2(a, d);
 }
 
-template <bool kServe = false>
-__device__ __forceinline__ float2 sample_control(const StepConst& c, const float* __restrict__ V, int k, int t) {
+template <class Mean>
+__device__ __forceinline__ float2 sample_control(const StepConst& c, const Mean& V, int k, int t) {
     const uint4 r = philox4x32_10((uint32_t)t, kCtrlWord, (uint32_t)k, c.step_idx, c.key0, c.key1);
-    return sample_control_from<kServe>(c, V, k, t, r, 0x7Fu);
+    return sample_control_from(c, V, k, t, r, 0x7Fu);
 }
 
 // Angle wrap to (-pi, pi].

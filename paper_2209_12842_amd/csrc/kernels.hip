@@ -42,7 +42,7 @@ __device__ __forceinline__ void rollout_launch_body(const RolloutArgs& a) {
     extern __shared__ float2 smem[];
     const int item = kFuse ? (int)blockIdx.x : rollout_item(a.c);
     if (!kFuse && a.clear && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0u;  // the update launch follows
-    rollout_body<kNoise, false, !kFuse>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
+    rollout_body<kNoise, !kFuse>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
     if constexpr (kFuse) {
         __shared__ float red[16];
         __shared__ int flag_sh;
@@ -108,7 +108,13 @@ __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg)
         c.theta0 = __uint_as_float(serve_value(words, kServeTheta));
         c.psi0 = __uint_as_float(serve_value(words, kServePsi));
         c.v0 = __uint_as_float(serve_value(words, kServeV));
-        rollout_body<kNoise, true>(c, p->obs, p->V, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
+        const ServedMean mean{p->V, reinterpret_cast<const float*>(smem) + c.mean_off, c.mean_off != 0};
+        if (mean.staged) {
+            float* sh = reinterpret_cast<float*>(smem) + c.mean_off;
+            for (int i = threadIdx.x; i < 2 * c.T; i += blockDim.x) sh[i] = agent_load(&p->V[i]);
+            __syncthreads();
+        }
+        rollout_body<kNoise, true>(c, p->obs, mean, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
         const RolloutArgs* e = late_args();
         StepConst ce = e->c;
         ce.step_idx = c.step_idx;

@@ -299,8 +299,8 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
 //    form 68.2), and for two-launch steps of one or two draws, where the
 //    nominal rollouts are as much work as the others and three waves out of
 //    four would wait (K = 200000, T = 20, M = 1: 82.4 -> 77.0 us).
-template <bool kServe, bool kOwn, class Late>
-__device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float* __restrict__ V,
+template <bool kOwn, class Mean, class Late>
+__device__ __forceinline__ void nominal_rollouts(const StepConst& c, const Mean& V,
                                                  float2* __restrict__ u_out, int item, float2* smem,
                                                  const float4* otab, const float4* gbox, int n_grp, int& n_cand,
                                                  int& n_gtest, Late late) {
@@ -323,12 +323,11 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const float
         for (int i = first; i < kCullSteps; i += count) {
             const int t = r * kCullSteps + i;
             if (t >= T) break;  // uniform
-            const float2 u = sample_control<kServe>(c, V, kc, t);
+            const float2 u = sample_control(c, V, kc, t);
             if (c.store_u && act) u_out[(size_t)t * c.K + k] = u;
             reinterpret_cast<float2*>(b)[i * 64 + lane] = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
             b[2 * 64 * kCullSteps + i * 64 + lane] =
-                __fmaf_rn(mean_load<kServe>(&V[2 * t]) * c.inv_var0, u.x,
-                          mean_load<kServe>(&V[2 * t + 1]) * c.inv_var1 * u.y);
+                __fmaf_rn(V[2 * t] * c.inv_var0, u.x, V[2 * t + 1] * c.inv_var1 * u.y);
         }
     };
     if (!own) produce(0, wave, n_waves);
@@ -408,10 +407,9 @@ __device__ __forceinline__ void count_work(unsigned long long* work, int item, i
 // nominal workgroup (one lane per sample), otherwise a disturbed workgroup
 // (spb samples of M lanes).  Ends with every lane past its last LDS access
 // (the caller may reuse the LDS after a barrier).
-template <int kNoise, bool kServe = false, bool kOwn = kServe, class Late>
-__device__ __forceinline__ void rollout_body(const StepConst& c, const float* __restrict__ obs,
-                                             const float* __restrict__ V, float2* __restrict__ u_out, int item,
-                                             float2* smem, Late late) {
+template <int kNoise, bool kOwn, class Mean, class Late>
+__device__ __forceinline__ void rollout_body(const StepConst& c, const float* __restrict__ obs, const Mean& V,
+                                             float2* __restrict__ u_out, int item, float2* smem, Late late) {
     float2* ctl = smem;
     const int tid = threadIdx.x;
     const int spb = c.spb, M = c.M, T = c.T;
@@ -424,7 +422,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     int n_gtest = 0;  // broad-phase group tests of this wave (wave-uniform)
 
     if (item < c.n_nom_wg) {
-        nominal_rollouts<kServe, kOwn>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
+        nominal_rollouts<kOwn>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
         count_work(late().work, item, n_cand, n_gtest);
         return;
     }
@@ -452,7 +450,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
         const int kk = k_first + sl;
         float2 cu = make_float2(0.0f, 0.0f);
         if (kk < c.K) {
-            const float2 u = sample_control<kServe>(c, V, kk, t);
+            const float2 u = sample_control(c, V, kk, t);
             cu = make_float2(c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase);
         }
         ctl[idx] = cu;
