@@ -172,6 +172,16 @@ void set_two_launch(Geometry* g, const mppi_params* p) {
     if (p->M < 3) set_nominal_packed(g, p);
 }
 
+// Serving workgroups of more than four waves that a compute unit starts at
+// once: k_serve holds four waves per SIMD, and one SIMD takes the waves of every
+// workgroup that do not share out evenly.  The occupancy query counts waves over
+// the unit (five-wave workgroups, M = 257 to 320: three, of which two start, and
+// a session of 518 never had its whole grid resident).
+int simd_workgroups(int block) {
+    const int waves = block / 64;
+    return waves > 4 ? std::max(1, 4 / ((waves + 3) / 4)) : 16;
+}
+
 // Integer tail size and warm count, computed in double precision.
 void derived_counts(const mppi_params* p, int* n_tail, int* n_warm) {
     int ka = (int)std::ceil((double)p->alpha * (double)p->M - 1e-9);
@@ -773,6 +783,7 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
         hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, step_lds + mean_lds, &per_cu);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device);
         if (e != hipSuccess) return hip_fail(e, "serving occupancy");
+        per_cu = std::min(per_cu, simd_workgroups(g.block));
         if (one_launch_grid(g, p.K) <= (int64_t)per_cu * n_cu) {
             lds = step_lds + mean_lds;
             mean_off = mean_lds ? (int)(step_lds / 4) : 0;

@@ -9,14 +9,18 @@ import pytest
 import fake_hip
 
 TWO, FLAT = ["k_rollout", "k_update"], ["k_rollout", "k_cvar_wave", "k_update"]
-CASES = {  # (K, M, resident workgroups per unit): the step's kernels, the served grid or None where it is refused
+CASES = {  # (K, M, waves per SIMD): the step's kernels, the served grid or None where it is refused
     (3852, 64, 4): (["k_rollout_fused"], 963 + 61),
     (3855, 64, 4): (TWO, 964 + 16),                   # 964 + 61 is one too many
     (4032, 64, 4): (TWO, 1008 + 16),
     (4033, 64, 4): (TWO, None),
     (14000, 16, 4): (TWO, 875 + 55),
-    (511, 512, 2): (FLAT, 511 + 1),
-    (254, 1024, 1): (["k_rollout", "k_cvar_sorted", "k_update"], 254 + 1),
+    (511, 512, 4): (FLAT, 511 + 1),
+    (504, 300, 4): (["k_rollout_fused"], 504 + 8),   # five waves: two on one SIMD, so two workgroups a unit, not three
+    (510, 300, 4): (["k_rollout_fused"], 510 + 2),
+    (512, 300, 4): (["k_rollout_fused"], None),
+    (2400, 90, 4): (["k_rollout_fused"], 1200 + 38),  # three waves
+    (254, 1024, 4): (["k_rollout", "k_cvar_sorted", "k_update"], 254 + 1),
 }
 
 

@@ -12,6 +12,7 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("world,kw", [("c2", dict(K=3900, T=13, M=64)), ("c2", dict(K=14001, T=6, M=16, noise_kind=1)),
                                       ("c2", dict(K=45000, T=7, M=4)), ("p0", dict(K=4030, T=5, M=60)),
                                       ("c2", dict(K=3999, T=1, M=64, n_obs=0)), ("c2", dict(K=511, T=12, M=512)),
+                                      ("c2", dict(K=510, T=9, M=300)),    # five waves: two workgroups a unit
                                       ("c2", dict(K=3900, T=20, M=64, n_obs=130, debug=True))])
 def test_packed_sessions_follow_launched_steps(world, kw):
     import paper_2209_12842_amd as ra
