@@ -767,10 +767,13 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
     if (p.flags & MPPI_F_SPLIT_UPDATE)
         return fail(MPPI_EUNSUPPORTED, "the step does not run as one launch, so it cannot be served");
     // the nominal form of the one-launch step, or where that grid cannot be
-    // resident at once, the one of fewer workgroups; in either, the mean
-    // sequence in LDS if its room costs neither the limit nor the residence
-    // (read from memory for every control, a served step of K = 32000, T = 50,
-    // M = 4 took 71 us, now 55)
+    // resident at once, the one of fewer workgroups.  The mean sequence is
+    // copied to LDS where reading it from memory for every control costs more
+    // than the copy's own trip: in packed workgroups, whose waves draw and roll
+    // in turn (K = 3900, T = 50, M = 64: 64.2 -> 57.9 us), and from about a
+    // million controls, all from the same few lines (K = 32000, T = 50, M = 4:
+    // 71.4 -> 54.8; K = 15000, T = 60, M = 8 49.9 and 50.1; K = 2048, M = 64
+    // 37.0 and 37.2), if its room costs neither the limit nor the residence
     Geometry g = geometry(&p);
     size_t lds = 0;
     int mean_off = 0;
@@ -778,9 +781,10 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
         if (form == 2) set_nominal_packed(&g, &p);
         const size_t step_lds = (std::max(g.lds_rollout, g.lds_update) + 15) / 16 * 16;
         const size_t mean_lds = form % 2 == 0 ? 8 * (size_t)p.T : 0;
-        if (mean_lds && step_lds + mean_lds > kMaxLdsBytes) continue;
+        if (mean_lds && (step_lds + mean_lds > kMaxLdsBytes || (form == 0 && (int64_t)p.K * p.T < 1000000))) continue;
         int per_cu = 0, n_cu = 0;
-        hipError_t e = ramppi::serve_capacity((int)p.noise_kind, g.block, step_lds + mean_lds, &per_cu);
+        hipError_t e = ramppi::serve_capacity((int)p.noise_kind, mean_lds != 0, g.nom_groups > 1, g.block,
+                                              step_lds + mean_lds, &per_cu);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device);
         if (e != hipSuccess) return hip_fail(e, "serving occupancy");
         per_cu = std::min(per_cu, simd_workgroups(g.block));

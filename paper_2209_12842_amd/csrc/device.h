@@ -103,14 +103,11 @@ __device__ __forceinline__ float mean_load(const float* p) {
     return *p;
 }
 
-// The mean sequence of a served step as its rollouts read it: from the copy in
-// LDS (`staged`), which each workgroup loads once per step, or where there is
-// no room for one from memory, past the caches, for every control.
+// The mean sequence of a served step as its rollouts read it where the step
+// has no copy of it in LDS: from memory, past the caches, for every control.
 struct ServedMean {
     const float* V;
-    const float* sh;
-    bool staged;
-    __device__ __forceinline__ float operator[](int i) const { return staged ? sh[i] : agent_load(&V[i]); }
+    __device__ __forceinline__ float operator[](int i) const { return agent_load(&V[i]); }
 };
 
 // Waits until this wave's stores have reached the scope they were made at.
@@ -239,7 +236,7 @@ struct StepConst {
     int32_t nom_groups;  // groups of 64 samples per nominal workgroup
     int32_t n_warm;      // samples k < n_warm keep the mean sequence
     int32_t n_tail;      // M - ceil(alpha M) + 1
-    int32_t mean_off;    // served steps: the LDS copy of the mean sequence (floats into the LDS), or 0
+    int32_t mean_off;    // served steps: the LDS copy of the mean sequence (floats into the LDS), or 0: none
     int32_t wave_tails;  // the per-sample layout's CVaR by single waves (cvar_waves)
     float dt, inv_wheelbase;
     float u_lo0, u_lo1, u_hi0, u_hi1;

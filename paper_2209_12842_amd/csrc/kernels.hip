@@ -78,7 +78,10 @@ __global__ void __launch_bounds__(1024) k_rollout_fused(RolloutArgs a) {
 // request (steps 1, 2, ... of the session).  The first wave of workgroup 0
 // takes the requests from host memory; the others wait on its device copy.
 // Every wait is bounded, so every wave leaves even if no request comes.
-template <int kNoise>
+// kMeanLds: every workgroup copies the mean sequence to LDS at c.mean_off.
+// kOwn: the nominal workgroups may be packed (code that the others do without:
+// K = 1500, T = 30, M = 100 34.0 -> 33.7 us).
+template <int kNoise, bool kMeanLds, bool kOwn>
 __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg) {
     extern __shared__ float2 smem[];
     const ServeArgs sa = global_view(sa_arg);
@@ -108,13 +111,15 @@ __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg)
         c.theta0 = __uint_as_float(serve_value(words, kServeTheta));
         c.psi0 = __uint_as_float(serve_value(words, kServePsi));
         c.v0 = __uint_as_float(serve_value(words, kServeV));
-        const ServedMean mean{p->V, reinterpret_cast<const float*>(smem) + c.mean_off, c.mean_off != 0};
-        if (mean.staged) {
-            float* sh = reinterpret_cast<float*>(smem) + c.mean_off;
-            for (int i = threadIdx.x; i < 2 * c.T; i += blockDim.x) sh[i] = agent_load(&p->V[i]);
+        const auto late = [] { return late_view(late_args()); };
+        if constexpr (kMeanLds) {
+            float* mean = reinterpret_cast<float*>(smem) + c.mean_off;
+            for (int i = threadIdx.x; i < 2 * c.T; i += blockDim.x) mean[i] = agent_load(&p->V[i]);
             __syncthreads();
+            rollout_body<kNoise, kOwn>(c, p->obs, mean, p->u, blockIdx.x, smem, late);
+        } else {
+            rollout_body<kNoise, kOwn>(c, p->obs, ServedMean{p->V}, p->u, blockIdx.x, smem, late);
         }
-        rollout_body<kNoise, true>(c, p->obs, mean, p->u, blockIdx.x, smem, [] { return late_view(late_args()); });
         const RolloutArgs* e = late_args();
         StepConst ce = e->c;
         ce.step_idx = c.step_idx;
@@ -275,22 +280,31 @@ hipError_t fused_rollout_capacity(int noise_kind, int block, size_t lds, int* bl
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_rollout_fused<0>, block, lds);
 }
 
-hipError_t serve_capacity(int noise_kind, int block, size_t lds, int* blocks_per_cu) {
-    if (noise_kind == 1) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_serve<1>, block, lds);
-    if (noise_kind == 2) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_serve<2>, block, lds);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_serve<0>, block, lds);
+using ServeKernel = void (*)(RolloutArgs, ServeArgs);
+
+template <bool kMeanLds, bool kOwn>
+static ServeKernel serve_kernel_t(int noise_kind) {
+    return noise_kind == 1 ? k_serve<1, kMeanLds, kOwn>
+           : noise_kind == 2 ? k_serve<2, kMeanLds, kOwn>
+                             : k_serve<0, kMeanLds, kOwn>;
+}
+
+static ServeKernel serve_kernel(int noise_kind, bool mean_lds, bool packed) {
+    return mean_lds ? serve_kernel_t<true, true>(noise_kind)
+           : packed ? serve_kernel_t<false, true>(noise_kind)
+                    : serve_kernel_t<false, false>(noise_kind);
+}
+
+hipError_t serve_capacity(int noise_kind, bool mean_lds, bool packed, int block, size_t lds, int* blocks_per_cu) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, serve_kernel(noise_kind, mean_lds, packed), block,
+                                                        lds);
 }
 
 hipError_t launch_serve(const StepConst& c, const StepBuffers& b, int block, size_t lds, const FuseArgs* fa,
                         const ServeArgs& sa, hipStream_t stream) {
     const dim3 grid(c.n_nom_wg + (c.K + c.spb - 1) / c.spb);
-    const RolloutArgs a = rollout_args(c, b, nullptr, nullptr, fa);
-    if (c.noise_kind == 1)
-        hipLaunchKernelGGL(k_serve<1>, grid, dim3(block), lds, stream, a, sa);
-    else if (c.noise_kind == 2)
-        hipLaunchKernelGGL(k_serve<2>, grid, dim3(block), lds, stream, a, sa);
-    else
-        hipLaunchKernelGGL(k_serve<0>, grid, dim3(block), lds, stream, a, sa);
+    hipLaunchKernelGGL(serve_kernel(c.noise_kind, c.mean_off != 0, c.nom_groups > 1), grid, dim3(block), lds, stream,
+                       rollout_args(c, b, nullptr, nullptr, fa), sa);
     return hipGetLastError();
 }
 

@@ -114,7 +114,7 @@ hipError_t launch_rollout(const StepConst& c, const StepBuffers& b, int block, s
 // Workgroups of the one-launch step (rollouts and update) resident per CU.
 hipError_t fused_rollout_capacity(int noise_kind, int block, size_t lds, int* blocks_per_cu);
 // Persistent serving (k_serve): resident workgroups per CU, and the launch.
-hipError_t serve_capacity(int noise_kind, int block, size_t lds, int* blocks_per_cu);
+hipError_t serve_capacity(int noise_kind, bool mean_lds, bool packed, int block, size_t lds, int* blocks_per_cu);
 hipError_t launch_serve(const StepConst& c, const StepBuffers& b, int block, size_t lds, const FuseArgs* fa,
                         const ServeArgs& sa, hipStream_t stream);
 hipError_t launch_grad(const StepConst& c, const StepBuffers& b, const GradArgs& a, const GradOut& go, int block,

@@ -1,5 +1,6 @@
-"""The LDS of a serving launch: the step's and a copy of the mean sequence, or
-the step's alone where both exceed the limit (CPU only)."""
+"""The LDS of a serving launch: with a copy of the mean sequence where a million
+controls read it or the nominal workgroups are packed, and both fit the limit
+(CPU only)."""
 import pytest
 
 import fake_hip
@@ -12,15 +13,19 @@ def lds(K, T, M):
     h = fake_hip.handle(p, obs)
     V = mem(8 * T)
     fake_hip.fake.fake_reset(-1)
-    R.check(L.mppi_step(h, x0, V, 0, None, None))
     R.check(L.mppi_serve_start(h, V, 100, None))
-    got = [(k, n) for k, _, _, n in fake_hip.launches()]
+    (got,) = [n for _, _, _, n in fake_hip.launches()]
     L.mppi_destroy(h)
     return got
 
 
-@pytest.mark.parametrize("K,T,M,copy", [(300, 29, 1, True), (300, 30, 1, False), (2048, 50, 64, True), (40, 3300, 256, False)])
-def test_copy_where_it_fits(K, T, M, copy):
-    (step, n), (serve, m) = fake_hip.run("test_serve_lds_cpu", "lds(%d, %d, %d)" % (K, T, M))
-    assert (step, serve) == ("k_rollout_fused", "k_serve")
-    assert m == (n + 15) // 16 * 16 + (8 * T if copy else 0) <= 64 * 1024
+# step: controls and costs of the workgroup's samples or the nominal buffers, and one group of obstacles
+@pytest.mark.parametrize("K,T,M,step,copy", [
+    (2048, 50, 64, 2 * 4608 + 1024, False),
+    (15625, 64, 8, 4 * (2 * 32 * 64 + 2 * 256 + 32) + 1024, True),       # a million controls
+    (15624, 64, 8, 4 * (2 * 32 * 64 + 2 * 256 + 32) + 1024, False),
+    (3900, 50, 64, 4 * 4608 + 1024, True),                               # packed
+    (34000, 30, 1, 64 * 1024, False),                                    # no room
+])
+def test_copy_where_it_pays_and_fits(K, T, M, step, copy):
+    assert fake_hip.run("test_serve_lds_cpu", "lds(%d, %d, %d)" % (K, T, M)) == step + (8 * T if copy else 0)

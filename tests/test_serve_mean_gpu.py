@@ -7,8 +7,9 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kw", [dict(K=300, T=29, M=1), dict(K=300, T=30, M=1),      # the second: 64 KB without it
-                                dict(K=5000, T=30, M=1), dict(K=64, T=1500, M=64), dict(K=40, T=3300, M=256),
+@pytest.mark.parametrize("kw", [dict(K=300, T=29, M=1), dict(K=300, T=30, M=1),
+                                dict(K=34000, T=30, M=1), dict(K=34500, T=29, M=1),  # 64 KB without the copy; with it
+                                dict(K=15625, T=64, M=8), dict(K=15624, T=64, M=8),  # a million controls dict(K=64, T=1500, M=64), dict(K=40, T=3300, M=256),
                                 dict(K=70, T=1, M=200), dict(K=600, T=130, M=8, lam=500.0)])
 def test_sessions_follow_launched_steps(kw):
     import paper_2209_12842_amd as ra
