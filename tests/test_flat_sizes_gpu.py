@@ -1,0 +1,50 @@
+"""Steps in the flattened layout, every disturbance form and up to 13 samples a
+workgroup, bit for bit against the per-sample layout that a gradient handle
+keeps, and on the caller's memory; sizes at which the flattened layout's LDS
+does not fit take the per-sample one there too."""
+import numpy as np
+import pytest
+
+from flat_cases import FLAT
+from paper_2209_12842_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", FLAT)
+def test_flat_equals_per_sample_layout(kw):
+    import paper_2209_12842_amd as R
+    w = W.make_world("c2", lam=50.0, **kw)
+    V0 = W.random_V(kw["T"], 5)
+    a = R.Controller(w["params"], w["obstacles"])
+    Va = a.new_V(V0)
+    a.step(w["x0"], Va, 9)
+    b = R.Controller(w["params"], w["obstacles"], grad=True)
+    b.free_energy(w["x0"], b.new_V(V0), 9)
+    Vn = a.new_V(V0)
+    R.step_noalloc(w["params"], torch.as_tensor(w["obstacles"]).cuda(), w["x0"], Vn, 9)
+    torch.cuda.synchronize()
+    for k in ("S", "cvar", "S_tilde"):
+        assert torch.equal(a.debug()[k], b.debug()[k]), k
+    assert torch.equal(Va, Vn)
+    a.close()
+    b.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [dict(K=100, T=3500, M=1024), dict(K=100, T=3800, M=300)])
+def test_long_horizons_on_the_callers_memory(kw):
+    import paper_2209_12842_amd as R
+    w = W.make_world("c2", lam=50.0, n_obs=10, **kw)
+    obs = torch.as_tensor(w["obstacles"]).cuda()
+    out = []
+    for split in (False, True):
+        c = R.Controller(w["params"], w["obstacles"], split_update=split)
+        out.append(c.new_V())
+        c.step(w["x0"], out[-1], 2)
+        c.close()
+    out.append(torch.zeros_like(out[0]))
+    R.step_noalloc(w["params"], obs, w["x0"], out[-1], 2)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
