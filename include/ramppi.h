@@ -225,9 +225,9 @@ mppi_status mppi_grad(mppi_handle *h, const float x0[4], const float *V_dev, uin
  * (shifted when MPPI_F_SHIFT) in V_dev, which the session keeps.
  *
  * mppi_serve_start(h, V_dev, idle_ms, stream)
- *   Only for handles whose step runs as one launch (every workgroup
- *   resident at once; MPPI_EUNSUPPORTED otherwise, or when the serving
- *   kernel itself cannot be resident).  The kernel occupies the GPU until
+ *   Only where every workgroup of the serving kernel can be resident at
+ *   once (MPPI_EUNSUPPORTED otherwise, and for handles created with
+ *   MPPI_F_SPLIT_UPDATE).  The kernel occupies the GPU until
  *   mppi_serve_stop, or until no request arrives for idle_ms milliseconds
  *   (1 <= idle_ms <= 60000), when it leaves by itself.  While a session
  *   runs, other work that needs the GPU's compute units waits behind it,
@@ -262,9 +262,10 @@ const char *mppi_last_error(void);
 mppi_status mppi_debug_view(const mppi_handle *h, mppi_debug_ptrs *out);
 
 /* Kernel timing with HIP events recorded on the step's stream around the
- * rollout kernel and around the update kernel.  enable = 1 starts recording
- * (and clears earlier records), enable = 2 resumes recording and keeps
- * them, enable = 0 pauses (records kept), so that a caller can time a
+ * rollout kernel (with the CVaR pass of the flattened layout, or in a one-
+ * launch step with the update) and around the update kernel.  enable = 1
+ * starts recording (and clears earlier records), enable = 2 resumes recording
+ * and keeps them, enable = 0 pauses (records kept), so that a caller can time a
  * sample of its steps; mppi_timing_read waits for the recorded steps,
  * returns the summed milliseconds and the step count, and clears the
  * records.  At most 4096 steps are kept. */
@@ -325,12 +326,12 @@ mppi_status mppi_batch_create(int32_t n, const mppi_params *p, const float *cons
 
 /* One step of every controller: x0_host n x 4 measured states (finite),
  * step_idx_host n call indices, u0_host NULL or n x 2 (first commands before
- * any shift; the call then waits for the step).  The step is three kernels:
- * per-controller set-up, one rollout launch with a workgroup for every item
- * of a (controller, workgroup) list, and one update launch over every
- * controller's chunks (before it, where draw counts leave many lanes of the
- * rollouts idle, a CVaR pass over rollouts laid out without gaps); with the graph on (the default) they are replayed from
- * a HIP graph captured on the first step.  Controller i's results equal those
+ * any shift; the call then waits for the step).  The step is three or four
+ * kernels: per-controller set-up, one rollout launch with a workgroup for
+ * every item of a (controller, workgroup) list, a CVaR pass where draw counts
+ * leave many lanes of the rollouts idle and they are laid out without gaps,
+ * and one update launch over every controller's chunks; with the graph on (the
+ * default) they are replayed from a HIP graph captured on the first step.  Controller i's results equal those
  * of mppi_step with the same parameters and inputs.  Before writing the inputs
  * the call waits for the previous step of this batch. */
 mppi_status mppi_batch_step(mppi_batch *b, const float *x0_host, const uint32_t *step_idx_host,
@@ -346,12 +347,13 @@ mppi_status mppi_batch_autotune(mppi_batch *b, int32_t trials, void *stream, int
 /* enable != 0: replay the step from a HIP graph (the default); 0: launch. */
 mppi_status mppi_batch_set_graph(mppi_batch *b, int enable);
 
-/* Kernel timing of batched steps: while enabled, steps launch their three
- * kernels directly (not from the graph; the kernels are the same) with HIP
- * events on the step's stream around the rollout kernel and
- * around the update kernel.  mppi_batch_timing_read waits for the recorded
- * steps, returns the summed milliseconds and the step count, and clears the
- * records.  At most 4096 steps are kept. */
+/* Kernel timing of batched steps: while enabled, steps launch their three or
+ * four kernels directly (not from the graph; the kernels are the same) with
+ * HIP events on the step's stream around the rollouts, with their CVaR pass
+ * where the batch has one (rollout_ms: the risk costs and their CVaRs in
+ * either layout), and around the update kernel.  mppi_batch_timing_read waits
+ * for the recorded steps, returns the summed milliseconds and the step count,
+ * and clears the records.  At most 4096 steps are kept. */
 mppi_status mppi_batch_timing_enable(mppi_batch *b, int enable);
 mppi_status mppi_batch_timing_read(mppi_batch *b, double *rollout_ms, double *update_ms, int32_t *n_steps);
 /* As mppi_timing_candidates and mppi_timing_work, over the batch's timed steps. */

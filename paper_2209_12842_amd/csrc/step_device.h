@@ -117,8 +117,8 @@ struct RolloutArgs {
 // argument when the kernel begins and keeps in scalar registers, or spilled
 // into vector-register lanes, whatever the end of the kernel uses; read again
 // through a pointer it cannot see through (late_ptr), these values need no
-// register while the rollouts run (scalar spills of the one-launch kernel
-// 118 -> 69, of k_serve 188 -> 91).
+// register while the rollouts run (with the nominal rollouts as they are now,
+// scalar spills of the one-launch kernel 94 -> 57, of k_serve 164 -> 68).
 struct RolloutLate {
     const StepConst* c;
     float* S;
@@ -432,8 +432,7 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     // the issue slots first: there are M of them per sample against one
     // nominal lane per sample.  On the receding-horizon workload (K = 2048,
     // M = 64) this order gave the shortest one-launch step of the three
-    // (equal priorities and nominal first were 2.7 us slower), although its
-    // nominal waves then finish a few microseconds after the disturbed ones.
+    // (equal priorities and nominal first were 2.7 us slower).
     __builtin_amdgcn_s_setprio(2);
     const int wg = item - c.n_nom_wg;
     // The workgroup's samples: spb of them, or with c.flat the (at most spb)
