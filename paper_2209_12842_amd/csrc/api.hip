@@ -37,6 +37,7 @@ mppi_status hip_fail(hipError_t e, const char* what) {
 constexpr size_t kAlign = 256;
 constexpr int kPartBlock = 256;           // samples per weight chunk
 constexpr size_t kMaxLdsBytes = 64 * 1024;  // per workgroup
+constexpr size_t kMaxLdsPerCu = 160 * 1024;
 constexpr int kMaxK = 1 << 20;
 constexpr int kMaxTimedSteps = 4096;
 
@@ -165,12 +166,24 @@ void set_nominal_packed(Geometry* g, const mppi_params* p) {
     if (packed.lds_rollout <= kMaxLdsBytes) *g = packed;
 }
 
-// The layout of a two-launch step: flattened or not; packed nominal workgroups
-// for one or two draws (K = 73773, T = 56, M = 2, boundary cost: 95.4 -> 92.1
-// us), not for three (K = 100000, T = 40, M = 3: 77.7, packed 83.3).
+// Rounds of workgroups a two-launch step takes with one group of nominal
+// samples a workgroup: compute units hold as many as their 160 KB of LDS have
+// room for, five at most (k_rollout's registers).
+double two_launch_rounds(const Geometry& g, int K) {
+    const size_t per_cu = std::min<size_t>(5, std::max<size_t>(1, kMaxLdsPerCu / g.lds_rollout));
+    return (double)one_launch_grid(g, K) / (256.0 * (double)per_cu);
+}
+
+// The layout of a two-launch step: flattened or not, nominal workgroups packed
+// or not.  Packed ones pay for up to four draws at all sizes (K = 60000, T = 76,
+// M = 3: 101.4 -> 88.7 us; K = 85000, T = 100, M = 4: 187.6 -> 176.7), for
+// five and six where the step takes many rounds of workgroups (K = 85000,
+// T = 134, M = 5, 5.9 rounds: 281.8 -> 260.5 us; T = 76, 2.9 rounds: 139.7 ->
+// 134.8; at 2.1 rounds, K = 60000, 102.7, packed 104.4), and not for more
+// (K = 60000, T = 100, M = 8: 171.5, packed 176.1).
 void set_two_launch(Geometry* g, const mppi_params* p) {
     if (flat_pays(*g, p)) set_flat(g, p);
-    if (p->M < 3) set_nominal_packed(g, p);
+    if (p->M < 5 || (p->M < 7 && two_launch_rounds(*g, p->K) > 2.5)) set_nominal_packed(g, p);
 }
 
 // Serving workgroups of more than four waves that a compute unit starts at

@@ -37,12 +37,12 @@ __device__ __forceinline__ int rollout_item(const StepConst& c) {
     return b < n_dist ? c.n_nom_wg + b : b - n_dist;
 }
 
-template <int kNoise, bool kFuse>
+template <int kNoise, bool kFuse, int kForm>
 __device__ __forceinline__ void rollout_launch_body(const RolloutArgs& a) {
     extern __shared__ float2 smem[];
     const int item = kFuse ? (int)blockIdx.x : rollout_item(a.c);
     if (!kFuse && a.clear && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0u;  // the update launch follows
-    rollout_body<kNoise, !kFuse>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
+    rollout_body<kNoise, kForm>(a.c, a.obs, a.V, a.u, item, smem, [] { return late_view(late_args()); });
     if constexpr (kFuse) {
         __shared__ float red[16];
         __shared__ int flag_sh;
@@ -61,17 +61,19 @@ __device__ __forceinline__ void rollout_launch_body(const RolloutArgs& a) {
 // then holds the per-step constants and keys in vector registers with room
 // for a fifth wave (measured on the large step: 0.71 -> 0.68 ms; the
 // one-launch kernel, whose grid holds two or three waves per SIMD, runs
-// faster with the registers it needs).
-template <int kNoise>
+// faster with the registers it needs).  kPacked: a kernel of its own for
+// packed nominal workgroups, whose code costs the others time even where it
+// does not run (K = 2048, T = 50, M = 64: step 32.5, in one kernel 33.0 us).
+template <int kNoise, bool kPacked>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) k_rollout(RolloutArgs a) {
-    rollout_launch_body<kNoise, false>(a);
+    rollout_launch_body<kNoise, false, kPacked ? kNomDirect : kNomSplit>(a);
 }
 
 // The one-launch step: rollouts, then the update in the workgroups that
 // finish each chunk.
 template <int kNoise>
 __global__ void __launch_bounds__(1024) k_rollout_fused(RolloutArgs a) {
-    rollout_launch_body<kNoise, true>(a);
+    rollout_launch_body<kNoise, true, kNomSplit>(a);
 }
 
 // Persistent serving: the one-launch step in a loop, one iteration per
@@ -116,9 +118,9 @@ __global__ void __launch_bounds__(1024) k_serve(RolloutArgs a, ServeArgs sa_arg)
             float* mean = reinterpret_cast<float*>(smem) + c.mean_off;
             for (int i = threadIdx.x; i < 2 * c.T; i += blockDim.x) mean[i] = agent_load(&p->V[i]);
             __syncthreads();
-            rollout_body<kNoise, kOwn>(c, p->obs, mean, p->u, blockIdx.x, smem, late);
+            rollout_body<kNoise, kOwn ? kNomOwn : kNomSplit>(c, p->obs, mean, p->u, blockIdx.x, smem, late);
         } else {
-            rollout_body<kNoise, kOwn>(c, p->obs, ServedMean{p->V}, p->u, blockIdx.x, smem, late);
+            rollout_body<kNoise, kOwn ? kNomOwn : kNomSplit>(c, p->obs, ServedMean{p->V}, p->u, blockIdx.x, smem, late);
         }
         const RolloutArgs* e = late_args();
         StepConst ce = e->c;
@@ -244,7 +246,7 @@ static RolloutArgs rollout_args(const StepConst& c, const StepBuffers& b, int* r
 
 // (Every launch is checked before the next is made: a launch works on what the
 // one before it has written, so none may follow a failure.)
-template <bool kFuse>
+template <bool kFuse, bool kPacked>
 static hipError_t launch_rollout_t(const StepConst& c, const StepBuffers& b, dim3 grid, int block, size_t lds,
                                    hipStream_t stream, int* ranks, int* tail_idx, const FuseArgs* fa) {
     const RolloutArgs a = rollout_args(c, b, ranks, tail_idx, fa);
@@ -257,19 +259,26 @@ static hipError_t launch_rollout_t(const StepConst& c, const StepBuffers& b, dim
             hipLaunchKernelGGL(k_rollout_fused<0>, grid, dim3(block), lds, stream, a);
     } else {
         if (c.noise_kind == 1)
-            hipLaunchKernelGGL(k_rollout<1>, grid, dim3(block), lds, stream, a);
+            hipLaunchKernelGGL((k_rollout<1, kPacked>), grid, dim3(block), lds, stream, a);
         else if (c.noise_kind == 2)
-            hipLaunchKernelGGL(k_rollout<2>, grid, dim3(block), lds, stream, a);
+            hipLaunchKernelGGL((k_rollout<2, kPacked>), grid, dim3(block), lds, stream, a);
         else
-            hipLaunchKernelGGL(k_rollout<0>, grid, dim3(block), lds, stream, a);
+            hipLaunchKernelGGL((k_rollout<0, kPacked>), grid, dim3(block), lds, stream, a);
     }
     return hipGetLastError();
 }
 
+// The rollouts of a two-launch step.
+static hipError_t launch_rollout_grid(const StepConst& c, const StepBuffers& b, dim3 grid, int block, size_t lds,
+                                      hipStream_t stream, int* ranks, int* tail_idx) {
+    if (c.nom_groups > 1)
+        return launch_rollout_t<false, true>(c, b, grid, block, lds, stream, ranks, tail_idx, nullptr);
+    return launch_rollout_t<false, false>(c, b, grid, block, lds, stream, ranks, tail_idx, nullptr);
+}
+
 hipError_t launch_rollout(const StepConst& c, const StepBuffers& b, int block, size_t lds_rollout, int n_dist_wg,
                           hipStream_t stream, int* ranks, int* tail_idx) {
-    return launch_rollout_t<false>(c, b, dim3(c.n_nom_wg + n_dist_wg), block, lds_rollout, stream, ranks, tail_idx,
-                                   nullptr);
+    return launch_rollout_grid(c, b, dim3(c.n_nom_wg + n_dist_wg), block, lds_rollout, stream, ranks, tail_idx);
 }
 
 hipError_t fused_rollout_capacity(int noise_kind, int block, size_t lds, int* blocks_per_cu) {
@@ -332,12 +341,12 @@ hipError_t launch_step(const StepConst& c, const StepBuffers& b, int block, size
     const dim3 grid((unsigned)(c.n_nom_wg + n_dist));
     if (ev_start) (void)hipEventRecord(ev_start, stream);
     if (fa) {  // one launch: the update runs in the workgroups that finish each chunk
-        const hipError_t e = launch_rollout_t<true>(c, b, grid, block, lds_rollout > lds_update ? lds_rollout : lds_update,
-                                                    stream, nullptr, nullptr, fa);
+        const hipError_t e = launch_rollout_t<true, false>(
+            c, b, grid, block, lds_rollout > lds_update ? lds_rollout : lds_update, stream, nullptr, nullptr, fa);
         if (ev_mid) (void)hipEventRecord(ev_mid, stream);
         return e;
     }
-    hipError_t e = launch_rollout_t<false>(c, b, grid, block, lds_rollout, stream, nullptr, nullptr, nullptr);
+    hipError_t e = launch_rollout_grid(c, b, grid, block, lds_rollout, stream, nullptr, nullptr);
     if (e != hipSuccess) return e;
     if (c.flat && c.n_tail <= kWaveTail) {  // each sample's CVaR from the stored risk costs
         e = launch_cvar_wave(b.L, c.K, c.M, c.n_tail, c.scale_risk, c.B, b.cvar, stream);

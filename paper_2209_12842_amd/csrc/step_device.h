@@ -280,6 +280,11 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
     }
 }
 
+// The forms of a kernel's nominal workgroups.
+constexpr int kNomSplit = 0;   // nominal_rollouts, one group of 64 samples
+constexpr int kNomOwn = 1;     // nominal_rollouts with kOwn: any number of groups
+constexpr int kNomDirect = 2;  // nominal_rollouts_packed: any number of groups
+
 // The nominal rollouts of a workgroup, one sample per lane, in runs of
 // kCullSteps steps whose sampled controls pass through LDS (lanes past K repeat
 // the last sample, since the obstacle test works on whole waves, and write
@@ -293,12 +298,10 @@ __device__ __forceinline__ void cvar_waves(const float* vals, int spb, int M, in
 //    T = 50, M = 64 end at 27 us of the launch instead of 35 us and no longer
 //    finish last (step 37.2 -> 33.4 us with RolloutLate).
 //  - nom_groups > 1 (kOwn): each of the first nom_groups waves draws the
-//    controls of 64 samples of its own and rolls them out.  For served steps
-//    whose grid would not be resident at once otherwise (K = 3900, T = 50,
-//    M = 64: served step 64.1 us; the groups one after the other in the first
-//    form 68.2), and for two-launch steps of one or two draws, where the
-//    nominal rollouts are as much work as the others and three waves out of
-//    four would wait (K = 200000, T = 20, M = 1: 82.4 -> 77.0 us).
+//    controls of 64 samples of its own, a run at a time, and rolls them out.
+//    For served steps whose grid would not be resident at once otherwise
+//    (K = 3900, T = 50, M = 64: served step 64.1 us; the groups one after the
+//    other in the first form 68.2).
 template <bool kOwn, class Mean, class Late>
 __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const Mean& V,
                                                  float2* __restrict__ u_out, int item, float2* smem,
@@ -394,6 +397,82 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const Mean&
     if (act) agent_store(&e.S[k], S);
 }
 
+// The nominal rollouts of a two-launch step's packed workgroups: a wave for
+// each 64 samples, every lane drawing its sample's controls as it rolls them
+// out (lanes past K as above).  A workgroup takes the LDS that the disturbed
+// ones need, so where these fill it a nominal workgroup costs the place of one
+// of them, whether four of its waves roll out samples or one does
+// (K = 60000, T = 76, M = 3, 65 obstacles: step 115.6 -> 98.9 us); and where
+// nominal rollouts are a good part of the work, the three waves that only draw
+// ahead wait (K = 200000, T = 22, M = 1: 82.4 -> 78.3 us).  Drawing a run ahead
+// through LDS instead, as in nominal_rollouts, is slower (102.2 and 80.6 us).
+template <class Late>
+__device__ __forceinline__ void nominal_rollouts_packed(const StepConst& c, const float* V,
+                                                        float2* __restrict__ u_out, int item, float2* smem,
+                                                        const float4* otab, const float4* gbox, int n_grp,
+                                                        int& n_cand, int& n_gtest, Late late) {
+    const int T = c.T;
+    float* vsh = reinterpret_cast<float*>(smem);  // the mean sequence: no step waits for a global load
+    for (int i = threadIdx.x; i < 2 * T; i += blockDim.x) vsh[i] = V[i];
+    __syncthreads();  // the mean sequence and the table staged
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int k0 = (item * c.nom_groups + wave) * 64;
+    const bool rolls = wave < c.nom_groups && k0 < c.K;
+    const int lane = threadIdx.x & 63;
+    const int k = k0 + lane;
+    const bool act = k < c.K;
+    const bool store = act && c.store_u;
+    const int kc = act ? k : c.K - 1;
+    const float4 first = n_grp > 0 ? (n_grp == 1 ? otab : gbox)[lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    State s{0.0f, 0.0f, c.psi0, c.v0};
+    float acc = 0.0f, ctrl = 0.0f;
+    int cnt = 0;
+    const StepConst cn = with_vector_constants(c);
+    auto step = [&](auto bdry, int t, float& px, float& py) {
+        const float2 u = sample_control(c, vsh, kc, t);
+        if (store) u_out[(size_t)t * c.K + k] = u;
+        acc = smooth_cost_acc<decltype(bdry)::value>(cn, s, acc);
+        px = s.x;
+        py = s.y;
+        const float term = __fmaf_rn(vsh[2 * t] * c.inv_var0, u.x, vsh[2 * t + 1] * c.inv_var1 * u.y);
+        ctrl = __fmaf_rn(c.gamma, term, ctrl);
+        bicycle_step(s, c.dt * u.x, tan_steer(u.y) * c.inv_wheelbase, cn.dt);
+    };
+    for (int t0 = 0; rolls && t0 < T; t0 += kCullSteps) {
+        float px[kCullSteps], py[kCullSteps];
+        const int n = min(kCullSteps, T - t0);
+        if (n == kCullSteps) {  // a whole run of steps with no branch between them
+            if (c.use_bdry) {
+#pragma unroll
+                for (int i = 0; i < kCullSteps; ++i) step(kTrue, t0 + i, px[i], py[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kCullSteps; ++i) step(kFalse, t0 + i, px[i], py[i]);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kCullSteps; ++i) {
+                if (i < n) {
+                    if (c.use_bdry)
+                        step(kTrue, t0 + i, px[i], py[i]);
+                    else
+                        step(kFalse, t0 + i, px[i], py[i]);
+                } else {
+                    px[i] = px[i > 0 ? i - 1 : 0];
+                    py[i] = py[i > 0 ? i - 1 : 0];
+                }
+            }
+        }
+        if (n_grp > 0) cnt += obstacle_hits_culled<kCullSteps>(otab, n_grp, first, px, py, n, n_cand, n_gtest);
+    }
+    if (!rolls) return;
+    const RolloutLate e = late();
+    float S = __fmaf_rn(e.c->c_obs, (float)cnt, acc);
+    if (e.c->use_ctrl) S += ctrl;
+    if (e.c->use_term) S += terminal_cost(c, s);
+    if (act) agent_store(&e.S[k], S);
+}
+
 // Adds a wave's broad-phase work to its slot of the counters (timing mode).
 __device__ __forceinline__ void count_work(unsigned long long* work, int item, int n_cand, int n_gtest) {
     if (work && (threadIdx.x & 63) == 0) {
@@ -407,7 +486,7 @@ __device__ __forceinline__ void count_work(unsigned long long* work, int item, i
 // nominal workgroup (one lane per sample), otherwise a disturbed workgroup
 // (spb samples of M lanes).  Ends with every lane past its last LDS access
 // (the caller may reuse the LDS after a barrier).
-template <int kNoise, bool kOwn, class Mean, class Late>
+template <int kNoise, int kForm, class Mean, class Late>
 __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __restrict__ obs, const Mean& V,
                                              float2* __restrict__ u_out, int item, float2* smem, Late late) {
     float2* ctl = smem;
@@ -422,7 +501,10 @@ __device__ __forceinline__ void rollout_body(const StepConst& c, const float* __
     int n_gtest = 0;  // broad-phase group tests of this wave (wave-uniform)
 
     if (item < c.n_nom_wg) {
-        nominal_rollouts<kOwn>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
+        if constexpr (kForm == kNomDirect)
+            nominal_rollouts_packed(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
+        else
+            nominal_rollouts<kForm == kNomOwn>(c, V, u_out, item, smem, otab, gbox, n_grp, n_cand, n_gtest, late);
         count_work(late().work, item, n_cand, n_gtest);
         return;
     }

@@ -51,7 +51,9 @@ def test_forms(K, M, per_cu):
     assert lds <= 64 * 1024
 
 
-@pytest.mark.parametrize("K,M,grid", [(200000, 1, 782 + 782), (80001, 2, 626 + 313), (100000, 3, 1177 + 1563)])
+@pytest.mark.parametrize("K,M,grid", [(200000, 1, 782 + 782), (80001, 2, 626 + 313), (100000, 3, 1177 + 391),
+                                      (100000, 4, 1563 + 391), (100000, 5, 1961 + 391), (80000, 5, 1569 + 1250),
+                                      (110000, 6, 2620 + 430), (60000, 6, 1429 + 938), (120000, 7, 3334 + 1875)])
 def test_few_draws_pack_their_nominal_workgroups(K, M, grid):
     step, _, _, got = fake_hip.run("test_nominal_forms_cpu", "launches(%d, %d, 4)" % (K, M))
     assert step == TWO and got == grid

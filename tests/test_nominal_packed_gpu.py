@@ -43,7 +43,9 @@ def test_packed_sessions_follow_launched_steps(world, kw):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("world,kw", [("c2", dict(K=1, T=1, M=1)), ("c2", dict(K=65, T=5, M=2)), ("p0", dict(K=256, T=6, M=1)),
-                                      ("c2", dict(K=257, T=13, M=2, n_obs=70)), ("p0", dict(K=3000, T=18, M=2, noise_kind=1))])
+                                      ("c2", dict(K=257, T=13, M=2, n_obs=70)), ("p0", dict(K=3000, T=18, M=2, noise_kind=1)),
+                                      ("c2", dict(K=1021, T=17, M=3)), ("p0", dict(K=768, T=8, M=4, n_obs=130)),
+                                      ("c2", dict(K=330, T=9, M=4, n_obs=0, c_bdry=1.0, noise_kind=2, jump_prob=0.2, jump_size=0.4))])
 def test_packed_two_launch_steps(world, kw):
     import paper_2209_12842_amd as ra
     from paper_2209_12842_amd import workloads as W
@@ -59,3 +61,24 @@ def test_packed_two_launch_steps(world, kw):
         c.close()
     for k in out[0]:
         assert np.array_equal(out[0][k], out[1][k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [dict(K=100001, T=3, M=5), dict(K=120000, T=9, M=6, n_obs=70, noise_kind=1)])
+def test_packed_steps_of_many_rounds(kw):
+    """The first samples of a large step against the one-launch step of these
+    samples alone (all of them warm, so a sample depends on its index only)."""
+    import paper_2209_12842_amd as ra
+    from paper_2209_12842_amd import workloads as W
+    out = []
+    for K in (kw["K"], 300):
+        w = W.make_world("c2", lam=50.0, eta=0.0, **dict(kw, K=K))
+        c = ra.Controller(w["params"], w["obstacles"], debug=True)
+        c.step(w["x0"], c.new_V(W.random_V(kw["T"], 3)), 5)
+        torch.cuda.synchronize()
+        d = c.debug()
+        assert torch.isfinite(d["S"]).all()
+        out.append((d["S"][:300].cpu().numpy(), d["cvar"][:300].cpu().numpy(), d["u"].cpu().numpy().reshape(kw["T"], K, 2)[:, :300]))
+        c.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
