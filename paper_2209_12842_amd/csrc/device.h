@@ -652,13 +652,16 @@ __device__ __forceinline__ float terminal_cost(const StepConst& c, const State& 
 // lane's rank counts the strictly larger values plus the equal values with a
 // smaller index, so ranks are a permutation of 0..M-1 and the n_tail largest
 // values land, in descending order, in tail[0..n_tail-1].  The caller
-// synchronises the workgroup between this and tail_sum.
+// synchronises the workgroup between this and tail_sum.  With kNanFirst a value
+// that is not a number comes before all others and has rank M itself, so that
+// tail[0] is not written where there is one.
+template <bool kNanFirst = false>
 __device__ __forceinline__ int tail_rank_scatter(const float* vals, float* tail, int M, int m, int n_tail) {
     const float v = vals[m];
     int rank = 0;
     for (int j = 0; j < M; ++j) {
         const float o = vals[j];
-        rank += (o > v) | ((o == v) & (j < m));
+        rank += (kNanFirst ? !(o <= v) : o > v) | ((o == v) & (j < m));
     }
     if (rank < n_tail) tail[rank] = v;
     return rank;

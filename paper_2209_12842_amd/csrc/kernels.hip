@@ -163,6 +163,11 @@ __global__ void k_normals(uint32_t key0, uint32_t key1, const uint4* __restrict_
     out[i] = normals4(philox4x32_10(cc.x, cc.y, cc.z, cc.w, key0, key1));
 }
 
+// The CVaR of risk costs in memory where the wave pass does not pay
+// (wave_tail_pays).  A cost that is not a number makes the CVaR one: ranks put
+// it first, the sort of M = 64 may lose it and its wave, a sample, looks for it
+// (kOneWave; in one kernel with the others K = 300000, M = 12: 13.3 -> 13.8 us).
+template <bool kOneWave>
 __global__ void __launch_bounds__(1024) k_cvar(const float* __restrict__ L, int K, int M, int spb, int n_tail,
                                                int scale_risk, float B, float* __restrict__ cvar_out) {
     extern __shared__ float csh[];
@@ -174,11 +179,14 @@ __global__ void __launch_bounds__(1024) k_cvar(const float* __restrict__ L, int 
     const int m = tid - sl * M;
     const int k = blockIdx.x * spb + sl;
     const bool active = (sl < spb) && (k < K);
+    float v = 0.0f;
     if (sl < spb) {
-        vals[tid] = active ? L[(size_t)k * M + m] : 0.0f;
+        if (active) v = L[(size_t)k * M + m];
+        vals[tid] = v;
         tail[tid] = __builtin_nanf("");
     }
-    const float cv = cvar_epilogue(vals, tail, means, spb, M, n_tail, scale_risk, B);
+    float cv = cvar_epilogue<true>(vals, tail, means, spb, M, n_tail, scale_risk, B);
+    if (kOneWave && __builtin_amdgcn_ballot_w64(v != v)) cv = __builtin_nanf("");
     if (active && m == 0) cvar_out[k] = cv;
 }
 
@@ -379,12 +387,31 @@ hipError_t launch_normals(uint64_t seed, const uint32_t* ctr, float* out, int64_
     return hipGetLastError();
 }
 
+// Whether the CVaR of risk costs in memory goes to the wave pass (a wave sorts
+// 64 values at 64 / M samples a time and adds each tail one value after the
+// other) or to k_cvar (M values a sample, M comparisons each or a bitonic sort
+// over the workgroup, all lanes used).  The wave pass gains where a segment's
+// lanes are used and the tail is short: of K M = 4e6 costs, M = 32, n_tail = 3
+// 25.1 -> 17.4 us; M = 48, 12 values (K = 65536) 24.1 -> 22.5; M = 64, 32 values
+// 32.2 -> 27.7; M = 100, 10 values 61.1 -> 21.9.  It loses where lanes idle
+// (M = 6: 7.4, by waves 9.8; 24: 18.9, 22.4; 40: 25.8, 28.8) or the tail is long
+// (M = 48, n_tail = 32: 30.2, 35.8; 64, 64: 34.4, 43.6; 65, 64: 46.5, 48.4).
+static bool wave_tail_pays(int M, int n_tail) {
+    if (n_tail > kWaveTail) return false;
+    if (M > 64 || M <= 4) return n_tail <= max(4, M - 16);
+    if (M == tail_lanes(M)) return n_tail <= 32;
+    return M >= 48 && n_tail <= min(32, 3 * (M - 44));
+}
+
 hipError_t launch_cvar(const float* L, int K, int M, int spb, int block, int n_tail, int scale_risk, float B,
                        float* out, hipStream_t stream) {
-    if (n_tail <= kWaveTail) return launch_cvar_wave(L, K, M, n_tail, scale_risk, B, out, stream);
+    if (wave_tail_pays(M, n_tail)) return launch_cvar_wave(L, K, M, n_tail, scale_risk, B, out, stream);
     const int blocks = (K + spb - 1) / spb;
     const size_t lds = sizeof(float) * (size_t)(2 * spb * M + spb);
-    hipLaunchKernelGGL(k_cvar, dim3(blocks), dim3(block), lds, stream, L, K, M, spb, n_tail, scale_risk, B, out);
+    if (M == 64)
+        hipLaunchKernelGGL(k_cvar<true>, dim3(blocks), dim3(block), lds, stream, L, K, M, spb, n_tail, scale_risk, B, out);
+    else
+        hipLaunchKernelGGL(k_cvar<false>, dim3(blocks), dim3(block), lds, stream, L, K, M, spb, n_tail, scale_risk, B, out);
     return hipGetLastError();
 }
 

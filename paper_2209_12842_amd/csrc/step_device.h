@@ -194,6 +194,8 @@ constexpr int kWorkSlots = 256;
 // lanes of a sample cover every draw once.  tid is the thread's index in the
 // workgroup (a caller may pass a copy the compiler cannot tie to values it
 // derived from the index earlier).
+// kNanFirst: see tail_rank_scatter (the sort leaves such values anywhere).
+template <bool kNanFirst = false>
 __device__ __forceinline__ float cvar_epilogue(float* vals, float* tail, float* means, int spb, int M,
                                                int n_tail, int scale_risk, float B, int* pos_out = nullptr,
                                                int* id_out = nullptr, int tid = (int)threadIdx.x) {
@@ -233,7 +235,7 @@ __device__ __forceinline__ float cvar_epilogue(float* vals, float* tail, float* 
         if (pos_out) *pos_out = m;
         if (id_out) *id_out = id;
     } else if (own) {
-        const int rank = tail_rank_scatter(vals + sl * M, tail + sl * M, M, m, n_tail);
+        const int rank = tail_rank_scatter<kNanFirst>(vals + sl * M, tail + sl * M, M, m, n_tail);
         if (pos_out) *pos_out = rank;
         if (id_out) *id_out = m;
     }
@@ -403,9 +405,10 @@ __device__ __forceinline__ void nominal_rollouts(const StepConst& c, const Mean&
 // ones need, so where these fill it a nominal workgroup costs the place of one
 // of them, whether four of its waves roll out samples or one does
 // (K = 60000, T = 76, M = 3, 65 obstacles: step 115.6 -> 98.9 us); and where
-// nominal rollouts are a good part of the work, the three waves that only draw
-// ahead wait (K = 200000, T = 22, M = 1: 82.4 -> 78.3 us).  Drawing a run ahead
-// through LDS instead, as in nominal_rollouts, is slower (102.2 and 80.6 us).
+// nominal rollouts are a good part of the work, three waves of four that only
+// draw ahead wait (K = 200000, T = 20, M = 1: 82.4 us).  Drawing a run ahead
+// through LDS, as nominal_rollouts does, is slower (102.2 us; and K = 200000,
+// T = 22, M = 1: 80.6, here 78.3 us).
 template <class Late>
 __device__ __forceinline__ void nominal_rollouts_packed(const StepConst& c, const float* V,
                                                         float2* __restrict__ u_out, int item, float2* smem,

@@ -56,3 +56,23 @@ def test_infinite_and_undefined_costs(M):
     ref[3] = np.nan
     out = ra.cvar(torch.as_tensor(L).cuda(), 0.9).cpu().numpy()
     assert np.array_equal(out, ref, equal_nan=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [1.0, 2.0])
+@pytest.mark.parametrize("M,alpha", [(3, 0.01), (4, 0.01), (5, 0.01), (5, 0.9), (40, 0.5), (47, 0.9), (48, 0.76), (48, 0.73), (52, 0.55),
+                                     (54, 0.45), (55, 0.42), (55, 0.4), (64, 0.52), (64, 0.48), (65, 0.25), (65, 0.2)])
+def test_either_side_of_the_pass_rule(M, alpha, B):
+    """Bits at the sizes where the entry point changes from one pass to the
+    other; a cost that is not a number makes its sample's CVaR one in both."""
+    import paper_2209_12842_amd as ra
+    rng = np.random.default_rng(M)
+    L = rng.gamma(2.0, 50.0, (531, M)).astype(np.float32)
+    L[:200] = np.round(L[:200])
+    undefined = {7: 0, 8: M // 2, 530: M - 1}
+    ref, n_tail = reference(L, alpha, B)
+    for k, m in undefined.items():
+        L[k, m] = np.nan
+        ref[k] = np.nan
+    out = ra.cvar(torch.as_tensor(L).cuda(), alpha, B).cpu().numpy()
+    assert np.array_equal(out, ref, equal_nan=True), n_tail
