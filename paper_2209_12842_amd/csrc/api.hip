@@ -141,22 +141,30 @@ double idle_lane_us(const Geometry& g, const mppi_params* p) {
     return (double)p->K * p->M * p->T * (1.0 / used - 1.0) / 3.4e5;
 }
 
+// Workgroups of the one-launch step.
+int64_t one_launch_grid(const Geometry& g, int K) { return g.n_nom_wg + ((int64_t)K + g.spb - 1) / g.spb; }
+
 // Whether a two-launch step takes the flattened layout: more than 256 draws
 // (a sample then needs five or more waves, and only three such workgroups
 // start on a compute unit at once), or draw counts that leave enough lanes
 // idle to pay for the CVaR pass and its launch, about 6 us (K = 4000, T = 60,
 // M = 100, 200 of 256 lanes: step 93 -> 83 us).  The gradient keeps the per-sample layout
-// (its tail ranks come from the rollout's own CVaR pass).
+// (its tail ranks come from the rollout's own CVaR pass), and so do small grids
+// (five-wave workgroups that all start at once) of long horizons among many
+// obstacles under impulses: a sample's draws then stay close together, so that
+// a wave of one sample meets few obstacles and one of two samples' draws many
+// (K = 150, T = 270, M = 300, 200 obstacles: 258 us flattened, 162 per sample;
+// T = 120 67 and 65; 65 obstacles, T = 270 133 and 109, T = 200 84 and 85).
 bool flat_pays(const Geometry& g, const mppi_params* p) {
     if (p->flags & MPPI_F_GRAD) return false;
     Geometry f = g;
     set_flat(&f, p);
     if (f.lds_rollout > kMaxLdsBytes) return false;  // it holds the controls of more samples
+    if (p->M > 256 && p->M < 320 && p->noise_kind == MPPI_NOISE_IMPULSE && p->n_obs > 64 &&
+        p->T * ramppi::rollout_n_grp(p->n_obs) >= 500 && one_launch_grid(g, p->K) <= 512)
+        return false;
     return p->M > 256 || idle_lane_us(g, p) > 8.0;
 }
-
-// Workgroups of the one-launch step.
-int64_t one_launch_grid(const Geometry& g, int K) { return g.n_nom_wg + ((int64_t)K + g.spb - 1) / g.spb; }
 
 // Nominal workgroups of a wave for each 64 samples, as many as the workgroup
 // has (eight at most, for the LDS of their controls).

@@ -4,7 +4,7 @@ import ctypes
 import pytest
 
 import fake_hip
-from flat_cases import FLAT, PER_SAMPLE
+from flat_cases import FLAT, IMPULSE, PER_SAMPLE
 
 
 def kernels(kw, noalloc):
@@ -25,3 +25,10 @@ def kernels(kw, noalloc):
 def test_layout(kw, flat, noalloc):
     got = fake_hip.run("test_flat_route_cpu", "kernels(%r, %r)" % (kw, noalloc))
     assert any(k.startswith("k_cvar") for k in got) == flat
+
+
+@pytest.mark.parametrize("K,T,M,n_obs", list(IMPULSE))
+def test_impulses_on_the_callers_memory(K, T, M, n_obs):
+    kw = dict(K=K, T=T, M=M, n_obs=n_obs, noise_kind=2, jump_prob=0.1, jump_size=0.4)
+    got = fake_hip.run("test_flat_route_cpu", "kernels(%r, True)" % (kw,))
+    assert any(k.startswith("k_cvar") for k in got) == IMPULSE[(K, T, M, n_obs)]

@@ -5,7 +5,7 @@ does not fit take the per-sample one there too."""
 import numpy as np
 import pytest
 
-from flat_cases import FLAT
+from flat_cases import FLAT, IMPULSE
 from paper_2209_12842_amd import workloads as W
 
 torch = pytest.importorskip("torch")
@@ -48,3 +48,18 @@ def test_long_horizons_on_the_callers_memory(kw):
     R.step_noalloc(w["params"], obs, w["x0"], out[-1], 2)
     torch.cuda.synchronize()
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,T,M,n_obs", list(IMPULSE)[:5])
+def test_impulses_on_the_callers_memory(K, T, M, n_obs):
+    import paper_2209_12842_amd as R
+    w = W.make_world("c2", lam=50.0, K=K, T=T, M=M, n_obs=n_obs, noise_kind=2, jump_prob=0.1, jump_size=0.4)
+    c = R.Controller(w["params"], w["obstacles"])
+    V = c.new_V(W.random_V(T, 5))
+    Vn = V.clone()
+    c.step(w["x0"], V, 9)
+    R.step_noalloc(w["params"], torch.as_tensor(w["obstacles"]).cuda(), w["x0"], Vn, 9)
+    torch.cuda.synchronize()
+    assert torch.equal(V, Vn)
+    c.close()
