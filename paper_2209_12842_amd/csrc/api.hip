@@ -194,11 +194,13 @@ void set_two_launch(Geometry* g, const mppi_params* p) {
     if (p->M < 5 || (p->M < 7 && two_launch_rounds(*g, p->K) > 2.5)) set_nominal_packed(g, p);
 }
 
-// Serving workgroups of more than four waves that a compute unit starts at
-// once: k_serve holds four waves per SIMD, and one SIMD takes the waves of every
-// workgroup that do not share out evenly.  The occupancy query counts waves over
-// the unit (five-wave workgroups, M = 257 to 320: three, of which two start, and
-// a session of 518 never had its whole grid resident).
+// Workgroups of more than four waves of a one-launch or served step that a
+// compute unit starts at once: its SIMDs hold four waves each, and one SIMD takes
+// the waves of every workgroup that do not share out evenly.  The occupancy query
+// counts waves over the unit: for five-wave workgroups (M = 257 to 320) three, of
+// which two start.  A session of 518 never had its whole grid resident, and steps
+// of 513 to 768 are faster flattened in two launches (T = 60, M = 300, 200
+// obstacles, impulses: K = 748 77.9 us in one launch, K = 760 56.5 in two).
 int simd_workgroups(int block) {
     const int waves = block / 64;
     return waves > 4 ? std::max(1, 4 / ((waves + 3) / 4)) : 16;
@@ -584,6 +586,7 @@ mppi_status mppi_create(const mppi_params* p, const float* obstacles_host, void*
         e = ramppi::fused_rollout_capacity((int)p->noise_kind, h->g.block,
                                            std::max(h->g.lds_rollout, h->g.lds_update), &per_cu);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+        per_cu = std::min(per_cu, simd_workgroups(h->g.block));
         h->fuse = e == hipSuccess && one_launch_grid(h->g, p->K) <= (int64_t)per_cu * n_cu;
         fa.chunk_ctr = reinterpret_cast<unsigned*>(h->ws + l.chunk);
         fa.counter = reinterpret_cast<unsigned*>(h->ws + l.counter);

@@ -17,8 +17,11 @@ CASES = {  # (K, M, waves per SIMD): the step's kernels, the served grid or None
     (14000, 16, 4): (TWO, 875 + 55),
     (511, 512, 4): (FLAT, 511 + 1),
     (504, 300, 4): (["k_rollout_fused"], 504 + 8),   # five waves: two on one SIMD, so two workgroups a unit, not three
-    (510, 300, 4): (["k_rollout_fused"], 510 + 2),
-    (512, 300, 4): (["k_rollout_fused"], None),
+    (505, 300, 4): (FLAT, 505 + 2),                  # 505 + 8 is one too many
+    (510, 300, 4): (FLAT, 510 + 2),
+    (512, 300, 4): (FLAT, None),
+    (504, 320, 4): (["k_rollout_fused"], 504 + 8),
+    (512, 321, 4): (FLAT, None),                     # six waves: two workgroups a unit
     (2400, 90, 4): (["k_rollout_fused"], 1200 + 38),  # three waves
     (254, 1024, 4): (["k_rollout", "k_cvar_sorted", "k_update"], 254 + 1),
 }
