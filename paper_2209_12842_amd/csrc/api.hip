@@ -834,6 +834,14 @@ mppi_status mppi_serve_start(mppi_handle* h, float* V_dev, uint32_t idle_ms, voi
     ramppi::ServeArgs sa;
     sa.req_host = reinterpret_cast<const ramppi::ServeReq*>(h->u0_pinned_dev + kServeOffset / 4);
     sa.req_dev = reinterpret_cast<ramppi::ServeReq*>(sv);
+    // Waiting workgroups read the request again without a pause where a step is
+    // few chunks (K = 2048, T = 50, M = 64, 8 chunks: 34.7 us, with pauses 34.8),
+    // and about every microsecond where many chunks are counted, updated and
+    // merged while others wait: their reads, and workgroup 0's of host memory,
+    // then slowed that down by up to 20 us at some grid sizes (K = 30000, T = 8,
+    // M = 1, 118 chunks: 43.8 -> 28.0 us; K = 7700, T = 11, M = 7, 31 chunks: 32.6
+    // -> 25.0; at others the pauses cost 1 to 2 us, K = 20000, M = 1: 22.6, 24.2).
+    sa.naps = h->g.G > 24 ? 4u : 0u;
     sa.idle_ticks = 100000ull * idle_ms;  // s_memrealtime runs at 100 MHz
 
     // a new session: requests and completions count from 1 again

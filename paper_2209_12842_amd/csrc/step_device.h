@@ -1192,6 +1192,7 @@ __host__ __device__ __forceinline__ uint64_t serve_word(uint32_t seq, uint32_t v
 struct ServeArgs {
     const ServeReq* req_host;  // mapped host memory (device address)
     ServeReq* req_dev;         // device copy read by the other workgroups
+    uint32_t naps;             // sleeps of 640 clocks added between two reads of either
     uint64_t idle_ticks;       // longest wait for a request (s_memrealtime ticks, 100 MHz)
 };
 
@@ -1231,6 +1232,7 @@ __device__ __forceinline__ bool serve_wait(const ServeArgs& sa, unsigned seq, bo
         leave = __builtin_amdgcn_s_memrealtime() - t0 > limit;
         if (leave) break;
         __builtin_amdgcn_s_sleep(1);
+        for (uint32_t n = sa.naps; n > 0u; --n) __builtin_amdgcn_s_sleep(10);
     }
     if (threadIdx.x < kServeFields) {
         if (leader)
